@@ -255,16 +255,20 @@ int check_geometry(const ebsd_geometry* geo) {
 bool g_timing = false;
 std::vector<std::pair<hipEvent_t, hipEvent_t>> g_events;
 
-// Constant operands of the search form: the split DFT-GEMM fragments, or the
-// phase tables of the exact FP32 DFT form (built here); none for the FFT form.
+// Constant operands of the search form: the DFT-GEMM fragments (split, or FP32
+// for the exact DFT form at max_shift <= 31), or the phase tables of the exact
+// FP32 DFT form over wider windows (built here); none for the FFT form.
 struct SearchConsts {
   unsigned short* frag = nullptr;
   float2* wtab = nullptr;
 };
 
 int search_consts(int n, const ebsd_params& p, Arena& ws, hipStream_t st, SearchConsts* c) {
-  if (p.form == EBSD_FORM_DFTGEMM) {
-    EBSD_ALLOC(f, unsigned short, gemm_frag_bytes(n, p.max_shift) / 2, ws);
+  const bool split = p.form == EBSD_FORM_DFTGEMM;
+  if (split || (p.form == EBSD_FORM_DFT && even_supported(n, p.max_shift))) {
+    const size_t bytes = split && p.precision != EBSD_PREC_FP16X2 ? gemm_frag_bytes(n, p.max_shift)
+                                                                  : even_frag_bytes(n, p.max_shift);
+    EBSD_ALLOC(f, unsigned short, bytes / 2, ws);
     c->frag = f;
   } else if (p.form == EBSD_FORM_DFT) {
     EBSD_ALLOC(t, float2, window_table_size(n, p.max_shift), ws);
@@ -275,24 +279,27 @@ int search_consts(int n, const ebsd_params& p, Arena& ws, hipStream_t st, Search
 }
 
 // The search in the requested form: FFT (FP32), split-precision DFT-GEMM, or
-// the exact FP32 DFT over the shift window.
+// the exact FP32 DFT over the shift window (disc: the spectra are this
+// library's own, zero outside the filter's disc).
 hipError_t launch_search(int n, const ebsd_params& prm, const float2* sp, int64_t p, const float2* sl, int64_t l,
-                         const SearchConsts& c, float* out, hipStream_t st) {
+                         const SearchConsts& c, bool disc, float* out, hipStream_t st) {
   if (prm.form == EBSD_FORM_DFTGEMM)
     return launch_xcf_gemm(n, prm.precision - 1, sp, p, sl, l, prm.max_shift, c.frag, out, st);
+  if (prm.form == EBSD_FORM_DFT && c.frag)
+    return launch_xcf_even(n, false, disc, sp, p, sl, l, prm.max_shift, c.frag, out, st);
   if (prm.form == EBSD_FORM_DFT) return launch_window_scores(n, sp, p, sl, l, prm.max_shift, c.wtab, out, st);
   return launch_xcf_scores(n, sp, p, sl, l, prm.max_shift, out, st);
 }
 
 hipError_t timed_scores(int n, const ebsd_params& prm, const float2* sp, int64_t p, const float2* sl, int64_t l,
-                        const SearchConsts& frag, float* out, hipStream_t st) {
-  if (!g_timing) return launch_search(n, prm, sp, p, sl, l, frag, out, st);
+                        const SearchConsts& frag, bool disc, float* out, hipStream_t st) {
+  if (!g_timing) return launch_search(n, prm, sp, p, sl, l, frag, disc, out, st);
   hipEvent_t a, b;
   hipError_t e;
   if ((e = hipEventCreate(&a)) != hipSuccess) return e;
   if ((e = hipEventCreate(&b)) != hipSuccess) return e;
   if ((e = hipEventRecord(a, st)) != hipSuccess) return e;
-  if ((e = launch_search(n, prm, sp, p, sl, l, frag, out, st)) != hipSuccess) return e;
+  if ((e = launch_search(n, prm, sp, p, sl, l, frag, disc, out, st)) != hipSuccess) return e;
   if ((e = hipEventRecord(b, st)) != hipSuccess) return e;
   g_events.emplace_back(a, b);
   return hipSuccess;
@@ -320,7 +327,7 @@ int index_against(int n, const ebsd_params& p, const float* pats, int64_t P, con
   if (int e = pattern_spectra(n, p, pats, P, fp, spec_p, nullptr, ws, st)) return e;
   SearchConsts consts;
   if ((rc = search_consts(n, p, ws, st, &consts))) return rc;
-  EBSD_TRY(timed_scores(n, p, spec_p, P, spec_l, L, consts, sc_out, st), "xcf_scores");
+  EBSD_TRY(timed_scores(n, p, spec_p, P, spec_l, L, consts, true, sc_out, st), "xcf_scores");
   EBSD_TRY(launch_library_argmax(sc_out, P, L, best_idx, h_int, st), "library_argmax");
   if (int e = do_peak(n, p, spec_p, spec_l, nullptr, best_idx, P, h_tmp, s_int, ws, st)) return e;
   EBSD_TRY(launch_subpixel_tables(n, p.upsample, roots, st), "subpixel tables");
@@ -473,7 +480,8 @@ int ebsd_xcf_scores(const float* spec_p, int64_t P, const float* spec_l, int64_t
   Scratch ws(st);
   SearchConsts consts;
   if ((rc = search_consts(n, p, ws, st, &consts))) return rc;
-  EBSD_TRY(timed_scores(n, p, (const float2*)spec_p, P, (const float2*)spec_l, L, consts, scores, st), "xcf_scores");
+  EBSD_TRY(timed_scores(n, p, (const float2*)spec_p, P, (const float2*)spec_l, L, consts, false, scores, st),
+           "xcf_scores");
   return EBSD_OK;
 }
 

@@ -108,6 +108,15 @@ size_t gemm_frag_bytes(int n, int max_shift);
 hipError_t launch_xcf_gemm(int n, int precision, const float2* spec_p, int64_t p, const float2* spec_l,
                            int64_t l, int max_shift, unsigned short* frag, float* scores, hipStream_t stream);
 
+// Windowed search with the +-u and +-s symmetries of the phase factors used (max_shift <= 31): the
+// products in FP32, or split into FP16 hi + lo halves (what launch_xcf_gemm runs for precision 0).
+// `disc`: the spectra are zero outside the filter's disc (every spectrum written here is; a caller's
+// own may not be).  `frag` is scratch of even_frag_bytes(n, max_shift) bytes.
+bool even_supported(int n, int max_shift);
+size_t even_frag_bytes(int n, int max_shift);
+hipError_t launch_xcf_even(int n, bool split, bool disc, const float2* spec_p, int64_t p, const float2* spec_l,
+                           int64_t l, int max_shift, void* frag, float* scores, hipStream_t stream);
+
 // Best template per pattern from the score matrix (ties: smallest index).
 hipError_t launch_library_argmax(const float* scores, int64_t p, int64_t l, int32_t* best,
                                  float* best_h, hipStream_t stream);

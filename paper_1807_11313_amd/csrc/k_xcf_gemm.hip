@@ -7,9 +7,9 @@
 //   stage 2  rho(s_y, s_x) = Re sum_v A(s_y, v) C(v, s_x), C = w_v exp(+2 pi i v s_x / N)
 // with Z = E conj(T) over the stored band (u in [-B, B], v in [0, B]) and
 // w_0 = 1, w_v = 2 (Hermitian half).  Both run on MFMA with every operand
-// split into two 16-bit halves, x = x_hi + x_lo (FP16 or BF16), products
-// formed as hi*hi + hi*lo + lo*hi and accumulated in FP32; the BF16 form
-// without the lo halves is the one-product variant.
+// split into two BF16 halves, x = x_hi + x_lo, products formed as
+// hi*hi + hi*lo + lo*hi and accumulated in FP32, or without the lo halves (the
+// one-product variant).  The FP16 hi + lo form runs in k_xcf_even.hip.
 //
 // Stage 1 is computed transposed, A^T (v x s_y) = Z^T W1, with Z^T as the
 // A operand of v_mfma_f32_16x16x32 (lane l: row v = l % 16, k = 8 (l / 16) + j)
@@ -30,8 +30,6 @@
 
 namespace ebsd {
 
-typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h4 __attribute__((ext_vector_type(4)));
 typedef __bf16 b8 __attribute__((ext_vector_type(8)));
 typedef short s4 __attribute__((ext_vector_type(4)));
 typedef unsigned u4v __attribute__((ext_vector_type(4)));
@@ -39,8 +37,7 @@ typedef unsigned u2v __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
 // Z (and the stage-1 output) is scaled by 2^12 before splitting so that the
-// lo halves of typical band coefficients stay in the FP16 normal range, while
-// |A| <= 2^12 sum_u |E||T| <= 2^11 stays far below the FP16 maximum.
+// small band coefficients stay clear of the denormal range (a power of two: exact).
 constexpr float kZScale = 4096.0f;
 constexpr float kZUnscale = 1.0f / 4096.0f;
 
@@ -93,53 +90,23 @@ struct GemmLay {
 };
 
 // ---------------------------------------------------------------------------
-// 16-bit halves: PREC 0 = FP16 hi + lo, 1 = BF16 hi + lo, 2 = BF16 hi only.
-template <int PREC>
+// 16-bit halves: PREC 1 = BF16 hi + lo, 2 = BF16 hi only.
 __device__ __forceinline__ void split2(float x, unsigned short& hi, unsigned short& lo) {
-  if constexpr (PREC == 0) {
-    const _Float16 h = (_Float16)x;
-    const _Float16 l = (_Float16)(x - (float)h);
-    hi = __builtin_bit_cast(unsigned short, h);
-    lo = __builtin_bit_cast(unsigned short, l);
-  } else {
-    const __bf16 h = (__bf16)x;
-    const __bf16 l = (__bf16)(x - (float)h);
-    hi = __builtin_bit_cast(unsigned short, h);
-    lo = __builtin_bit_cast(unsigned short, l);
-  }
+  const __bf16 h = (__bf16)x;
+  const __bf16 l = (__bf16)(x - (float)h);
+  hi = __builtin_bit_cast(unsigned short, h);
+  lo = __builtin_bit_cast(unsigned short, l);
 }
 
-// x - hi for the FP16 half hi held in the low / high 16 bits of a packed
-// dword: one mixed-precision FMA (-hi * 1 + x, exact in FP32) instead of a
-// conversion and a subtraction.
-__device__ __forceinline__ float sub_half_lo(unsigned packed, float x) {
-  float r;
-  asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(r) : "v"(packed), "v"(x));
-  return r;
-}
-__device__ __forceinline__ float sub_half_hi(unsigned packed, float x) {
-  float r;
-  asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(r) : "v"(packed), "v"(x));
-  return r;
-}
-
-// Splits two floats into packed (hi, hi) and (lo, lo) dwords.  FP16 uses the
-// packed round-toward-zero conversion (the lo half carries the exact fp32
-// remainder x - hi, so truncation costs at most one lo ulp).
-template <int PREC>
+// Splits two floats into packed (hi, hi) and (lo, lo) dwords, round to nearest
+// even: both values by one packed conversion; the hi halves back in FP32 are
+// the top 16 bits, so x - hi is exact.
 __device__ __forceinline__ void split_pair(float a, float b, unsigned& hi, unsigned& lo) {
-  if constexpr (PREC == 0) {
-    hi = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(a, b));
-    lo = __builtin_bit_cast(unsigned, __builtin_amdgcn_cvt_pkrtz(sub_half_lo(hi, a), sub_half_hi(hi, b)));
-  } else {
-    // BF16, round to nearest even: both values by one packed conversion; the
-    // hi halves back in FP32 are the top 16 bits, so x - hi is exact
-    typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
-    typedef float f2v __attribute__((ext_vector_type(2)));
-    hi = __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{a, b}, bf2));
-    const float ha = __builtin_bit_cast(float, hi << 16), hb = __builtin_bit_cast(float, hi & 0xffff0000u);
-    lo = __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{a - ha, b - hb}, bf2));
-  }
+  typedef __bf16 bf2 __attribute__((ext_vector_type(2)));
+  typedef float f2v __attribute__((ext_vector_type(2)));
+  hi = __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{a, b}, bf2));
+  const float ha = __builtin_bit_cast(float, hi << 16), hb = __builtin_bit_cast(float, hi & 0xffff0000u);
+  lo = __builtin_bit_cast(unsigned, __builtin_convertvector(f2v{a - ha, b - hb}, bf2));
 }
 
 // Builds the constant fragments in FP64 and stores them split.
@@ -196,24 +163,16 @@ __global__ void k_gemm_consts(unsigned short* __restrict__ frag) {
     lo_at = base + 256;
   }
   unsigned short h, l;
-  split2<PREC>((float)val, h, l);
+  split2((float)val, h, l);
   frag[hi_at] = h;
   frag[lo_at] = PREC == 2 ? (unsigned short)0 : l;
 }
 
-template <int PREC>
 __device__ __forceinline__ f4 mfma32(const u4v& a, const u4v& b, const f4& c) {
-  if constexpr (PREC == 0)
-    return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x32_bf16(__builtin_bit_cast(b8, a), __builtin_bit_cast(b8, b), c, 0, 0, 0);
 }
-template <int PREC>
 __device__ __forceinline__ f4 mfma16(const u2v& a, const u2v& b, const f4& c) {
-  if constexpr (PREC == 0)
-    return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(h4, a), __builtin_bit_cast(h4, b), c, 0, 0, 0);
-  else
-    return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s4, a), __builtin_bit_cast(s4, b), c, 0, 0, 0);
+  return __builtin_amdgcn_mfma_f32_16x16x16bf16_1k(__builtin_bit_cast(s4, a), __builtin_bit_cast(s4, b), c, 0, 0, 0);
 }
 
 // Operand values of one (v tile, row chunk) for this lane: row v = vt 16 + lane % 16,
@@ -345,10 +304,10 @@ __global__ __launch_bounds__(512) void k_xcf_gemm(const cf* __restrict__ spec_p,
         for (int j = 0; j < 8; j += 2) {
           const cf z0 = cmulc(ev[j], tcur[j]), z1 = cmulc(ev[j + 1], tcur[j + 1]);
           unsigned h, lo;
-          split_pair<PREC>(z0.x, z1.x, h, lo);
+          split_pair(z0.x, z1.x, h, lo);
           zrh[j / 2] = h;
           zrl[j / 2] = lo;
-          split_pair<PREC>(z0.y, z1.y, h, lo);
+          split_pair(z0.y, z1.y, h, lo);
           zih[j / 2] = h;
           zil[j / 2] = lo;
         }
@@ -361,35 +320,35 @@ __global__ __launch_bounds__(512) void k_xcf_gemm(const cf* __restrict__ spec_p,
           const u4v wih = w1f[fb + 128], wil = w1f[fb + 192];
           if constexpr (G::NEGW) {
             const u4v nwh = w1f[fb + 256], nwl = w1f[fb + 320];
-            ar[s] = mfma32<PREC>(zrh, wrh, ar[s]);
-            ai[s] = mfma32<PREC>(zrh, wih, ai[s]);
-            ar[s] = mfma32<PREC>(zih, nwh, ar[s]);
-            ai[s] = mfma32<PREC>(zih, wrh, ai[s]);
+            ar[s] = mfma32(zrh, wrh, ar[s]);
+            ai[s] = mfma32(zrh, wih, ai[s]);
+            ar[s] = mfma32(zih, nwh, ar[s]);
+            ai[s] = mfma32(zih, wrh, ai[s]);
             if constexpr (TWO) {
-              ar[s] = mfma32<PREC>(zrh, wrl, ar[s]);
-              ai[s] = mfma32<PREC>(zrh, wil, ai[s]);
-              ar[s] = mfma32<PREC>(zih, nwl, ar[s]);
-              ai[s] = mfma32<PREC>(zih, wrl, ai[s]);
-              ar[s] = mfma32<PREC>(zrl, wrh, ar[s]);
-              ai[s] = mfma32<PREC>(zrl, wih, ai[s]);
-              ar[s] = mfma32<PREC>(zil, nwh, ar[s]);
-              ai[s] = mfma32<PREC>(zil, wrh, ai[s]);
+              ar[s] = mfma32(zrh, wrl, ar[s]);
+              ai[s] = mfma32(zrh, wil, ai[s]);
+              ar[s] = mfma32(zih, nwl, ar[s]);
+              ai[s] = mfma32(zih, wrl, ai[s]);
+              ar[s] = mfma32(zrl, wrh, ar[s]);
+              ai[s] = mfma32(zrl, wih, ai[s]);
+              ar[s] = mfma32(zil, nwh, ar[s]);
+              ai[s] = mfma32(zil, wrh, ai[s]);
             }
           } else {
             const u4v nzh = zih ^ 0x80008000u, nzl = zil ^ 0x80008000u;
-            ar[s] = mfma32<PREC>(zrh, wrh, ar[s]);
-            ai[s] = mfma32<PREC>(zrh, wih, ai[s]);
-            ar[s] = mfma32<PREC>(nzh, wih, ar[s]);
-            ai[s] = mfma32<PREC>(zih, wrh, ai[s]);
+            ar[s] = mfma32(zrh, wrh, ar[s]);
+            ai[s] = mfma32(zrh, wih, ai[s]);
+            ar[s] = mfma32(nzh, wih, ar[s]);
+            ai[s] = mfma32(zih, wrh, ai[s]);
             if constexpr (TWO) {
-              ar[s] = mfma32<PREC>(zrh, wrl, ar[s]);
-              ai[s] = mfma32<PREC>(zrh, wil, ai[s]);
-              ar[s] = mfma32<PREC>(nzh, wil, ar[s]);
-              ai[s] = mfma32<PREC>(zih, wrl, ai[s]);
-              ar[s] = mfma32<PREC>(zrl, wrh, ar[s]);
-              ai[s] = mfma32<PREC>(zrl, wih, ai[s]);
-              ar[s] = mfma32<PREC>(nzl, wih, ar[s]);
-              ai[s] = mfma32<PREC>(zil, wrh, ai[s]);
+              ar[s] = mfma32(zrh, wrl, ar[s]);
+              ai[s] = mfma32(zrh, wil, ai[s]);
+              ar[s] = mfma32(nzh, wil, ar[s]);
+              ai[s] = mfma32(zih, wrl, ai[s]);
+              ar[s] = mfma32(zrl, wrh, ar[s]);
+              ai[s] = mfma32(zrl, wih, ai[s]);
+              ar[s] = mfma32(nzl, wih, ar[s]);
+              ai[s] = mfma32(zil, wrh, ai[s]);
             }
           }
         }
@@ -403,10 +362,10 @@ __global__ __launch_bounds__(512) void k_xcf_gemm(const cf* __restrict__ spec_p,
 #pragma unroll
         for (int i = 0; i < 4; i += 2) {
           unsigned h, lo;
-          split_pair<PREC>(ar[s][i], ar[s][i + 1], h, lo);
+          split_pair(ar[s][i], ar[s][i + 1], h, lo);
           brh[s][i / 2] = h;
           brl[s][i / 2] = lo;
-          split_pair<PREC>(ai[s][i], ai[s][i + 1], h, lo);
+          split_pair(ai[s][i], ai[s][i + 1], h, lo);
           bih[s][i / 2] = h;
           bil[s][i / 2] = lo;
         }
@@ -417,19 +376,19 @@ __global__ __launch_bounds__(512) void k_xcf_gemm(const cf* __restrict__ spec_p,
         const u2v crh = cfr[fb], crl = cfr[fb + 64];
         const u2v cih = cfr[fb + 128], cil = cfr[fb + 192];
 #pragma unroll
-        for (int sy = 0; sy < ST; ++sy) rho[sx][sy] = mfma16<PREC>(crh, brh[sy], rho[sx][sy]);
+        for (int sy = 0; sy < ST; ++sy) rho[sx][sy] = mfma16(crh, brh[sy], rho[sx][sy]);
 #pragma unroll
-        for (int sy = 0; sy < ST; ++sy) rho[sx][sy] = mfma16<PREC>(cih, bih[sy], rho[sx][sy]);
+        for (int sy = 0; sy < ST; ++sy) rho[sx][sy] = mfma16(cih, bih[sy], rho[sx][sy]);
         if constexpr (TWO) {
 #pragma unroll
           for (int sy = 0; sy < ST; ++sy) {
-            rho[sx][sy] = mfma16<PREC>(crh, brl[sy], rho[sx][sy]);
-            rho[sx][sy] = mfma16<PREC>(cih, bil[sy], rho[sx][sy]);
+            rho[sx][sy] = mfma16(crh, brl[sy], rho[sx][sy]);
+            rho[sx][sy] = mfma16(cih, bil[sy], rho[sx][sy]);
           }
 #pragma unroll
           for (int sy = 0; sy < ST; ++sy) {
-            rho[sx][sy] = mfma16<PREC>(crl, brh[sy], rho[sx][sy]);
-            rho[sx][sy] = mfma16<PREC>(cil, bih[sy], rho[sx][sy]);
+            rho[sx][sy] = mfma16(crl, brh[sy], rho[sx][sy]);
+            rho[sx][sy] = mfma16(cil, bih[sy], rho[sx][sy]);
           }
         }
       }
@@ -493,35 +452,35 @@ __device__ __forceinline__ void stage1_tile(const u4v& zrh, const u4v& zrl, cons
   const u4v wih = w1f[fb + 128], wil = w1f[fb + 192];
   if constexpr (NEGW) {
     const u4v nwh = w1f[fb + 256], nwl = w1f[fb + 320];
-    ar = mfma32<PREC>(zrh, wrh, ar);
-    ai = mfma32<PREC>(zrh, wih, ai);
-    ar = mfma32<PREC>(zih, nwh, ar);
-    ai = mfma32<PREC>(zih, wrh, ai);
+    ar = mfma32(zrh, wrh, ar);
+    ai = mfma32(zrh, wih, ai);
+    ar = mfma32(zih, nwh, ar);
+    ai = mfma32(zih, wrh, ai);
     if constexpr (TWO) {
-      ar = mfma32<PREC>(zrh, wrl, ar);
-      ai = mfma32<PREC>(zrh, wil, ai);
-      ar = mfma32<PREC>(zih, nwl, ar);
-      ai = mfma32<PREC>(zih, wrl, ai);
-      ar = mfma32<PREC>(zrl, wrh, ar);
-      ai = mfma32<PREC>(zrl, wih, ai);
-      ar = mfma32<PREC>(zil, nwh, ar);
-      ai = mfma32<PREC>(zil, wrh, ai);
+      ar = mfma32(zrh, wrl, ar);
+      ai = mfma32(zrh, wil, ai);
+      ar = mfma32(zih, nwl, ar);
+      ai = mfma32(zih, wrl, ai);
+      ar = mfma32(zrl, wrh, ar);
+      ai = mfma32(zrl, wih, ai);
+      ar = mfma32(zil, nwh, ar);
+      ai = mfma32(zil, wrh, ai);
     }
   } else {
     const u4v nzh = zih ^ 0x80008000u, nzl = zil ^ 0x80008000u;
-    ar = mfma32<PREC>(zrh, wrh, ar);
-    ai = mfma32<PREC>(zrh, wih, ai);
-    ar = mfma32<PREC>(nzh, wih, ar);
-    ai = mfma32<PREC>(zih, wrh, ai);
+    ar = mfma32(zrh, wrh, ar);
+    ai = mfma32(zrh, wih, ai);
+    ar = mfma32(nzh, wih, ar);
+    ai = mfma32(zih, wrh, ai);
     if constexpr (TWO) {
-      ar = mfma32<PREC>(zrh, wrl, ar);
-      ai = mfma32<PREC>(zrh, wil, ai);
-      ar = mfma32<PREC>(nzh, wil, ar);
-      ai = mfma32<PREC>(zih, wrl, ai);
-      ar = mfma32<PREC>(zrl, wrh, ar);
-      ai = mfma32<PREC>(zrl, wih, ai);
-      ar = mfma32<PREC>(nzl, wih, ar);
-      ai = mfma32<PREC>(zil, wrh, ai);
+      ar = mfma32(zrh, wrl, ar);
+      ai = mfma32(zrh, wil, ai);
+      ar = mfma32(nzh, wil, ar);
+      ai = mfma32(zih, wrl, ai);
+      ar = mfma32(zrl, wrh, ar);
+      ai = mfma32(zrl, wih, ai);
+      ar = mfma32(nzl, wih, ar);
+      ai = mfma32(zil, wrh, ai);
     }
   }
 }
@@ -551,31 +510,31 @@ __device__ __forceinline__ void stage1_tiles2(const u4v& zrh, const u4v& zrl, co
     z2h = zih ^ 0x80008000u;
     z2l = zil ^ 0x80008000u;
   }
-  ar[0] = mfma32<PREC>(zrh, wrh0, ar[0]);
-  ar[1] = mfma32<PREC>(zrh, wrh1, ar[1]);
-  ai[0] = mfma32<PREC>(zrh, wih0, ai[0]);
-  ai[1] = mfma32<PREC>(zrh, wih1, ai[1]);
-  ar[0] = mfma32<PREC>(z2h, nwh0, ar[0]);
-  ar[1] = mfma32<PREC>(z2h, nwh1, ar[1]);
-  ai[0] = mfma32<PREC>(zih, wrh0, ai[0]);
-  ai[1] = mfma32<PREC>(zih, wrh1, ai[1]);
+  ar[0] = mfma32(zrh, wrh0, ar[0]);
+  ar[1] = mfma32(zrh, wrh1, ar[1]);
+  ai[0] = mfma32(zrh, wih0, ai[0]);
+  ai[1] = mfma32(zrh, wih1, ai[1]);
+  ar[0] = mfma32(z2h, nwh0, ar[0]);
+  ar[1] = mfma32(z2h, nwh1, ar[1]);
+  ai[0] = mfma32(zih, wrh0, ai[0]);
+  ai[1] = mfma32(zih, wrh1, ai[1]);
   if constexpr (TWO) {
-    ar[0] = mfma32<PREC>(zrh, wrl0, ar[0]);
-    ar[1] = mfma32<PREC>(zrh, wrl1, ar[1]);
-    ai[0] = mfma32<PREC>(zrh, wil0, ai[0]);
-    ai[1] = mfma32<PREC>(zrh, wil1, ai[1]);
-    ar[0] = mfma32<PREC>(z2h, nwl0, ar[0]);
-    ar[1] = mfma32<PREC>(z2h, nwl1, ar[1]);
-    ai[0] = mfma32<PREC>(zih, wrl0, ai[0]);
-    ai[1] = mfma32<PREC>(zih, wrl1, ai[1]);
-    ar[0] = mfma32<PREC>(zrl, wrh0, ar[0]);
-    ar[1] = mfma32<PREC>(zrl, wrh1, ar[1]);
-    ai[0] = mfma32<PREC>(zrl, wih0, ai[0]);
-    ai[1] = mfma32<PREC>(zrl, wih1, ai[1]);
-    ar[0] = mfma32<PREC>(z2l, nwh0, ar[0]);
-    ar[1] = mfma32<PREC>(z2l, nwh1, ar[1]);
-    ai[0] = mfma32<PREC>(zil, wrh0, ai[0]);
-    ai[1] = mfma32<PREC>(zil, wrh1, ai[1]);
+    ar[0] = mfma32(zrh, wrl0, ar[0]);
+    ar[1] = mfma32(zrh, wrl1, ar[1]);
+    ai[0] = mfma32(zrh, wil0, ai[0]);
+    ai[1] = mfma32(zrh, wil1, ai[1]);
+    ar[0] = mfma32(z2h, nwl0, ar[0]);
+    ar[1] = mfma32(z2h, nwl1, ar[1]);
+    ai[0] = mfma32(zih, wrl0, ai[0]);
+    ai[1] = mfma32(zih, wrl1, ai[1]);
+    ar[0] = mfma32(zrl, wrh0, ar[0]);
+    ar[1] = mfma32(zrl, wrh1, ar[1]);
+    ai[0] = mfma32(zrl, wih0, ai[0]);
+    ai[1] = mfma32(zrl, wih1, ai[1]);
+    ar[0] = mfma32(z2l, nwh0, ar[0]);
+    ar[1] = mfma32(z2l, nwh1, ar[1]);
+    ai[0] = mfma32(zil, wrh0, ai[0]);
+    ai[1] = mfma32(zil, wrh1, ai[1]);
   }
 }
 
@@ -704,10 +663,10 @@ __global__ __launch_bounds__(512) void k_xcf_gemm_pt(const cf* __restrict__ spec
         for (int j = 0; j < 8; j += 2) {
           const cf z0 = cmulc(ep[val_at(j)], tcur[j]), z1 = cmulc(ep[val_at(j + 1)], tcur[j + 1]);
           unsigned h, lo;
-          split_pair<PREC>(z0.x, z1.x, h, lo);
+          split_pair(z0.x, z1.x, h, lo);
           zrh[j / 2] = h;
           zrl[j / 2] = lo;
-          split_pair<PREC>(z0.y, z1.y, h, lo);
+          split_pair(z0.y, z1.y, h, lo);
           zih[j / 2] = h;
           zil[j / 2] = lo;
         }
@@ -744,10 +703,10 @@ __global__ __launch_bounds__(512) void k_xcf_gemm_pt(const cf* __restrict__ spec
 #pragma unroll
         for (int i = 0; i < 4; i += 2) {
           unsigned h, lo;
-          split_pair<PREC>(ar[pb][s][i], ar[pb][s][i + 1], h, lo);
+          split_pair(ar[pb][s][i], ar[pb][s][i + 1], h, lo);
           brh[s][i / 2] = h;
           brl[s][i / 2] = lo;
-          split_pair<PREC>(ai[pb][s][i], ai[pb][s][i + 1], h, lo);
+          split_pair(ai[pb][s][i], ai[pb][s][i + 1], h, lo);
           bih[s][i / 2] = h;
           bil[s][i / 2] = lo;
         }
@@ -759,13 +718,13 @@ __global__ __launch_bounds__(512) void k_xcf_gemm_pt(const cf* __restrict__ spec
         const u2v cih = cfr[fb + 128], cil = cfr[fb + 192];
 #pragma unroll
         for (int sy = 0; sy < ST; ++sy) {
-          rho[pb][sx][sy] = mfma16<PREC>(crh, brh[sy], rho[pb][sx][sy]);
-          rho[pb][sx][sy] = mfma16<PREC>(cih, bih[sy], rho[pb][sx][sy]);
+          rho[pb][sx][sy] = mfma16(crh, brh[sy], rho[pb][sx][sy]);
+          rho[pb][sx][sy] = mfma16(cih, bih[sy], rho[pb][sx][sy]);
           if constexpr (TWO) {
-            rho[pb][sx][sy] = mfma16<PREC>(crh, brl[sy], rho[pb][sx][sy]);
-            rho[pb][sx][sy] = mfma16<PREC>(cih, bil[sy], rho[pb][sx][sy]);
-            rho[pb][sx][sy] = mfma16<PREC>(crl, brh[sy], rho[pb][sx][sy]);
-            rho[pb][sx][sy] = mfma16<PREC>(cil, bih[sy], rho[pb][sx][sy]);
+            rho[pb][sx][sy] = mfma16(crh, brl[sy], rho[pb][sx][sy]);
+            rho[pb][sx][sy] = mfma16(cih, bil[sy], rho[pb][sx][sy]);
+            rho[pb][sx][sy] = mfma16(crl, brh[sy], rho[pb][sx][sy]);
+            rho[pb][sx][sy] = mfma16(cil, bih[sy], rho[pb][sx][sy]);
           }
         }
       }
@@ -894,14 +853,15 @@ hipError_t launch_xcf_gemm(int n, int precision, const float2* spec_p, int64_t p
                            int max_shift, unsigned short* frag, float* scores, hipStream_t stream) {
   if (p <= 0 || l <= 0) return hipSuccess;
   if (!gemm_supported(n, max_shift) || precision < 0 || precision > 2) return hipErrorInvalidValue;
+  if (precision == 0) return launch_xcf_even(n, true, true, spec_p, p, spec_l, l, max_shift, frag, scores, stream);
   const int st = gemm_slot_tiles(max_shift);
 #define EBSD_GP(NN, SS, PP) \
   if (n == NN && st == SS && precision == PP) return run_gemm<NN, SS, PP>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
 #define EBSD_GS(NN) \
-  EBSD_GP(NN, 1, 0) EBSD_GP(NN, 1, 1) EBSD_GP(NN, 1, 2) \
-  EBSD_GP(NN, 2, 0) EBSD_GP(NN, 2, 1) EBSD_GP(NN, 2, 2) \
-  EBSD_GP(NN, 3, 0) EBSD_GP(NN, 3, 1) EBSD_GP(NN, 3, 2) \
-  EBSD_GP(NN, 4, 0) EBSD_GP(NN, 4, 1) EBSD_GP(NN, 4, 2)
+  EBSD_GP(NN, 1, 1) EBSD_GP(NN, 1, 2) \
+  EBSD_GP(NN, 2, 1) EBSD_GP(NN, 2, 2) \
+  EBSD_GP(NN, 3, 1) EBSD_GP(NN, 3, 2) \
+  EBSD_GP(NN, 4, 1) EBSD_GP(NN, 4, 2)
   EBSD_GEMM_SIZES(EBSD_GS)
 #undef EBSD_GS
 #undef EBSD_GP
