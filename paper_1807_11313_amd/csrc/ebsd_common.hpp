@@ -356,4 +356,32 @@ __device__ __forceinline__ void qstore(double* q, const double* v) {
   for (int c = 0; c < 4; ++c) q[c] = v[c] * sg;
 }
 
+// Entry i of the phase tables of a local grid of shifts: F1 [2B+1][M], F2 [B+1][M],
+// roots_n [n] in FP64, rounded (M = 2m + 1).
+__device__ __forceinline__ float2 grid_table_entry(int i, int n, int bnd, int kappa, int m) {
+  const int msz = 2 * m + 1;
+  const int nk = 2 * bnd + 1, nv = bnd + 1;
+  const long kn = (long)kappa * n;
+  long idx, den;
+  if (i < nk * msz) {
+    const int kk = i / msz, b = i - kk * msz;
+    const int u = kk <= bnd ? kk : kk - nk;
+    idx = (long)u * (b - m);
+    den = kn;
+  } else if (i < (nk + nv) * msz) {
+    const int j = i - nk * msz;
+    const int v = j / msz, a = j - v * msz;
+    idx = (long)v * (a - m);
+    den = kn;
+  } else {
+    idx = i - (nk + nv) * msz;
+    den = n;
+  }
+  idx %= den;
+  if (idx < 0) idx += den;
+  double s, c;
+  sincospi(2.0 * (double)idx / (double)den, &s, &c);
+  return make_float2((float)c, (float)s);
+}
+
 }  // namespace ebsd

@@ -79,8 +79,12 @@ hipError_t launch_xcf_peak(int n, const float2* spec_p, const float2* spec_l,
                            const int32_t* pi, const int32_t* li, int64_t k, int max_shift,
                            float* h_int, int32_t* s_int, float* map, hipStream_t stream);
 
+// Phase tables of a local grid of shifts (k_grid_peak.hip), in complex elements.
+int grid_table_size(int n, int kappa, int m);
+size_t grid_lds_bytes(int n, int m);
+
 // Phase tables of the upsampled peak for (n, kappa): size in complex
-// elements, their construction, and the LDS one block of the kernel needs.
+// elements, their construction, and the LDS that bounds the accepted kappa.
 int subpixel_table_size(int n, int kappa);
 size_t subpixel_lds_bytes(int n, int kappa);
 hipError_t launch_subpixel_tables(int n, int kappa, float2* tab, hipStream_t stream);

@@ -40,34 +40,9 @@ size_t grid_lds_bytes(int n, int m) {
   return sizeof(cf) * ((size_t)UC * nv + (size_t)UC * msz + (size_t)msz * nv);
 }
 
-// F1 [2B+1][M], F2 [B+1][M], roots_n [n] in FP64, rounded
 __global__ void k_grid_tables(int n, int bnd, int kappa, int m, float2* tab) {
-  const int msz = 2 * m + 1;
-  const int nk = 2 * bnd + 1, nv = bnd + 1;
-  const long kn = (long)kappa * n;
   const int i = blockIdx.x * 256 + threadIdx.x;
-  const int total = (nk + nv) * msz + n;
-  if (i >= total) return;
-  long idx, den;
-  if (i < nk * msz) {
-    const int kk = i / msz, b = i - kk * msz;
-    const int u = kk <= bnd ? kk : kk - nk;
-    idx = (long)u * (b - m);
-    den = kn;
-  } else if (i < (nk + nv) * msz) {
-    const int j = i - nk * msz;
-    const int v = j / msz, a = j - v * msz;
-    idx = (long)v * (a - m);
-    den = kn;
-  } else {
-    idx = i - (nk + nv) * msz;
-    den = n;
-  }
-  idx %= den;
-  if (idx < 0) idx += den;
-  double s, c;
-  sincospi(2.0 * (double)idx / (double)den, &s, &c);
-  tab[i] = make_float2((float)c, (float)s);
+  if (i < ((2 * bnd + 1) + (bnd + 1)) * (2 * m + 1) + n) tab[i] = grid_table_entry(i, n, bnd, kappa, m);
 }
 
 // TB x TB threads: thread (ty, tx) holds rows b = ty + TB i and columns
@@ -235,7 +210,7 @@ __global__ __launch_bounds__(TB * TB) void k_grid_peak(int n, int bnd, const cf*
   }
 }
 
-hipError_t launch_grid_tables(int n, int kappa, int m, float2* tab, hipStream_t stream) {
+static hipError_t launch_grid_tables(int n, int kappa, int m, float2* tab, hipStream_t stream) {
   const int bnd = band_of(n);
   if (bnd < 0) return hipErrorInvalidValue;
   const int total = grid_table_size(n, kappa, m);
@@ -308,19 +283,6 @@ static hipError_t launch_grid(int n, const float2* spec_p, const float2* spec_l,
     return wide ? grid_vj<4, 32>(n, bnd, spec_p, spec_l, pi, li, k, centre, kappa, m, int_keys, tab, h, s, si, stream)
                 : grid_vj<7, 16>(n, bnd, spec_p, spec_l, pi, li, k, centre, kappa, m, int_keys, tab, h, s, si, stream);
   return hipErrorInvalidValue;
-}
-
-int subpixel_table_size(int n, int kappa) { return grid_table_size(n, kappa, (3 * kappa + 3) / 4); }
-size_t subpixel_lds_bytes(int n, int kappa) { return grid_lds_bytes(n, (3 * kappa + 3) / 4); }
-hipError_t launch_subpixel_tables(int n, int kappa, float2* tab, hipStream_t stream) {
-  return launch_grid_tables(n, kappa, (3 * kappa + 3) / 4, tab, stream);
-}
-
-hipError_t launch_subpixel(int n, const float2* spec_p, const float2* spec_l, const int32_t* pi, const int32_t* li,
-                           int64_t k, const int32_t* s_int, int kappa, const float2* tab, float* h_sub,
-                           float* s_sub, hipStream_t stream) {
-  return launch_grid(n, spec_p, spec_l, pi, li, k, s_int, kappa, (3 * kappa + 3) / 4, 0, tab, h_sub, s_sub,
-                     nullptr, stream);
 }
 
 int window_table_size(int n, int max_shift) { return grid_table_size(n, 1, max_shift); }
