@@ -38,43 +38,10 @@ int fail_hip(hipError_t e, const char* where) {
     if (e_ != hipSuccess) return fail_hip(e_, where); \
   } while (0)
 
-// Where an entry point's device scratch comes from.
-class Arena {
- public:
-  virtual ~Arena() = default;
-  virtual void* raw(size_t bytes, hipError_t* err) = 0;
-  template <class T>
-  T* get(size_t count, hipError_t* err) {
-    return static_cast<T*>(raw((count ? count : 1) * sizeof(T), err));
-  }
-};
-
-// Scratch allocated in stream order on the caller's stream and released in
-// stream order when the call returns; the device memory pool keeps it for
-// the next call, so repeated calls do not reach the kernel-mode allocator.
-class Scratch : public Arena {
- public:
-  explicit Scratch(hipStream_t s) : stream_(s) {}
-  ~Scratch() override {
-    for (void* p : ptrs_) (void)hipFreeAsync(p, stream_);
-  }
-  void* raw(size_t bytes, hipError_t* err) override {
-    void* p = nullptr;
-    *err = hipMallocAsync(&p, bytes, stream_);
-    if (*err != hipSuccess) return nullptr;
-    ptrs_.push_back(p);
-    return p;
-  }
-
- private:
-  hipStream_t stream_;
-  std::vector<void*> ptrs_;
-};
-
 // Consecutive 256-byte aligned pieces of one caller-given device buffer
 // (base may be null: the arena then only adds up the bytes it would hand
 // out, to size a call before anything is enqueued).
-class FixedArena : public Arena {
+class FixedArena : public ScratchSource {
  public:
   FixedArena(void* base, size_t cap) : base_(static_cast<char*>(base)), cap_(cap) {}
   void* raw(size_t bytes, hipError_t* err) override {
@@ -171,7 +138,7 @@ FilterParams filter_of(const ebsd_params& p, int n) {
 // scratch at 256 (s256: spectra256_scratch_bytes(k) bytes, or taken from ws
 // when null).
 int do_spectra(int n, const float* imgs, int64_t k, const FilterParams& fp, float2* spec, double* energy,
-               Arena& ws, hipStream_t st, void* s256 = nullptr) {
+               ScratchSource& ws, hipStream_t st, void* s256 = nullptr) {
   if (n == 256) {
     if (!s256) {
       EBSD_ALLOC(buf, unsigned char, spectra256_scratch_bytes(k), ws);
@@ -188,7 +155,7 @@ int do_spectra(int n, const float* imgs, int64_t k, const FilterParams& fp, floa
 // otherwise the exact shift-window evaluation (needs max_shift >= 0) with
 // the phase tables tab (built here into ws when null).
 int do_peak(int n, const ebsd_params& p, const float2* sp, const float2* sl, const int32_t* pi, const int32_t* li,
-            int64_t k, float* h, int32_t* s, Arena& ws, hipStream_t st, const float2* tab = nullptr) {
+            int64_t k, float* h, int32_t* s, ScratchSource& ws, hipStream_t st, const float2* tab = nullptr) {
   if (fft_supported(n)) {
     EBSD_TRY(launch_xcf_peak(n, sp, sl, pi, li, k, p.max_shift, h, s, nullptr, st), "xcf_peak");
     return EBSD_OK;
@@ -213,7 +180,7 @@ int f32_images_only(const ebsd_params& p) {
 // Spectra and log-polar images of the caller's patterns (FP32, or BF16 as
 // p.input says).
 int pattern_spectra(int n, const ebsd_params& p, const float* imgs, int64_t k, const FilterParams& fp, float2* spec,
-                    double* energy, Arena& ws, hipStream_t st, void* s256 = nullptr) {
+                    double* energy, ScratchSource& ws, hipStream_t st, void* s256 = nullptr) {
   if (p.input == EBSD_INPUT_BF16) {
     EBSD_TRY(launch_spectra(n, reinterpret_cast<const __bf16*>(imgs), (int64_t)n * n, k, fp, spec, energy, st),
              "spectra(bf16)");
@@ -263,7 +230,7 @@ struct SearchConsts {
   float2* wtab = nullptr;
 };
 
-int search_consts(int n, const ebsd_params& p, Arena& ws, hipStream_t st, SearchConsts* c) {
+int search_consts(int n, const ebsd_params& p, ScratchSource& ws, hipStream_t st, SearchConsts* c) {
   const bool split = p.form == EBSD_FORM_DFTGEMM;
   if (split || (p.form == EBSD_FORM_DFT && even_supported(n, p.max_shift))) {
     const size_t bytes = split && p.precision != EBSD_PREC_FP16X2 ? gemm_frag_bytes(n, p.max_shift)
@@ -310,7 +277,7 @@ hipError_t timed_scores(int n, const ebsd_params& prm, const float2* sp, int64_t
 // argmax, the winner's integer and sub-pixel peaks.
 int index_against(int n, const ebsd_params& p, const float* pats, int64_t P, const float2* spec_l,
                   const double* lib_q, int64_t L, int32_t* best_idx, double* best_q, float* peak_h, float* shift,
-                  float* scores, Arena& ws, hipStream_t st) {
+                  float* scores, ScratchSource& ws, hipStream_t st) {
   int rc;
   const int64_t sc = spec_complex(n);
   const FilterParams fp = filter_of(p, n);
@@ -694,7 +661,7 @@ struct RefineBufs {
   float2* wtab;   // shift-window phase tables (null where the FFT form runs)
 };
 
-int alloc_refine(Arena& ws, int n, int64_t P, const ebsd_params& p, RefineBufs* b) {
+int alloc_refine(ScratchSource& ws, int n, int64_t P, const ebsd_params& p, RefineBufs* b) {
   const int64_t sc = spec_complex(n);
   const int64_t npix = (int64_t)n * n;
   const int64_t lp = (int64_t)p.n_rho * p.n_eta;

@@ -432,15 +432,13 @@ int ebsd_index_proposed(const ebsd_batch* pats, const ebsd_master* mp, const ebs
   const FilterParams fp = filter_of(p, n);
   const int64_t PK = P * top_k;
   // scratch (stream ordered)
-  std::vector<void*> held;
+  Scratch ws(st);
+  bool short_of = false;
   auto get = [&](size_t bytes) -> void* {
-    void* ptr = nullptr;
-    if (hipMallocAsync(&ptr, bytes ? bytes : 1, st) != hipSuccess) return nullptr;
-    held.push_back(ptr);
+    hipError_t e = hipSuccess;
+    void* ptr = ws.raw(bytes ? bytes : 1, &e);
+    short_of |= e != hipSuccess;
     return ptr;
-  };
-  auto release = [&]() {
-    for (void* ptr : held) (void)hipFreeAsync(ptr, st);
   };
   float* x = (float*)get(sizeof(float) * P * cnn::kInSize * cnn::kInSize);
   float* logits = (float*)get(sizeof(float) * std::min<int64_t>(P, kChunk) * L);
@@ -458,11 +456,7 @@ int ebsd_index_proposed(const ebsd_batch* pats, const ebsd_master* mp, const ebs
   int32_t* s_int = (int32_t*)get(sizeof(int32_t) * 2 * P);
   float* h_tmp = (float*)get(sizeof(float) * P);
   float2* roots = (float2*)get(sizeof(float2) * subpixel_table_size(n, p.upsample));
-  for (void* ptr : held)
-    if (!ptr) {
-      release();
-      return fail(EBSD_E_NOMEM, "proposal scratch allocation failed");
-    }
+  if (short_of) return fail(EBSD_E_NOMEM, "proposal scratch allocation failed");
   auto run = [&]() -> int {
     int r;
     // network: top-k library orientations per pattern
@@ -503,7 +497,7 @@ int ebsd_index_proposed(const ebsd_batch* pats, const ebsd_master* mp, const ebs
       float* sc_f = (float*)get(sizeof(float) * (size_t)nf * L);
       int32_t* b_f = (int32_t*)get(sizeof(int32_t) * nf);
       float* h_f = (float*)get(sizeof(float) * nf);
-      if (!spec_f || !sc_f || !b_f || !h_f) return fail(EBSD_E_NOMEM, "fallback scratch allocation failed");
+      if (short_of) return fail(EBSD_E_NOMEM, "fallback scratch allocation failed");
       hipLaunchKernelGGL(k_gather_rows, dim3(nb((int64_t)nf * sc)), dim3(256), 0, st, spec_p, list, (int64_t)nf, sc,
                          spec_f);
       CN_TRY(launch_xcf_scores(n, spec_f, nf, spec_l, L, p.max_shift, sc_f, st), "xcf(fallback)");
@@ -522,9 +516,7 @@ int ebsd_index_proposed(const ebsd_batch* pats, const ebsd_master* mp, const ebs
     if (fallback) CN_TRY(hipMemcpyAsync(fallback, flag, sizeof(int32_t) * P, hipMemcpyDeviceToDevice, st), "flags");
     return EBSD_OK;
   };
-  rc = run();
-  release();
-  return rc;
+  return run();
 }
 
 }  // extern "C"
