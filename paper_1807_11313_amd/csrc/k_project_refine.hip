@@ -194,63 +194,126 @@ __global__ void k_gather_q(const double* __restrict__ lib_q, const int32_t* __re
 // centre ((n-1)/2, (n-1)/2), n_rho radii log-spaced in [2, n/2 - 2] px, n_eta
 // angles eta_m = 2 pi m / n_eta measured from +column toward +row, bilinear
 // samples of the contrast-normalised image, each radius row mean-removed.
+//
+// LDS: the block's image (widened to FP32, rows one value apart so that samples
+// along a column spread over the banks) is read from memory once, in 16-byte
+// pieces, and both the statistics and the samples come from LDS; at 256 an
+// image does not fit and both read global memory.  The FP64 sums are formed by
+// 256 threads in a fixed order, whatever the block's size; the radii (an FP64
+// power each) and the angles are worked out by the other waves meanwhile, one
+// per thread.  Bound by latency before (73 % of the wave time waiting for the
+// statistics' and the samples' loads, half of the instructions in the powers).
+// 5,000 images at 128 x 128: 0.145 ms, 4.5 TB/s of images read and log-polar images written (0.43 ms with four
+// waves reading global memory twice); one image 9.5 us (41).
+// MPL samples per lane; EXACT: n_eta = 64 MPL.  The FMAs are written out, so
+// that the bits do not depend on how the compiler schedules the code.
 template <class T>
-__global__ __launch_bounds__(256) void k_logpolar(const T* __restrict__ imgs, int n, int n_rho,
-                                                  int n_eta, float* __restrict__ out) {
+struct __attribute__((packed)) Px4 {
+  T v[4];
+};
+
+template <class T, int NT, int MPL, bool EXACT, bool LDS>
+__global__ __launch_bounds__(NT, LDS ? 8 : 4) void k_logpolar(const T* __restrict__ imgs, int n, int n_rho, int n_eta,
+                                                 float* __restrict__ out) {
+#pragma clang fp contract(off)
+  extern __shared__ float lsm[];  // [n][n + 1] (LDS), radii [n_rho]
   const int64_t k = blockIdx.x;
-  const int tid = threadIdx.x;
-  const T* img = imgs + k * (int64_t)n * n;
-  double s1 = 0.0, s2 = 0.0;
-  for (int i = tid; i < n * n; i += 256) {
-    const double v = ld_px(img[i]);
-    s1 += v;
-    s2 += v * v;
-  }
-  s1 = wave_sum(s1);
-  s2 = wave_sum(s2);
+  const int tid = threadIdx.x, npx = n * n;
+  const T* img = imgs + k * (int64_t)npx;
+  float* radius = lsm + (LDS ? n * (n + 1) : 0);
+  __shared__ float2 ang[64 * MPL];
   __shared__ double red[8];
-  if ((tid & 63) == 0) {
-    red[tid >> 6] = s1;
-    red[4 + (tid >> 6)] = s2;
+  if constexpr (LDS) {
+    for (int i = 4 * tid; i < npx; i += 4 * NT) {  // n is a multiple of 4
+      const Px4<T> px = *reinterpret_cast<const Px4<T>*>(img + i);
+      float* o = lsm + i + i / n;
+#pragma unroll
+      for (int c = 0; c < 4; ++c) o[c] = ld_px(px.v[c]);
+    }
+    __syncthreads();
   }
-  __syncthreads();
-  const double mean = (red[0] + red[1] + red[2] + red[3]) / (double)(n * n);
-  const double var = (red[4] + red[5] + red[6] + red[7]) / (double)(n * n) - mean * mean;
-  const float fmean = (float)mean, inv_std = var > 0.0 ? (float)(1.0 / sqrt(var)) : 0.0f;
-  const float c = 0.5f * (float)(n - 1);
+  if (tid < 256) {
+    double s1 = 0.0, s2 = 0.0;
+    if constexpr (LDS) {
+      // pixel tid + 256 j: its row advances by 256 / n, its column by 256 mod n
+      int at = tid + tid / n, col = tid % n;
+      const int dc = 256 % n, step = 256 + 256 / n;
+#pragma unroll 8
+      for (int i = tid; i < npx; i += 256) {
+        const double v = lsm[at];
+        s1 += v;
+        s2 = fma(v, v, s2);
+        at += step;
+        col += dc;
+        const int w = col >= n ? 1 : 0;
+        at += w;
+        col -= w ? n : 0;
+      }
+    } else {
+#pragma unroll 8
+      for (int i = tid; i < npx; i += 256) {
+        const double v = ld_px(img[i]);
+        s1 += v;
+        s2 = fma(v, v, s2);
+      }
+    }
+    s1 = wave_sum(s1);
+    s2 = wave_sum(s2);
+    if ((tid & 63) == 0) {
+      red[tid >> 6] = s1;
+      red[4 + (tid >> 6)] = s2;
+    }
+  }
   const double rmin = 2.0, rmax = 0.5 * n - 2.0;
-  const int lane = tid & 63, wave = tid >> 6;
-  float* o = out + k * (int64_t)n_rho * n_eta;
-  // the angles' (cos, sin), the same for every radius; each lane keeps its
-  // samples of a row in registers until the row mean is known, so every
-  // output value is written once
-  __shared__ float2 ang[1024];
-  for (int m = tid; m < n_eta; m += 256) {
+  for (int i = NT - 1 - tid; i < n_rho; i += NT)
+    radius[i] = (float)(rmin * pow(rmax / rmin, (double)i / (double)(n_rho - 1)));
+  // the angles' (cos, sin), the same for every radius
+  for (int m = tid; m < n_eta; m += NT) {
     float sn, cs;
     sincospif(2.0f * (float)m / (float)n_eta, &sn, &cs);
     ang[m] = make_float2(cs, sn);
   }
   __syncthreads();
-  constexpr int MPL = 1024 / 64;  // samples per lane at the largest n_eta
-  for (int row = wave; row < n_rho; row += 4) {
-    const float r = (float)(rmin * pow(rmax / rmin, (double)row / (double)(n_rho - 1)));
+  const double mean = (red[0] + red[1] + red[2] + red[3]) / (double)npx;
+  const double var = fma(-mean, mean, (red[4] + red[5] + red[6] + red[7]) / (double)npx);
+  const float fmean = (float)mean, inv_std = var > 0.0 ? (float)(1.0 / sqrt(var)) : 0.0f;
+  const float c = 0.5f * (float)(n - 1);
+  const int lane = tid & 63, wave = tid >> 6;
+  float* o = out + k * (int64_t)n_rho * n_eta;
+  // a wave takes a row; each lane keeps its samples in registers until the
+  // row mean is known, so every output value is written once
+  for (int row = wave; row < n_rho; row += NT / 64) {
+    const float r = radius[row];
     float sum = 0.0f;
     float xs[MPL];
 #pragma unroll
     for (int i = 0; i < MPL; ++i) {
       const int m = lane + 64 * i;
-      if (m < n_eta) {
-        const float cs = ang[m].x, sn = ang[m].y;
-        const float col = c + r * cs, rw = c + r * sn;
+      if (EXACT || m < n_eta) {
+        const float2 a = ang[m];
+        const float col = __fmaf_rn(a.x, r, c), rw = __fmaf_rn(a.y, r, c);
         const float r0f = floorf(rw), c0f = floorf(col);
         const float fr = rw - r0f, fc = col - c0f;
         const int r0 = (int)r0f, c0 = (int)c0f;
-        const T* p = img + r0 * n + c0;
-        const float val = (1.0f - fr) * ((1.0f - fc) * ld_px(p[0]) + fc * ld_px(p[1])) +
-                          fr * ((1.0f - fc) * ld_px(p[n]) + fc * ld_px(p[n + 1]));
-        const float x = (val - fmean) * inv_std;
-        xs[i] = x;
-        sum += x;
+        float p0, p1, q0, q1;
+        if constexpr (LDS) {
+          const float* p = lsm + r0 * (n + 1) + c0;
+          p0 = p[0];
+          p1 = p[1];
+          q0 = p[n + 1];
+          q1 = p[n + 2];
+        } else {
+          const T* p = img + r0 * n + c0;
+          p0 = ld_px(p[0]);
+          p1 = ld_px(p[1]);
+          q0 = ld_px(p[n]);
+          q1 = ld_px(p[n + 1]);
+        }
+        const float top = __fmaf_rn(p1, fc, p0 * (1.0f - fc));
+        const float bot = __fmaf_rn(q0, 1.0f - fc, fc * q1);
+        const float d = __fmaf_rn(1.0f - fr, top, fr * bot) - fmean;
+        xs[i] = inv_std * d;
+        sum = __fmaf_rn(inv_std, d, sum);
       }
     }
 #pragma unroll
@@ -259,7 +322,7 @@ __global__ __launch_bounds__(256) void k_logpolar(const T* __restrict__ imgs, in
 #pragma unroll
     for (int i = 0; i < MPL; ++i) {
       const int m = lane + 64 * i;
-      if (m < n_eta) o[row * n_eta + m] = xs[i] - mu;
+      if (EXACT || m < n_eta) o[row * n_eta + m] = xs[i] - mu;
     }
   }
 }
@@ -303,6 +366,88 @@ __device__ __forceinline__ void eta_interpolate(const float* cqr, const float* c
     for (int w = 1; w < 4; ++w) argmax_merge(best, besta, rv[w], ri[w]);
     const double dsub = (double)d_int + (double)(besta - m) / (double)kappa;
     *gamma_out = 2.0 * 3.14159265358979323846 * dsub / (double)n_eta;
+  }
+}
+
+// The same maximum for the row-transform kernel (n_eta = NE), from few of its points: 31 of them spread
+// over the range, then those of the cells that can hold the winner.  Between two points h apart the
+// interpolant f lies at most h^2 / 8 max |f''| above the larger, and |f''| is bounded by the sum of its
+// terms' (2 pi q / NE)^2 |C(q)|; cells below the coarse maximum by that and by the rounding of both sides are
+// dropped, and the rest evaluated: about 15 points of 151.  A point's terms are formed by all threads into
+// `terms` (31 rows of NE / 2 values, an odd stride) and added in order of q by one thread per point, so each value has
+// the bits of eta_interpolate's.  Values that are not finite keep every point.
+template <int NE>
+__device__ __forceinline__ void eta_interpolate_fft(const float* cqr, const float* cqi, int d_int, int kappa,
+                                                    float* terms, double* gamma_out) {
+#pragma clang fp contract(off)
+  constexpr int NT = NE / 2 - 1, TS = NE / 2 + 1 - (NE / 2) % 2, PTS = 31;
+  __shared__ float val[PTS];
+  const int tid = threadIdx.x;
+  const int m = (3 * kappa + 3) / 4, st = (m + 14) / 15, kn = kappa * NE;
+  const float fkn = (float)kn;
+  // f at a0 + i s, i < cnt (positions past m repeat m)
+  auto eval = [&](int a0, int s, int cnt) {
+    __syncthreads();
+    for (int t = tid; t < cnt * NT; t += 256) {
+      const int i = t / NT, q = t - i * NT + 1;
+      int idx = (q * (kappa * d_int + min(a0 + i * s, m))) % kn;
+      if (idx < 0) idx += kn;
+      float sn, cs;
+      sincospif(2.0f * (float)idx / fkn, &sn, &cs);
+      terms[i * TS + q - 1] = __fmaf_rn(cqr[q], cs, -(cqi[q] * sn));
+    }
+    __syncthreads();
+    if (tid < cnt) {
+      const int a = min(a0 + tid * s, m);
+      const float* tr = terms + tid * TS;
+      float v = cqr[0];
+#pragma unroll 8
+      for (int q = 0; q < NT; ++q) v = __fmaf_rn(2.0f, tr[q], v);
+      const float ny = ((d_int & 1) ? -1.0f : 1.0f) * cospif((float)a / (float)kappa);
+      v = __fmaf_rn(cqr[NE / 2], ny, v);
+      val[tid] = v / (float)NE;
+    }
+    __syncthreads();
+  };
+  // sums for the bound, every wave by itself
+  float sabs = 0.0f, kabs = 0.0f;
+  for (int q = tid & 63; q <= NE / 2; q += 64) {
+    const float w = (q == 0 || q == NE / 2) ? 1.0f : 2.0f;
+    const float az = w * sqrtf(cqr[q] * cqr[q] + cqi[q] * cqi[q]) / (float)NE;
+    sabs += az;
+    kabs += az * (float)(q * q);
+  }
+#pragma unroll
+  for (int off = 32; off > 0; off >>= 1) {
+    sabs += __shfl_xor(sabs, off, 64);
+    kabs += __shfl_xor(kabs, off, 64);
+  }
+  eval(-m, st, PTS);
+  float top = -INFINITY;
+  for (int i = 0; i < PTS; ++i) top = fmaxf(top, val[i]);
+  const float h = (float)st / (float)kappa, tpn = 6.2831855f / (float)NE;
+  const float floor_ = top - (1.01f * 0.125f * h * h * tpn * tpn * kabs + (float)(2 * (NE / 2 + 16)) * 6.0e-8f * sabs);
+  int lo = PTS, hi = -1;
+  for (int i = 0; i + 1 < PTS; ++i)
+    if (fmaxf(val[i], val[i + 1]) >= floor_) {
+      lo = min(lo, i);
+      hi = i + 1;
+    }
+  const bool all = !(fabsf(floor_) < INFINITY) || hi < 0;
+  const int a_lo = all ? -m : min(m, -m + lo * st), a_hi = all ? m : min(m, -m + hi * st);
+  float best = -INFINITY;
+  int besta = 0x7fffffff;
+  for (int a0 = a_lo; a0 <= a_hi; a0 += PTS) {
+    const int cnt = min(PTS, a_hi - a0 + 1);
+    eval(a0, 1, cnt);
+    if (tid < cnt) argmax_merge(best, besta, val[tid], a0 + tid + m);
+  }
+  if (tid < 64) {
+    wave_argmax(best, besta);
+    if (tid == 0) {
+      const double dsub = (double)d_int + (double)(besta - m) / (double)kappa;
+      *gamma_out = 2.0 * 3.14159265358979323846 * dsub / (double)NE;
+    }
   }
 }
 
@@ -516,20 +661,44 @@ hipError_t launch_gather_q(const double* lib_q, const int32_t* best, int64_t p, 
   return hipGetLastError();
 }
 
+// Samples per lane fixed for the default grids (n_eta = 2n: 128, 192, 256, 320, 512), tested otherwise;
+// the image in LDS with a block of 16 waves where it fits (64 to 160: 17 to 104 KB), 4 waves at 256.
+template <class T>
+static hipError_t logpolar_t(int n, const T* imgs, int64_t k, int n_rho, int n_eta, float* out, hipStream_t stream) {
+  if (k <= 0) return hipSuccess;
+  if (n_eta > 1024 || k > (int64_t(1) << 31) / 256) return hipErrorInvalidValue;
+  const size_t image = sizeof(float) * (size_t)n * (n + 1), radii = sizeof(float) * (size_t)n_rho;
+  const bool lds = n % 4 == 0 && image + radii <= 120 * 1024;
+  const size_t shm = (lds ? image : 0) + radii;
+  if (radii > 40 * 1024) return hipErrorInvalidValue;
+  auto kernel = lds ? k_logpolar<T, 1024, 16, false, true> : k_logpolar<T, 256, 16, false, false>;
+  switch (n_eta) {
+#define EBSD_LP(NE) \
+  case NE: kernel = lds ? k_logpolar<T, 1024, NE / 64, true, true> : k_logpolar<T, 256, NE / 64, true, false>; break;
+    EBSD_LP(128) EBSD_LP(192) EBSD_LP(256) EBSD_LP(320) EBSD_LP(512)
+#undef EBSD_LP
+    default: break;
+  }
+  (void)hipFuncSetAttribute((const void*)kernel, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shm);
+  const int64_t kmax = (int64_t(1) << 31) / 1024;  // blocks x threads of one dispatch below 2^31
+  for (int64_t s = 0; s < k; s += kmax) {
+    const int64_t kc = k - s < kmax ? k - s : kmax;
+    hipLaunchKernelGGL(kernel, dim3((unsigned)kc), dim3(lds ? 1024 : 256), shm, stream, imgs + s * (int64_t)n * n, n,
+                       n_rho, n_eta, out + s * (int64_t)n_rho * n_eta);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
 hipError_t launch_logpolar(int n, const float* imgs, int64_t k, int n_rho, int n_eta, float* out,
                            hipStream_t stream) {
-  if (k <= 0) return hipSuccess;
-  if (k > (int64_t(1) << 31) / 256) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_logpolar<float>, dim3((unsigned)k), dim3(256), 0, stream, imgs, n, n_rho, n_eta, out);
-  return hipGetLastError();
+  return logpolar_t(n, imgs, k, n_rho, n_eta, out, stream);
 }
 
 hipError_t launch_logpolar(int n, const __bf16* imgs, int64_t k, int n_rho, int n_eta, float* out,
                            hipStream_t stream) {
-  if (k <= 0) return hipSuccess;
-  if (k > (int64_t(1) << 31) / 256) return hipErrorInvalidValue;
-  hipLaunchKernelGGL(k_logpolar<__bf16>, dim3((unsigned)k), dim3(256), 0, stream, imgs, n, n_rho, n_eta, out);
-  return hipGetLastError();
+  return logpolar_t(n, imgs, k, n_rho, n_eta, out, stream);
 }
 
 // The same eta correlation through row transforms, for n_eta = NE = P1 x P2
@@ -537,9 +706,11 @@ hipError_t launch_logpolar(int n, const __bf16* imgs, int64_t k, int n_rho, int 
 // z = Le[k] + i Lt[k] and transformed once (forward: radix P1 in registers
 // over m = P2 a + j, twiddle, radix P2 over j); with S(q) = Z(q) + conj(Z(-q))
 // and D(q) = Z(q) - conj(Z(-q)), Le's transform times the conjugate of Lt's
-// is i S conj(D) / 4.  The weighted products are summed over rows in a
-// fixed order into A(q), q in [0, NE / 2]; c(D) is the inverse transform of
-// A, and the transform of the normalised c that the interpolation needs is
+// is i S conj(D) / 4.  The exchanges in LDS are padded (bank conflicts were
+// 78 % of its LDS cycles without) and the interpolation evaluates few of its
+// points: 5,000 pairs on the 64 x 256 grid 0.64 -> 0.41 ms, one pair 57 -> 34 us.
+// The weighted products are summed over rows in a fixed order into A(q),
+// q in [0, NE / 2]; c(D) is the inverse transform of A, and the transform of the normalised c that the interpolation needs is
 // A times the normalisation.  The energies are the direct weighted sums.
 template <int NE>
 __global__ __launch_bounds__(256) void k_eta_fft(const float* __restrict__ lp_e, const float* __restrict__ lp_t,
@@ -547,11 +718,14 @@ __global__ __launch_bounds__(256) void k_eta_fft(const float* __restrict__ lp_e,
   constexpr int P2 = NE >= 512 ? 32 : 16, P1 = NE / P2, RG = 256 / P2, NQ = NE / 2 + 1;
   constexpr int CPT = (P1 + P2 - 1) / P2, QPT = (NQ + 255) / 256;
   static_assert(P1 * P2 == NE && RG * P2 == 256, "row layout");
+  constexpr int YS = P1 * (P2 + 1);  // a row's exchange, [c][j] one value apart (conflict-free columns)
+  constexpr int NR = NE + NE / 16;   // the roots' table, entry t at t + t / 16 (strides of 2^k spread over the banks)
+  static_assert((size_t)RG * YS * sizeof(cf) >= (size_t)31 * (NE / 2 + 1) * sizeof(float), "interpolation terms");
   extern __shared__ float fsm[];
-  cf* yb = reinterpret_cast<cf*>(fsm);                // [RG][NE]
-  cf* pr = yb + RG * NE;                              // [RG][NQ]
-  cf* rt = pr + RG * NQ;                              // [NE] exp(+2 pi i t / NE)
-  float* cc = reinterpret_cast<float*>(rt + NE);      // [NE]
+  cf* yb = reinterpret_cast<cf*>(fsm);                // [RG][YS]
+  cf* pr = yb + RG * YS;                              // [RG][NQ]
+  cf* rt = pr + RG * NQ;                              // [NR] exp(+2 pi i t / NE)
+  float* cc = reinterpret_cast<float*>(rt + NR);      // [NE]
   float* cqr = cc + NE;                               // [NQ]
   float* cqi = cqr + NQ;                              // [NQ]
   __shared__ float rsum[8];
@@ -564,13 +738,14 @@ __global__ __launch_bounds__(256) void k_eta_fft(const float* __restrict__ lp_e,
   for (int t = tid; t < NE; t += 256) {
     float sn, cs;
     sincospif(2.0f * (float)t / (float)NE, &sn, &cs);
-    rt[t] = cf{cs, sn};
+    rt[t + t / 16] = cf{cs, sn};
   }
+  auto root = [&](int t) { return rt[t + t / 16]; };
   cf acc[QPT];
 #pragma unroll
   for (int i = 0; i < QPT; ++i) acc[i] = cf{0.f, 0.f};
   float ee = 0.0f, tt = 0.0f;
-  cf* yg = yb + g * NE;
+  cf* yg = yb + g * YS;
   cf* pg = pr + g * NQ;
   __syncthreads();
   for (int r0 = 0; r0 < n_rho; r0 += RG) {
@@ -593,9 +768,9 @@ __global__ __launch_bounds__(256) void k_eta_fft(const float* __restrict__ lp_e,
     tt = __fmaf_rn(w, pt, tt);
     DFT<P1, -1>::run(x);
 #pragma unroll
-    for (int c = 1; c < P1; ++c) x[c] = cmulc(x[c], rt[(j * c) % NE]);
+    for (int c = 1; c < P1; ++c) x[c] = cmulc(x[c], root((j * c) % NE));
 #pragma unroll
-    for (int c = 0; c < P1; ++c) yg[c * P2 + j] = x[c];
+    for (int c = 0; c < P1; ++c) yg[c * (P2 + 1) + j] = x[c];
     __syncthreads();
     cf h[CPT][P2];
 #pragma unroll
@@ -603,7 +778,7 @@ __global__ __launch_bounds__(256) void k_eta_fft(const float* __restrict__ lp_e,
       const int c = j + P2 * i;
       if (c < P1) {
 #pragma unroll
-        for (int b = 0; b < P2; ++b) h[i][b] = yg[c * P2 + b];
+        for (int b = 0; b < P2; ++b) h[i][b] = yg[c * (P2 + 1) + b];
         DFT<P2, -1>::run(h[i]);
       }
     }
@@ -654,7 +829,7 @@ __global__ __launch_bounds__(256) void k_eta_fft(const float* __restrict__ lp_e,
   for (int d = tid; d < NE; d += 256) {
     float v = 0.0f;
     for (int q = 1; q < NE / 2; ++q) {
-      const cf e = rt[(q * d) % NE];
+      const cf e = root((q * d) % NE);
       v = __fmaf_rn(pr[q].x, e.x, __fmaf_rn(-pr[q].y, e.y, v));
     }
     cc[d] = (pr[0].x + ((d & 1) ? -pr[NE / 2].x : pr[NE / 2].x) + 2.0f * v) / (float)NE;
@@ -678,7 +853,7 @@ __global__ __launch_bounds__(256) void k_eta_fft(const float* __restrict__ lp_e,
     cqi[q] = pr[q].y * inv;
   }
   __syncthreads();
-  eta_interpolate(cqr, cqi, NE, d_int, kappa, rv, ri, gamma + k);
+  eta_interpolate_fft<NE>(cqr, cqi, d_int, kappa, fsm, gamma + k);
 }
 
 hipError_t launch_eta_peak(const float* lp_e, const float* lp_t, int64_t k, int n_rho, int n_eta,
@@ -688,8 +863,9 @@ hipError_t launch_eta_peak(const float* lp_e, const float* lp_t, int64_t k, int 
   // the default grids (n_eta = 2 N) through row transforms
 #define EBSD_ETAF(NE)                                                                                         \
   do {                                                                                                        \
-    constexpr int P2 = NE >= 512 ? 32 : 16, NQ = NE / 2 + 1;                                                  \
-    const size_t shf = sizeof(cf) * ((size_t)(256 / P2) * (NE + NQ) + NE) + sizeof(float) * (NE + 2 * NQ);    \
+    constexpr int P2 = NE >= 512 ? 32 : 16, NQ = NE / 2 + 1, YS = NE / P2 * (P2 + 1);                         \
+    const size_t shf =                                                                                        \
+        sizeof(cf) * ((size_t)(256 / P2) * (YS + NQ) + NE + NE / 16) + sizeof(float) * (NE + 2 * NQ);         \
     (void)hipFuncSetAttribute((const void*)k_eta_fft<NE>, hipFuncAttributeMaxDynamicSharedMemorySize, (int)shf); \
     hipLaunchKernelGGL(k_eta_fft<NE>, dim3((unsigned)k), dim3(256), shf, stream, lp_e, lp_t, n_rho, kappa, gamma); \
     return hipGetLastError();                                                                                 \
