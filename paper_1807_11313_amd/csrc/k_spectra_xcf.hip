@@ -43,14 +43,33 @@ struct Lay {
 
 __device__ __forceinline__ int signed_shift(int k, int n) { return k >= n / 2 ? k - n : k; }
 
-// exp(+2 pi i k / N), k in [0, N), into LDS (FP64 evaluation, rounded)
+// exp(+2 pi i k / N), k in [0, N): worked out at compile time in FP64, rounded
+// (the values sincospi gives in FP64, rounded)
+template <int N>
+struct RootTable {
+  cf w[N];
+  constexpr RootTable() : w() {
+    for (int k = 0; k < N; ++k) {
+      w[k].x = (float)cx::cos2pi(k, N);
+      w[k].y = (float)cx::sin2pi(k, N);
+    }
+  }
+};
+__constant__ RootTable<64> c_roots64 = RootTable<64>();
+__constant__ RootTable<96> c_roots96 = RootTable<96>();
+__constant__ RootTable<128> c_roots128 = RootTable<128>();
+__constant__ RootTable<160> c_roots160 = RootTable<160>();
+template <int N>
+__device__ __forceinline__ cf root_of(int k) {
+  if constexpr (N == 64) return c_roots64.w[k];
+  else if constexpr (N == 96) return c_roots96.w[k];
+  else if constexpr (N == 128) return c_roots128.w[k];
+  else return c_roots160.w[k];
+}
+
 template <int N, int NT>
 __device__ __forceinline__ void load_roots(cf* tw, int tid) {
-  for (int k = tid; k < N; k += NT) {
-    double s, c;
-    sincospi(2.0 * (double)k / (double)N, &s, &c);
-    tw[k] = cf{(float)c, (float)s};
-  }
+  for (int k = tid; k < N; k += NT) tw[k] = root_of<N>(k);
 }
 
 // ---------------------------------------------------------------------------
@@ -237,18 +256,6 @@ __device__ __forceinline__ __amdgpu_buffer_rsrc_t spectrum_rsrc(const cf* p, int
 __device__ __forceinline__ cf buffer_cf(__amdgpu_buffer_rsrc_t r, unsigned voff, int soff) {
   return __builtin_bit_cast(cf, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
 }
-
-template <int N>
-struct RootTable {
-  cf w[N];
-  constexpr RootTable() : w() {
-    for (int k = 0; k < N; ++k) {
-      w[k].x = (float)cx::cos2pi(k, N);
-      w[k].y = (float)cx::sin2pi(k, N);
-    }
-  }
-};
-__constant__ RootTable<128> c_roots128 = RootTable<128>();
 
 // CAND: template l of pattern p is spec_l[cand[p nl + l]] (a list of nl
 // candidates per pattern, as the learned proposal makes; indices clamped to
@@ -459,18 +466,6 @@ __global__ __launch_bounds__(512, 4) void k_xcf_scores128(const cf* __restrict__
 // transform on row pairs (q, q + N/2) packed as one complex transform, with
 // lanes along q in blocks of QB rows; where R1 is not a multiple of R2 the
 // waves past R1 idle in the second radix pass.
-__constant__ RootTable<64> c_roots64 = RootTable<64>();
-__constant__ RootTable<96> c_roots96 = RootTable<96>();
-__constant__ RootTable<160> c_roots160 = RootTable<160>();
-
-template <int N>
-__device__ __forceinline__ cf root_of(int k) {
-  if constexpr (N == 64) return c_roots64.w[k];
-  else if constexpr (N == 96) return c_roots96.w[k];
-  else if constexpr (N == 128) return c_roots128.w[k];
-  else return c_roots160.w[k];
-}
-
 #ifndef EBSD_SEARCHW_MINW64
 #define EBSD_SEARCHW_MINW64 6
 #endif
@@ -995,29 +990,62 @@ __global__ __launch_bounds__(FLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresf(cons
 
 // ---------------------------------------------------------------------------
 // Forward spectra of K images (pixels of type T: float or __bf16).
+// The image is read from memory once, in 16-byte pieces (any alignment), into
+// LDS (rows R2 values longer, so that a wave's 64 / R2 rows by R2 columns meet
+// distinct banks), where the statistics and the first pass read it; all of a
+// thread's loads are in flight together with the twiddles' and the window's.
+// One block's latency is what bounds it (two blocks per CU by LDS, ten
+// barriers).  4,900 images: 42 / 106 / 175 / 415 us at 64 / 96 / 128 / 160 (47 /
+// 153 / 298 / 790 with 4-byte loads of global memory for both and the roots of
+// unity worked out per block); one image at 128 13 us with its launch (15-20).
+template <class T>
+struct __attribute__((packed)) SpecPx4 {
+  T v[4];
+};
+
 template <int N, int NT, class T>
 __global__ __launch_bounds__(NT) void k_spectra(const T* __restrict__ imgs, int64_t img_stride,
                                                 const int64_t* __restrict__ img_off, FilterParams fp,
                                                 cf* __restrict__ spec, double* __restrict__ energy) {
   using L = Lay<N>;
   constexpr int R1 = L::R1, R2 = L::R2, B = L::B, NV = L::NV, NK = L::NK;
-  __shared__ cf lds[L::LDS];
+  constexpr int IS = N + R2;                                   // row stride of the image in LDS
+  constexpr int PX = N * N / 4, PT = (PX + NT - 1) / NT;       // 16-byte pieces, per thread
+  __shared__ __align__(16) cf lds[L::cmax(L::LDS, N * IS / 2)];
   __shared__ cf tw[N];
   __shared__ float win[N];
   __shared__ double red[2 * (NT / 64)];
+  float* im = reinterpret_cast<float*>(lds);
   const int tid = threadIdx.x;
   const int64_t k = blockIdx.x;
   const T* img = imgs + (img_off ? img_off[k] : k * img_stride);
+  SpecPx4<T> px[PT];
+#pragma unroll
+  for (int j = 0; j < PT; ++j) {
+    const int t = tid + NT * j;
+    if (PX % NT == 0 || t < PX) px[j] = *reinterpret_cast<const SpecPx4<T>*>(img + 4 * t);
+  }
   load_roots<N, NT>(tw, tid);
   for (int i = tid; i < N; i += NT) {
     const float s = sinpif(((float)i + 0.5f) / (float)N);
     win[i] = fp.window ? s * s : 1.0f;
   }
+#pragma unroll
+  for (int j = 0; j < PT; ++j) {
+    const int t = tid + NT * j;
+    if (PX % NT == 0 || t < PX) {
+      const int row = 4 * t / N, col = 4 * t - row * N;
+      *reinterpret_cast<float4*>(im + row * IS + col) =
+          make_float4(ld_px(px[j].v[0]), ld_px(px[j].v[1]), ld_px(px[j].v[2]), ld_px(px[j].v[3]));
+    }
+  }
+  __syncthreads();
 
   // mean and standard deviation in FP64
   double s1 = 0.0, s2 = 0.0;
+#pragma unroll 8
   for (int i = tid; i < N * N; i += NT) {
-    const double v = (double)ld_px(img[i]);
+    const double v = (double)im[i + (i / N) * R2];
     s1 += v;
     s2 += v * v;
   }
@@ -1037,26 +1065,38 @@ __global__ __launch_bounds__(NT) void k_spectra(const T* __restrict__ imgs, int6
   const double var = t2 / (double)(N * N) - mean * mean;
   const float fmean = (float)mean;
   const float inv_std = var > 0.0 ? (float)(1.0 / sqrt(var)) : 0.0f;
-  __syncthreads();
 
-  // row pass, radix R1 on row pairs (q, q + N/2) packed as real + i imag
-  constexpr int TF1 = (N / 2) * R2;
-  for (int t = tid; t < TF1; t += NT) {
-    const int q = t / R2, b = t - q * R2;
-    cf x[R1];
-    const float wq0 = win[q] * inv_std, wq1 = win[q + N / 2] * inv_std;
+  // row pass, radix R1 on row pairs (q, q + N/2) packed as real + i imag; the
+  // values leave the image's LDS before the transforms overwrite it
+  constexpr int TF1 = (N / 2) * R2, JF1 = (TF1 + NT - 1) / NT;
+  cf h1[JF1][R1];
 #pragma unroll
-    for (int a = 0; a < R1; ++a) {
-      const int col = R2 * a + b;
-      const float v0 = (ld_px(img[q * N + col]) - fmean) * wq0 * win[col];
-      const float v1 = (ld_px(img[(q + N / 2) * N + col]) - fmean) * wq1 * win[col];
-      x[a] = cf{v0, v1};
+  for (int j = 0; j < JF1; ++j) {
+    const int t = tid + j * NT;
+    if (t < TF1) {
+      const int q = t / R2, b = t - q * R2;
+      const float wq0 = win[q] * inv_std, wq1 = win[q + N / 2] * inv_std;
+#pragma unroll
+      for (int a = 0; a < R1; ++a) {
+        const int col = R2 * a + b;
+        const float v0 = (im[q * IS + col] - fmean) * wq0 * win[col];
+        const float v1 = (im[(q + N / 2) * IS + col] - fmean) * wq1 * win[col];
+        h1[j][a] = cf{v0, v1};
+      }
+      DFT<R1, -1>::run(h1[j]);
+#pragma unroll
+      for (int c = 1; c < R1; ++c) h1[j][c] = cmulc(h1[j][c], tw[b * c]);
     }
-    DFT<R1, -1>::run(x);
+  }
+  __syncthreads();
 #pragma unroll
-    for (int c = 1; c < R1; ++c) x[c] = cmulc(x[c], tw[b * c]);
+  for (int j = 0; j < JF1; ++j) {
+    const int t = tid + j * NT;
+    if (t < TF1) {
+      const int q = t / R2, b = t - q * R2;
 #pragma unroll
-    for (int c = 0; c < R1; ++c) lds[q * L::YS + c * R2 + b] = x[c];
+      for (int c = 0; c < R1; ++c) lds[q * L::YS + c * R2 + b] = h1[j][c];
+    }
   }
   __syncthreads();
 
@@ -1207,7 +1247,7 @@ bool size_supported(int n) { return band_of(n) > 0; }
 bool fft_supported(int n) { return n == 64 || n == 96 || n == 128 || n == 160; }
 
 template <int N>
-static constexpr int nt_xcf() { return N <= 96 ? 256 : 256; }
+static constexpr int nt_xcf() { return N <= 64 ? 256 : 512; }  // 128: one pair 12.6 us (256 threads: 15.3)
 template <int N>
 static constexpr int nt_spec() { return N <= 96 ? 256 : 512; }
 
