@@ -1333,13 +1333,25 @@ constexpr bool search_flat() { return EBSD_SEARCH_FLAT && (N == 96 || N == 160);
 // spectra) stays in one XCD's 4 MB L2 while the blocks running there stream
 // their patterns, and halves the pattern re-reads of a 32-template chunk at
 // the same time (measured); 128 or more templates no longer fit and raise
-// the traffic again.  The other sizes keep 32.
-static int search_lchunk(int n) { return n == 128 ? 64 : 32; }
+// the traffic again.  The other sizes keep 32.  A block works through its
+// chunk one template after the other, so a call that would leave compute units
+// without one takes shorter chunks, down to 4.  Measured, 1 pattern against
+// 1,000 templates: 42 -> 12 us at 64, 90 -> 14 at 96, 264 -> 22 at 128, 197 ->
+// 32 at 160; 32 against 250: 42 -> 27, 88 -> 63, 246 -> 97, 193 -> 195; 24
+// against 1,000: 73 -> 70, 193 -> 177, 388 -> 279, 584 -> 585.  A chunk's own
+// cost (the pattern's values, the twiddles) sets the number of blocks aimed at:
+// 2,048 at 160 costs 3 to 7 % at 8,000 to 16,000 pairs, 256 at 128 leaves 388.
+static int search_lchunk(int n, int64_t p, int64_t l) {
+  const int64_t blocks = n == 160 ? 512 : (n == 96 ? 1024 : 2048);
+  int c = n == 128 ? 64 : 32;
+  while (c > 4 && p * ((l + c - 1) / c) < blocks) c >>= 1;
+  return c;
+}
 
 hipError_t launch_xcf_scores(int n, const float2* spec_p, int64_t p, const float2* spec_l,
                              int64_t l, int max_shift, float* scores, hipStream_t stream) {
   if (p <= 0 || l <= 0) return hipSuccess;
-  const int lchunk = search_lchunk(n);
+  const int lchunk = search_lchunk(n, p, l);
   const int64_t nchunk = (l + lchunk - 1) / lchunk;
   // patterns per dispatch so that blocks x threads stays below 2^31
   const int64_t pmax = (kMaxItems / 1024 - 8) / nchunk;
@@ -1395,7 +1407,7 @@ hipError_t launch_xcf_scores_cand(int n, const float2* spec_p, int64_t p, const 
   if (p <= 0 || k <= 0) return hipSuccess;
   if (l <= 0) return hipErrorInvalidValue;
   if (n != 128) return hipErrorInvalidValue;
-  const int lchunk = search_lchunk(n);
+  const int lchunk = search_lchunk(n, p, k);
   const int64_t nchunk = (k + lchunk - 1) / lchunk;
   const int64_t pmax = (kMaxItems / 1024 - 8) / nchunk;
   if (pmax < 1) return hipErrorInvalidValue;
@@ -1488,7 +1500,7 @@ hipError_t launch_xcf_peak(int n, const float2* spec_p, const float2* spec_l,
                            const int32_t* pi, const int32_t* li, int64_t k, int max_shift,
                            float* h_int, int32_t* s_int, float* map, hipStream_t stream) {
   if (k <= 0) return hipSuccess;
-  const int64_t kmax = kMaxItems / 256;
+  const int64_t kmax = kMaxItems / 512;
   if (k > kmax) {
     const int64_t sc = (int64_t)(band_of(n) + 1) * (2 * band_of(n) + 1);
     for (int64_t s = 0; s < k; s += kmax) {
