@@ -176,7 +176,9 @@ const char* ebsd_last_error(void);
  *   best_q    float64 [P][4]  lib_q[best_idx]        (may be NULL)
  *   peak_h    float32 [P] upsampled peak height of the winner
  *   shift     float32 [P][2] upsampled (s_x, s_y) px of the winner
- *   scores    float32 [P][L] integer peak of every pair (may be NULL)
+ *   scores    float32 [P][L] integer peak of every pair (may be NULL: large FP32
+ *             searches then drop templates by an upper bound of their peak;
+ *             the picks are the same)
  */
 int ebsd_index_patterns(const ebsd_batch* pats, const ebsd_master* mp, const ebsd_geometry* geo,
                         const double* lib_q, int64_t L, const ebsd_params* prm, int32_t* best_idx,
@@ -188,12 +190,12 @@ int ebsd_index_patterns(const ebsd_batch* pats, const ebsd_master* mp, const ebs
  * and Pattern Centre Refinement", one library at the nominal pattern
  * centre).  ebsd_plan_create projects the L templates at geo's nominal
  * pattern centre and keeps their filtered band spectra, with a copy of
- * lib_q, in device memory the plan owns (L x 38 KB at n = 128); the
- * parameters are fixed with it.  It first checks on the device that every
- * lib_q row is a unit quaternion (| |q| - 1 | <= 1e-6; EBSD_E_INVALID
- * otherwise, nothing kept) and therefore waits for `stream` once.  The
- * spectra are ready in stream order: calls on the same stream may follow at
- * once, calls on another stream after it has been synchronised.
+ * lib_q, in device memory the plan owns (L x 38 KB at n = 128, and 4 KB for
+ * the search's bounds); the parameters are fixed with it.  It first checks on
+ * the device that every lib_q row is a unit quaternion (| |q| - 1 | <= 1e-6;
+ * EBSD_E_INVALID otherwise, nothing kept) and therefore waits for `stream`
+ * once.  The spectra are ready in stream order: calls on the same stream may
+ * follow at once, calls on another stream after it has been synchronised.
  *
  * ebsd_index_patterns_plan is ebsd_index_patterns against the plan's library
  * (pats->n must equal the plan's n; outputs as there, best_q from the plan's
@@ -423,7 +425,9 @@ int ebsd_measure_rotation(const float* pats, const float* tmpls, int64_t K, int3
 /*
  * Instrumentation.  While enabled, every launch of the correlation search
  * kernel (the dominant kernel of ebsd_index_patterns and ebsd_xcf_scores)
- * is bracketed by a pair of HIP events recorded on the caller's stream.
+ * is bracketed by a pair of HIP events recorded on the caller's stream; the
+ * launches of an ebsd_index_patterns search that keeps no score matrix (which
+ * drops templates by a bound before their full correlation) count as one.
  * ebsd_timing_read (after the stream has been synchronised) returns the
  * summed elapsed time in ms and the number of launches, and clears the
  * record.  Not for concurrent use from several threads.

@@ -258,32 +258,88 @@ hipError_t launch_search(int n, const ebsd_params& prm, const float2* sp, int64_
   return launch_xcf_scores(n, sp, p, sl, l, prm.max_shift, out, st);
 }
 
-hipError_t timed_scores(int n, const ebsd_params& prm, const float2* sp, int64_t p, const float2* sl, int64_t l,
-                        const SearchConsts& frag, bool disc, float* out, hipStream_t st) {
-  if (!g_timing) return launch_search(n, prm, sp, p, sl, l, frag, disc, out, st);
+// run(), between an event pair while timing is enabled
+template <class F>
+hipError_t timed(hipStream_t st, F run) {
+  if (!g_timing) return run();
   hipEvent_t a, b;
   hipError_t e;
   if ((e = hipEventCreate(&a)) != hipSuccess) return e;
   if ((e = hipEventCreate(&b)) != hipSuccess) return e;
   if ((e = hipEventRecord(a, st)) != hipSuccess) return e;
-  if ((e = launch_search(n, prm, sp, p, sl, l, frag, disc, out, st)) != hipSuccess) return e;
+  if ((e = run()) != hipSuccess) return e;
   if ((e = hipEventRecord(b, st)) != hipSuccess) return e;
   g_events.emplace_back(a, b);
   return hipSuccess;
+}
+
+hipError_t timed_scores(int n, const ebsd_params& prm, const float2* sp, int64_t p, const float2* sl, int64_t l,
+                        const SearchConsts& frag, bool disc, float* out, hipStream_t st) {
+  return timed(st, [&] { return launch_search(n, prm, sp, p, sl, l, frag, disc, out, st); });
+}
+
+// Whether a search takes the bound-pruned argmax: the FFT form where no score
+// matrix is wanted, at the sizes whose search kernel reads lists, from 2^13
+// pairs on (2^14 at 96, whose full search is the cheapest).  Below that the
+// pruned search's six launches and its lists cost more than they save: a plan's
+// call with 4,000 pairs 121 -> 152 us at 128, 200 -> 200 at 160; 8,000 pairs
+// 174 -> 166 and 309 -> 205, 118 -> 130 at 96; 16,000 pairs 178 -> 134 at 96,
+// 261 -> 163 at 128, 514 -> 206 at 160.
+constexpr int64_t kPruneSlab = int64_t(1) << 26;  // score and list entries held at a time
+bool prunes(int n, const ebsd_params& p) { return p.form == EBSD_FORM_FFT && (n == 96 || n == 128 || n == 160); }
+bool prunes(int n, const ebsd_params& p, int64_t pairs) {
+  return prunes(n, p) && pairs >= (int64_t(1) << (n == 96 ? 14 : 13));
+}
+
+// Best template of every pattern by the pruned search, in slabs of patterns.
+// low_l / stat_l: the library's low parts (a plan keeps them), or null.
+int pruned_best(int n, const ebsd_params& p, const float2* spec_p, int64_t P, const float2* spec_l, int64_t L,
+                const float2* low_l, const float2* stat_l, int32_t* best, ScratchSource& ws, hipStream_t st) {
+  const int64_t sc = spec_complex(n), lc = low_spec_complex();
+  const int64_t slab = std::max<int64_t>(1, std::min({P, kPruneSlab / L, int64_t(1) << 22}));
+  if (!low_l) {
+    EBSD_ALLOC(lo, float2, lc * L, ws);
+    EBSD_ALLOC(sl, float2, L, ws);
+    EBSD_TRY(launch_low_spectra(n, spec_l, L, lo, sl, st), "low spectra(library)");
+    low_l = lo;
+    stat_l = sl;
+  }
+  EBSD_ALLOC(low_p, float2, lc * slab, ws);
+  EBSD_ALLOC(stat_p, float2, slab, ws);
+  EBSD_ALLOC(scores, float, slab * L, ws);
+  EBSD_ALLOC(cand, int32_t, slab * L, ws);
+  EBSD_ALLOC(count, int32_t, slab, ws);
+  EBSD_ALLOC(h0, float, slab, ws);
+  EBSD_ALLOC(items, int2, slab * ((L + kListChunk - 1) / kListChunk), ws);
+  EBSD_ALLOC(queue, int, 2, ws);
+  const PruneScratch t{scores, cand, count, h0, items, queue};
+  for (int64_t s = 0; s < P; s += slab) {
+    const int64_t pc = std::min(slab, P - s);
+    EBSD_TRY(timed(st,
+                   [&] {
+                     const hipError_t e = launch_low_spectra(n, spec_p + s * sc, pc, low_p, stat_p, st);
+                     if (e != hipSuccess) return e;
+                     return launch_pruned_best(n, spec_p + s * sc, low_p, stat_p, pc, spec_l, low_l, stat_l, L,
+                                               p.max_shift, t, best + s, st);
+                   }),
+             "pruned search");
+  }
+  return EBSD_OK;
 }
 
 // Steps A2-A8 of ebsd_index_patterns against library spectra already in
 // spec_l (L templates, orientations lib_q): pattern spectra, search, library
 // argmax, the winner's integer and sub-pixel peaks.
 int index_against(int n, const ebsd_params& p, const float* pats, int64_t P, const float2* spec_l,
-                  const double* lib_q, int64_t L, int32_t* best_idx, double* best_q, float* peak_h, float* shift,
-                  float* scores, ScratchSource& ws, hipStream_t st) {
+                  const float2* low_l, const float2* stat_l, const double* lib_q, int64_t L, int32_t* best_idx,
+                  double* best_q, float* peak_h, float* shift, float* scores, ScratchSource& ws, hipStream_t st) {
   int rc;
   const int64_t sc = spec_complex(n);
   const FilterParams fp = filter_of(p, n);
   EBSD_ALLOC(spec_p, float2, sc * P, ws);
   float* sc_out = scores;
-  if (!sc_out) {
+  const bool prune = !scores && prunes(n, p, P * L);
+  if (!sc_out && !prune) {
     EBSD_ALLOC(tmp_scores, float, P * L, ws);
     sc_out = tmp_scores;
   }
@@ -292,10 +348,14 @@ int index_against(int n, const ebsd_params& p, const float* pats, int64_t P, con
   EBSD_ALLOC(h_tmp, float, P, ws);
   EBSD_ALLOC(roots, float2, subpixel_table_size(n, p.upsample), ws);
   if (int e = pattern_spectra(n, p, pats, P, fp, spec_p, nullptr, ws, st)) return e;
-  SearchConsts consts;
-  if ((rc = search_consts(n, p, ws, st, &consts))) return rc;
-  EBSD_TRY(timed_scores(n, p, spec_p, P, spec_l, L, consts, true, sc_out, st), "xcf_scores");
-  EBSD_TRY(launch_library_argmax(sc_out, P, L, best_idx, h_int, st), "library_argmax");
+  if (prune) {
+    if ((rc = pruned_best(n, p, spec_p, P, spec_l, L, low_l, stat_l, best_idx, ws, st))) return rc;
+  } else {
+    SearchConsts consts;
+    if ((rc = search_consts(n, p, ws, st, &consts))) return rc;
+    EBSD_TRY(timed_scores(n, p, spec_p, P, spec_l, L, consts, true, sc_out, st), "xcf_scores");
+    EBSD_TRY(launch_library_argmax(sc_out, P, L, best_idx, h_int, st), "library_argmax");
+  }
   if (int e = do_peak(n, p, spec_p, spec_l, nullptr, best_idx, P, h_tmp, s_int, ws, st)) return e;
   EBSD_TRY(launch_subpixel_tables(n, p.upsample, roots, st), "subpixel tables");
   EBSD_TRY(launch_subpixel(n, spec_p, spec_l, nullptr, best_idx, P, s_int, p.upsample, roots, peak_h, shift, st),
@@ -541,7 +601,8 @@ int ebsd_index_patterns(const ebsd_batch* pats, const ebsd_master* mp, const ebs
   EBSD_TRY(launch_project(n, mp->data, mp->H, mp->W, lib_q, L, nullptr, geo->pcx, geo->pcy, geo->pcz, tmpl, st),
            "project");
   if (int e = do_spectra(n, tmpl, L, fp, spec_l, nullptr, ws, st)) return e;
-  return index_against(n, p, pats->data, P, spec_l, lib_q, L, best_idx, best_q, peak_h, shift, scores, ws, st);
+  return index_against(n, p, pats->data, P, spec_l, nullptr, nullptr, lib_q, L, best_idx, best_q, peak_h, shift,
+                       scores, ws, st);
 }
 
 
@@ -553,6 +614,8 @@ struct ebsd_plan_s {
   int64_t L;
   float2* spec_l;
   double* lib_q;
+  float2* low_l;   // the pruned search's low parts and their statistics (null where it does not apply)
+  float2* stat_l;
 };
 
 int ebsd_plan_create(const ebsd_master* mp, const ebsd_geometry* geo, const double* lib_q, int64_t L, int32_t n,
@@ -583,11 +646,14 @@ int ebsd_plan_create(const ebsd_master* mp, const ebsd_geometry* geo, const doub
     memcpy(&dev, &bits, sizeof(float));
     if (!(dev <= 1e-6f)) return fail(EBSD_E_INVALID, "library orientations must be unit quaternions");
   }
-  auto* pl = new (std::nothrow) ebsd_plan_s{n, p, L, nullptr, nullptr};
+  auto* pl = new (std::nothrow) ebsd_plan_s{n, p, L, nullptr, nullptr, nullptr, nullptr};
   if (!pl) return fail(EBSD_E_NOMEM, "plan allocation failed");
   const int64_t sc = spec_complex(n);
+  const bool prune = prunes(n, p);
   if (hipMalloc(&pl->spec_l, sizeof(float2) * sc * L) != hipSuccess ||
-      hipMalloc(&pl->lib_q, sizeof(double) * 4 * L) != hipSuccess) {
+      hipMalloc(&pl->lib_q, sizeof(double) * 4 * L) != hipSuccess ||
+      (prune && (hipMalloc(&pl->low_l, sizeof(float2) * low_spec_complex() * L) != hipSuccess ||
+                 hipMalloc(&pl->stat_l, sizeof(float2) * L) != hipSuccess))) {
     ebsd_plan_destroy(pl);
     return fail(EBSD_E_NOMEM, "plan device allocation failed");
   }
@@ -597,7 +663,9 @@ int ebsd_plan_create(const ebsd_master* mp, const ebsd_geometry* geo, const doub
     EBSD_ALLOC(tmpl, float, (int64_t)n * n * L, ws);
     EBSD_TRY(launch_project(n, mp->data, mp->H, mp->W, lib_q, L, nullptr, geo->pcx, geo->pcy, geo->pcz, tmpl, st),
              "project");
-    return do_spectra(n, tmpl, L, filter_of(p, n), pl->spec_l, nullptr, ws, st);
+    if (int e = do_spectra(n, tmpl, L, filter_of(p, n), pl->spec_l, nullptr, ws, st)) return e;
+    if (prune) EBSD_TRY(launch_low_spectra(n, pl->spec_l, L, pl->low_l, pl->stat_l, st), "low spectra(library)");
+    return EBSD_OK;
   }();
   if (rc) {
     (void)hipStreamSynchronize(st);
@@ -620,14 +688,16 @@ int ebsd_index_patterns_plan(ebsd_plan plan, const ebsd_batch* pats, int32_t* be
   if (!pats->data || !best_idx || !peak_h || !shift) return fail(EBSD_E_INVALID, "null pointer");
   hipStream_t st = (hipStream_t)stream;
   Scratch ws(st);
-  return index_against(plan->n, plan->p, pats->data, P, plan->spec_l, plan->lib_q, plan->L, best_idx, best_q,
-                       peak_h, shift, scores, ws, st);
+  return index_against(plan->n, plan->p, pats->data, P, plan->spec_l, plan->low_l, plan->stat_l, plan->lib_q, plan->L,
+                       best_idx, best_q, peak_h, shift, scores, ws, st);
 }
 
 int ebsd_plan_destroy(ebsd_plan plan) {
   if (!plan) return EBSD_OK;
   if (plan->spec_l) (void)hipFree(plan->spec_l);
   if (plan->lib_q) (void)hipFree(plan->lib_q);
+  if (plan->low_l) (void)hipFree(plan->low_l);
+  if (plan->stat_l) (void)hipFree(plan->stat_l);
   delete plan;
   return EBSD_OK;
 }

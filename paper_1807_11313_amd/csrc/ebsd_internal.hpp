@@ -68,10 +68,35 @@ hipError_t launch_xcf_scores_persistent(int n, const float2* spec_p, int64_t p, 
 hipError_t launch_xcf_scores(int n, const float2* spec_p, int64_t p, const float2* spec_l,
                              int64_t l, int max_shift, float* scores, hipStream_t stream);
 // The same for each pattern's own k candidates among l templates: scores[p][j]
-// for template cand[p][j], clamped to [0, l) (n = 128; hipErrorInvalidValue for
-// other sizes).
+// for template cand[p][j], clamped to [0, l) (n = 96, 128, 160;
+// hipErrorInvalidValue for other sizes), and for lists of their own lengths,
+// cand[p][j], j < count[p] <= l, in rows of l, as queue[1] chunks (pattern,
+// first entry) of up to kListChunk entries; queue[0] is 0 at entry.
 hipError_t launch_xcf_scores_cand(int n, const float2* spec_p, int64_t p, const float2* spec_l, int64_t l,
                                   const int32_t* cand, int k, int max_shift, float* scores, hipStream_t stream);
+constexpr int kListChunk = 8;
+hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_items, const float2* spec_l, int64_t l,
+                                   const int32_t* cand, const int32_t* count, const int2* items, int* queue,
+                                   int max_shift, float* scores, hipStream_t stream);
+
+// Best template of every pattern under the FFT search without the score matrix
+// (k_prune.hip; n = 96, 128, 160).  low and stat of both sides come from
+// launch_low_spectra (low_spec_complex() values and one float2 per spectrum).
+// PruneScratch: scores and cand [p][l], count and h0 [p], items
+// [p][ceil(l / kListChunk)], queue [2].
+struct PruneScratch {
+  float* scores;
+  int32_t* cand;
+  int32_t* count;
+  float* h0;
+  int2* items;
+  int* queue;
+};
+int64_t low_spec_complex();
+hipError_t launch_low_spectra(int n, const float2* spec, int64_t k, float2* low, float2* stat, hipStream_t stream);
+hipError_t launch_pruned_best(int n, const float2* spec_p, const float2* low_p, const float2* stat_p, int64_t p,
+                              const float2* spec_l, const float2* low_l, const float2* stat_l, int64_t l,
+                              int max_shift, const PruneScratch& ws, int32_t* best, hipStream_t stream);
 
 // Integer peak (value, signed shift) for K explicit pairs (pi[k], li[k]),
 // and optionally the full correlation map [K][n][n] (row = s_y mod n).

@@ -1,0 +1,288 @@
+// Bound-pruned library argmax (gfx950): the best template of every pattern under the FP32 FFT
+// search, without the full-size transform of the pairs that cannot win.
+//
+// For band-limited spectra the correlation splits into rho = low + high, low the part of the
+// coefficients with |u|, |v| <= 15:
+//   |high(s)| <= sum_high |E||T| <= sqrt(eh_E eh_T)      (Cauchy-Schwarz; eh = energy of the high part),
+//   low(s)    <= max of low over the corners of s's cell of a 32 x 32 shift grid, h = N / 32 px apart,
+//                + h^2 / 8 (|low_xx| + |low_yy|)          (a bilinear interpolant's error),
+//   |low_xx| + |low_yy| <= (2 pi / N)^2 sum_low |E||T| (u^2 + v^2) <= sqrt(k_E k_T),
+//                k = (2 pi / N)^2 sum_low |X|^2 (u^2 + v^2).
+// So   score(p, l) <= coarse(p, l) + h^2 / 8 sqrt(k_p k_l) + sqrt(eh_p eh_l) + rounding,
+// where coarse is the largest low value of the grid and the other terms are products of two numbers
+// per spectrum.  With h0, the full-size score of the template with the largest coarse value, every
+// template whose bound lies below h0 is out.  The others (0.8 % of a 4,000-template library for patterns
+// that match it, SNR 5) get their full-size score from the search kernel itself, so the pick is that of
+// the whole score matrix, bit for bit, ties included.  Patterns that match nothing keep most of their
+// templates; then the coarse values and the lists come on top of the full search: 200 patterns of noise
+// against 3,000 templates 4.28 -> 5.10 ms at 96, 6.66 -> 7.28 at 128, 14.4 -> 15.5 at 160, where 200
+// patterns of the library's material take 4.28 -> 0.56, 6.66 -> 0.61 and 14.4 -> 0.74 ms (whole calls).
+#include "ebsd_common.hpp"
+#include "ebsd_internal.hpp"
+
+#include <math.h>
+
+#include <algorithm>
+
+namespace ebsd {
+
+namespace {
+
+typedef float f4 __attribute__((ext_vector_type(4)));
+
+constexpr int BL = 15, G = 32;       // low band, grid points per axis
+constexpr int FRAG = 4 * 64;         // float4 values of one spectrum's low part
+constexpr int PT = 16, TC = 16;      // patterns per block, most templates per wave of the coarse kernel
+
+// Both evaluations round: each transform's error is a few ulp of sum |Z| <= 1 per pass
+constexpr float kRound = 1e-5f;
+
+// The low part of each spectrum in the coarse kernel's order, (X(u), X(-u)) of u = 4 (lane / 16) + j,
+// v = lane % 16 at [j][lane] (X(-0) = 0), and stat = (sqrt(eh), sqrt(k)); one block per spectrum
+__global__ __launch_bounds__(256) void k_low_spectra(const cf* __restrict__ spec, int n, int bnd,
+                                                     f4* __restrict__ low, float2* __restrict__ stat) {
+  const int nv = bnd + 1, nk = 2 * bnd + 1, spec_n = nv * nk;
+  const int64_t k = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63;
+  const cf* S = spec + k * spec_n;
+  const int u0 = 4 * (lane >> 4) + (tid >> 6), v0 = lane & 15;
+  const cf xp = S[u0 * nv + v0], xm = u0 ? S[(nk - u0) * nv + v0] : cf{0.f, 0.f};
+  low[k * FRAG + tid] = f4{xp.x, xp.y, xm.x, xm.y};
+  float eh = 0.0f, kl = 0.0f;
+  for (int t = tid; t < spec_n; t += 256) {
+    const int kk = t / nv, v = t - kk * nv;
+    const int u = kk <= bnd ? kk : kk - nk;
+    const cf z = S[t];
+    const float e = (v == 0 ? 1.0f : 2.0f) * (z.x * z.x + z.y * z.y);
+    if (abs(u) <= BL && v <= BL) kl += e * (float)(u * u + v * v);
+    else eh += e;
+  }
+  eh = wave_sum(eh);
+  kl = wave_sum(kl);
+  __shared__ float red[2][4];
+  if (lane == 0) {
+    red[0][tid >> 6] = eh;
+    red[1][tid >> 6] = kl;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    const float tpn = 6.2831855f / (float)n;
+    stat[k] = make_float2(sqrtf(red[0][0] + red[0][1] + red[0][2] + red[0][3]),
+                          tpn * sqrtf(red[1][0] + red[1][1] + red[1][2] + red[1][3]));
+  }
+}
+
+// Largest value of the wave's 64 lanes in lane 63 (NaN is passed over)
+template <int CTRL>
+__device__ __forceinline__ float dpp_max(float v) {
+  const int o = __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, -INFINITY), __builtin_bit_cast(int, v), CTRL, 0xf,
+                                            0xf, false);
+  return fmaxf(v, __builtin_bit_cast(float, o));
+}
+__device__ __forceinline__ float wave_max_last(float v) {
+  v = dpp_max<0x111>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row
+  v = dpp_max<0x112>(v);
+  v = dpp_max<0x114>(v);
+  v = dpp_max<0x118>(v);
+  v = dpp_max<0x142>(v);  // row_bcast 15, 31
+  return dpp_max<0x143>(v);
+}
+
+// coarse[p][l] = the largest low value over the grid points t h, t = +-(j + 1/2), j <= last (both axes), by
+// the +-u, +-s symmetric products of k_xcf_even.hip in FP32: one 16 x 16 tile per stage (u and j below
+// 16, v and j below 16), 32 of v_mfma_f32_16x16x4_f32 a pair, which with about 100 vector instructions is
+// what bounds it.  A block holds PT patterns in LDS; each of its 8 waves takes tc templates in turn,
+// a template's 16 values per lane serving all the patterns; every phase constant stays in registers.
+// 200 x 3,000 pairs take 424 us (1.4e9 pairs/s; 381 us is 1,400 cycles a pair and SIMD); a 64 x 64 FFT search
+// of wider low parts (|u|, |v| <= 24) in its place ran at 4.2e8 pairs/s.  4 KB a spectrum are read
+// once per block of 16 patterns and 128 templates: 2 % of the time.
+__global__ __launch_bounds__(512, 4) void k_coarse(const f4* __restrict__ low_p, int64_t np,
+                                                   const f4* __restrict__ low_l, int64_t nl, int64_t npt,
+                                                   int64_t nblk, int tc, int last, float* __restrict__ coarse,
+                                                   int* __restrict__ queue) {
+  __shared__ f4 ep[PT * FRAG];
+  __shared__ float out[PT][8 * TC];
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, q4 = lane >> 4;
+  if (blockIdx.x == 0 && tid < 2) queue[tid] = 0;  // for the lists of the templates that are kept
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t per = (nblk + 7) / 8;
+  const int64_t g = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (g >= nblk) return;
+  const int64_t chunk = g / npt, p0 = (g - chunk * npt) * PT, l0 = chunk * (8 * tc);
+  const int pc = (int)(np - p0 < PT ? np - p0 : PT);
+  for (int i = tid; i < pc * FRAG; i += 512) ep[i] = low_p[p0 * FRAG + i];
+  // stage 1: cos, sin of 2 pi u (j + 1/2) / G for this lane's column j = r16 and rows u = 4 q + i; stage 2: the
+  // same with v in the place of u and the Hermitian weight
+  float c1[4], s1[4], c2[4], s2[4];
+#pragma unroll
+  for (int i = 0; i < 4; ++i) {
+    const int f = 4 * q4 + i;
+    sincospif((float)(f * (2 * r16 + 1)) / (float)G, &s1[i], &c1[i]);
+    c2[i] = f ? 2.0f * c1[i] : c1[i];
+    s2[i] = f ? 2.0f * s1[i] : s1[i];
+  }
+  __syncthreads();
+#pragma unroll 1
+  for (int t = 0; t < tc; ++t) {
+    const int64_t l = l0 + wave * tc + t;
+    if (l >= nl) break;
+    f4 tv[4];
+#pragma unroll
+    for (int j = 0; j < 4; ++j) tv[j] = low_l[l * FRAG + j * 64 + lane];
+#pragma unroll 1
+    for (int pb = 0; pb < pc; ++pb) {
+      f4 acc[4], r[4];
+#pragma unroll
+      for (int c = 0; c < 4; ++c) {
+        acc[c] = f4{0.f, 0.f, 0.f, 0.f};
+        r[c] = f4{0.f, 0.f, 0.f, 0.f};
+      }
+#pragma unroll
+      for (int j = 0; j < 4; ++j) {
+        const f4 e = ep[pb * FRAG + j * 64 + lane], x = tv[j];
+        const float mr = __fmaf_rn(e[2], x[2], e[3] * x[3]), mi = __fmaf_rn(e[3], x[2], -(e[2] * x[3]));
+        const float ar = __fmaf_rn(e[0], x[0], __fmaf_rn(e[1], x[1], mr));
+        const float ai = __fmaf_rn(e[1], x[0], __fmaf_rn(-e[0], x[1], mi));
+        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, c1[j], acc[0], 0, 0, 0);
+        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai, c1[j], acc[1], 0, 0, 0);
+        acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(__fmaf_rn(-2.0f, mr, ar), s1[j], acc[2], 0, 0, 0);
+        acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(__fmaf_rn(-2.0f, mi, ai), s1[j], acc[3], 0, 0, 0);
+      }
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        r[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(c2[i], acc[0][i], r[0], 0, 0, 0);
+        r[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(c2[i], acc[3][i], r[1], 0, 0, 0);
+        r[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(s2[i], acc[1][i], r[2], 0, 0, 0);
+        r[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(s2[i], acc[2][i], r[3], 0, 0, 0);
+      }
+      float m = -INFINITY;
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float v = fmaxf((r[0][i] - r[1][i]) + fabsf(r[2][i] + r[3][i]),
+                              (r[0][i] + r[1][i]) + fabsf(r[2][i] - r[3][i]));
+        m = fmaxf(m, 4 * q4 + i <= last ? v : -INFINITY);
+      }
+      m = wave_max_last(r16 <= last ? m : -INFINITY);
+      if (lane == 63) out[pb][wave * tc + t] = m;
+    }
+  }
+  __syncthreads();
+  for (int i = tid; i < pc * 8 * tc; i += 512) {
+    const int pb = i / (8 * tc), c = i - pb * (8 * tc);
+    if (l0 + c < nl) coarse[(p0 + pb) * nl + l0 + c] = out[pb][c];
+  }
+}
+
+// The templates of each pattern that its bound keeps: cand[p l ..] (any order) and count[p], and their chunks
+// in the queue
+__global__ __launch_bounds__(256) void k_prune_select(const float* __restrict__ coarse, int64_t l, float h28,
+                                                      const float2* __restrict__ stat_p,
+                                                      const float2* __restrict__ stat_l,
+                                                      const float* __restrict__ h0, int32_t* __restrict__ cand,
+                                                      int32_t* __restrict__ count, int2* __restrict__ items,
+                                                      int* __restrict__ queue) {
+  const int64_t p = blockIdx.x;
+  const int lane = threadIdx.x & 63;
+  __shared__ int kept;
+  if (threadIdx.x == 0) kept = 0;
+  __syncthreads();
+  const float2 sp = stat_p[p];
+  const float eh = 1.0002f * sp.x, kl = 1.0002f * h28 * sp.y, least = h0[p] - kRound;
+  for (int64_t i0 = 0; i0 < l; i0 += 256) {
+    const int64_t i = i0 + threadIdx.x;
+    bool keep = false;
+    if (i < l) {
+      const float2 sl = stat_l[i];
+      keep = coarse[p * l + i] + __fmaf_rn(kl, sl.y, eh * sl.x) >= least;
+    }
+    const unsigned long long mask = __ballot(keep);
+    if (mask == 0) continue;
+    int at = 0;
+    if (lane == 0) at = atomicAdd(&kept, __popcll(mask));
+    at = __shfl(at, 0, 64) + __popcll(mask & ((1ull << lane) - 1));
+    if (keep) cand[p * l + at] = (int32_t)i;
+  }
+  __syncthreads();
+  const int nc = (kept + kListChunk - 1) / kListChunk;
+  __shared__ int first;
+  if (threadIdx.x == 0) {
+    count[p] = kept;
+    first = nc ? atomicAdd(queue + 1, nc) : 0;
+  }
+  __syncthreads();
+  for (int i = threadIdx.x; i < nc; i += 256) items[first + i] = make_int2((int)p, i * kListChunk);
+}
+
+// Best of the kept templates (ties: smallest index; none kept, every score NaN: 0)
+__global__ __launch_bounds__(256) void k_prune_argmax(const float* __restrict__ scores,
+                                                      const int32_t* __restrict__ cand,
+                                                      const int32_t* __restrict__ count, int64_t l,
+                                                      int32_t* __restrict__ best) {
+  const int64_t p = blockIdx.x;
+  float bv = -INFINITY;
+  int bi = 0x7fffffff;
+  for (int i = threadIdx.x; i < count[p]; i += 256) argmax_merge(bv, bi, scores[p * l + i], cand[p * l + i]);
+  wave_argmax(bv, bi);
+  __shared__ float rv[4];
+  __shared__ int ri[4];
+  if ((threadIdx.x & 63) == 0) {
+    rv[threadIdx.x >> 6] = bv;
+    ri[threadIdx.x >> 6] = bi;
+  }
+  __syncthreads();
+  if (threadIdx.x == 0) {
+    for (int w = 1; w < 4; ++w) argmax_merge(bv, bi, rv[w], ri[w]);
+    best[p] = bi < 0 || bi >= l ? 0 : bi;
+  }
+}
+
+}  // namespace
+
+int64_t low_spec_complex() { return FRAG * 2; }
+
+hipError_t launch_low_spectra(int n, const float2* spec, int64_t k, float2* low, float2* stat, hipStream_t stream) {
+  if (k <= 0) return hipSuccess;
+  const int bnd = band_of(n);
+  if (bnd < BL + 1) return hipErrorInvalidValue;
+  const int64_t sc = (int64_t)(bnd + 1) * (2 * bnd + 1), kmax = (int64_t(1) << 31) / 256;
+  for (int64_t s = 0; s < k; s += kmax) {
+    hipLaunchKernelGGL(k_low_spectra, dim3((unsigned)(k - s < kmax ? k - s : kmax)), dim3(256), 0, stream,
+                       (const cf*)spec + s * sc, n, bnd, (f4*)low + s * FRAG, stat + s);
+    const hipError_t e = hipGetLastError();
+    if (e != hipSuccess) return e;
+  }
+  return hipSuccess;
+}
+
+hipError_t launch_pruned_best(int n, const float2* spec_p, const float2* low_p, const float2* stat_p, int64_t p,
+                              const float2* spec_l, const float2* low_l, const float2* stat_l, int64_t l,
+                              int max_shift, const PruneScratch& ws, int32_t* best, hipStream_t stream) {
+  if (p <= 0) return hipSuccess;
+  if (p > (int64_t(1) << 31) / 256) return hipErrorInvalidValue;
+  hipError_t e;
+  const float h = (float)n / (float)G;
+  // the grid's cells that cover a shift window
+  const int last = max_shift < 0 ? 15 : std::min(15, std::max(0, (int)ceilf((float)max_shift / h - 0.5f)));
+  // templates per wave: TC, fewer where that leaves less than four rounds of the 512 blocks that run at once
+  int tc = TC;
+  while (tc > 1 && ((p + PT - 1) / PT) * ((l + 8 * tc - 1) / (8 * tc)) < 2048) tc >>= 1;
+  const int64_t nch = (l + 8 * tc - 1) / (8 * tc), pmax = std::max<int64_t>(1, ((int64_t(1) << 31) / 512 - 8) / nch) * PT;
+  for (int64_t s = 0; s < p; s += pmax) {
+    const int64_t pc = p - s < pmax ? p - s : pmax, npt = (pc + PT - 1) / PT, nblk = npt * nch;
+    hipLaunchKernelGGL(k_coarse, dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(512), 0, stream, (const f4*)low_p + s * FRAG,
+                       pc, (const f4*)low_l, l, npt, nblk, tc, last, ws.scores + s * l, ws.queue);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+  }
+  if ((e = launch_library_argmax(ws.scores, p, l, best, ws.h0, stream)) != hipSuccess) return e;
+  if ((e = launch_xcf_scores_cand(n, spec_p, p, spec_l, l, best, 1, max_shift, ws.h0, stream)) != hipSuccess) return e;
+  hipLaunchKernelGGL(k_prune_select, dim3((unsigned)p), dim3(256), 0, stream, ws.scores, l, 0.125f * h * h, stat_p,
+                     stat_l, ws.h0, ws.cand, ws.count, ws.items, ws.queue);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = launch_xcf_scores_lists(n, spec_p, p * ((l + kListChunk - 1) / kListChunk), spec_l, l, ws.cand, ws.count,
+                                   ws.items, ws.queue, max_shift, ws.scores, stream)) != hipSuccess)
+    return e;
+  hipLaunchKernelGGL(k_prune_argmax, dim3((unsigned)p), dim3(256), 0, stream, ws.scores, ws.cand, ws.count, l, best);
+  return hipGetLastError();
+}
+
+}  // namespace ebsd

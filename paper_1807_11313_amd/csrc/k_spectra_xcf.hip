@@ -259,14 +259,18 @@ __device__ __forceinline__ cf buffer_cf(__amdgpu_buffer_rsrc_t r, unsigned voff,
 
 // CAND: template l of pattern p is spec_l[cand[p nl + l]] (a list of nl
 // candidates per pattern, as the learned proposal makes; indices clamped to
-// [0, lib_n)) instead of spec_l[l]
+// [0, lib_n)) instead of spec_l[l].  With PERSIST the lists have count[p]
+// entries in rows of nl, and work item g is chunk items[g] = (pattern, first
+// entry), g < queue[1]
 template <bool WINDOW, bool PERSIST, bool CAND = false>
 __global__ __launch_bounds__(512, 4) void k_xcf_scores128(const cf* __restrict__ spec_p, int64_t np,
                                                           const cf* __restrict__ spec_l, int64_t nl,
                                                           int lchunk, int64_t nblk, int max_shift,
                                                           float* __restrict__ scores, int* __restrict__ queue,
                                                           const int32_t* __restrict__ cand = nullptr,
-                                                          int64_t lib_n = 0) {
+                                                          int64_t lib_n = 0,
+                                                          const int32_t* __restrict__ count = nullptr,
+                                                          const int2* __restrict__ items = nullptr) {
   constexpr int N = 128, R1 = 16, R2 = 8, B = 48, NV = 49;
   constexpr int SPEC = NV * (2 * B + 1);
   constexpr int GAP = band_gap_mask<N, R1, R2, B>();  // a = 7, 8, 9
@@ -290,6 +294,7 @@ __global__ __launch_bounds__(512, 4) void k_xcf_scores128(const cf* __restrict__
     const int64_t per = (nblk + 7) / 8;
     g = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
   }
+  if constexpr (CAND && PERSIST) nblk = queue[1];
   if (g >= nblk) return;
   const bool vlane = lane < NV;
 
@@ -299,7 +304,17 @@ __global__ __launch_bounds__(512, 4) void k_xcf_scores128(const cf* __restrict__
   for (int c = 0; c < R1; ++c) tw[c] = c_roots128.w[(wave * c) & (N - 1)];
 
   while (g < nblk) {
-  const int64_t chunk = g / np, p = g - chunk * np;
+  int64_t p, l0, ln = nl;
+  if constexpr (CAND && PERSIST) {
+    const int2 it = items[g];
+    p = it.x;
+    l0 = it.y;
+    ln = count[p];
+  } else {
+    const int64_t chunk = g / np;
+    p = g - chunk * np;
+    l0 = chunk * lchunk;
+  }
   // pattern spectrum values used by this lane in phase 1
   const cf* E = spec_p + p * SPEC;
   cf ev[R1];
@@ -310,8 +325,7 @@ __global__ __launch_bounds__(512, 4) void k_xcf_scores128(const cf* __restrict__
     ev[a] = (kk >= 0 && vlane) ? E[kk * NV + lane] : cf{0.f, 0.f};
   }
 
-  const int64_t l0 = chunk * lchunk;
-  const int64_t l1 = l0 + lchunk < nl ? l0 + lchunk : nl;
+  const int64_t l1 = l0 + lchunk < ln ? l0 + lchunk : ln;
   for (int64_t l = l0; l < l1; ++l) {
     int64_t tl = l;
     if constexpr (CAND) {
@@ -769,11 +783,15 @@ constexpr int band_class_nb(int lo, int hi) {
   return hi <= B ? kPos : (lo >= N - B ? kNeg : ((lo > B && hi < N - B) ? kGap : kStraddle));
 }
 
-template <int N, bool WINDOW, bool PERSIST>
+template <int N, bool WINDOW, bool PERSIST, bool CAND = false>
 __global__ __launch_bounds__(FLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresf(const cf* __restrict__ spec_p, int64_t np,
                                                              const cf* __restrict__ spec_l, int64_t nl,
                                                              int lchunk, int64_t nblk, int max_shift,
-                                                             float* __restrict__ scores, int* __restrict__ queue) {
+                                                             float* __restrict__ scores, int* __restrict__ queue,
+                                                             const int32_t* __restrict__ cand = nullptr,
+                                                             int64_t lib_n = 0,
+                                                             const int32_t* __restrict__ count = nullptr,
+                                                             const int2* __restrict__ items = nullptr) {
   using L = WLay<N>;
   using F = FLay<N>;
   constexpr int R1 = L::R1, R2 = L::R2, B = L::B, NV = L::NV, SPEC = L::SPEC, AV = L::AV;
@@ -838,10 +856,21 @@ __global__ __launch_bounds__(FLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresf(cons
     g = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
     __syncthreads();  // the twiddle table
   }
+  if constexpr (CAND && PERSIST) nblk = queue[1];
   if (g >= nblk) return;
 
   while (g < nblk) {
-    const int64_t chunk = g / np, p = g - chunk * np;
+    int64_t p, l0, ln = nl;
+    if constexpr (CAND && PERSIST) {
+      const int2 it = items[g];
+      p = it.x;
+      l0 = it.y;
+      ln = count[p];
+    } else {
+      const int64_t chunk = g / np;
+      p = g - chunk * np;
+      l0 = chunk * lchunk;
+    }
     const cf* E = spec_p + p * SPEC;
     cf ev[R1];
 #pragma unroll
@@ -850,8 +879,15 @@ __global__ __launch_bounds__(FLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresf(cons
       const int kk = u <= B ? u : (u >= N - B ? u - N + 2 * B + 1 : -1);
       ev[a] = (kk >= 0 && act1) ? E[kk * NV + v1] : cf{0.f, 0.f};
     }
-    const int64_t l0 = chunk * lchunk;
-    const int64_t l1 = l0 + lchunk < nl ? l0 + lchunk : nl;
+    const int64_t l1 = l0 + lchunk < ln ? l0 + lchunk : ln;
+    const auto tmpl = [&](int64_t l) {
+      if constexpr (CAND) {
+        const int64_t tl = cand[p * nl + l];
+        return spec_l + (tl < 0 ? 0 : (tl >= lib_n ? lib_n - 1 : tl)) * SPEC;
+      } else {
+        return spec_l + l * SPEC;
+      }
+    };
     // pass-1 inputs of template T.  At 96 they are issued one template ahead
     // (before the last pass 4 of the template before), so that their latency
     // overlaps that pass and the barrier after it (measured 1.05x); at 160
@@ -875,11 +911,11 @@ __global__ __launch_bounds__(FLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresf(cons
         else xn[a] = *reinterpret_cast<const cf*>(reinterpret_cast<const char*>(T) + vo + so);
       });
     };
-    if (PREFETCH && act1) load1(spec_l + l0 * SPEC);
+    if (PREFETCH && act1) load1(tmpl(l0));
     for (int64_t l = l0; l < l1; ++l) {
       // pass 1: item (b1, v1): radix R1 over u = R2 a + b1, twiddle
       if (act1) {
-        if constexpr (!PREFETCH) load1(spec_l + l * SPEC);
+        if constexpr (!PREFETCH) load1(tmpl(l));
         cf x[R1];
 #pragma unroll
         for (int a = 0; a < R1; ++a)
@@ -939,7 +975,7 @@ __global__ __launch_bounds__(FLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresf(cons
           for (int c = 0; c < R1; ++c) Y[(c * R2 + b3) * QB + q3] = sv[c];
         }
         __syncthreads();
-        if (PREFETCH && qb + 1 == NQB && act1 && l + 1 < l1) load1(spec_l + (l + 1) * SPEC);
+        if (PREFETCH && qb + 1 == NQB && act1 && l + 1 < l1) load1(tmpl(l + 1));
         // pass 4: item (c4, q4): radix R2 over b -> x = c4 + R1 d
 #pragma unroll
         for (int r = 0; r < R4; ++r) {
@@ -1398,39 +1434,60 @@ hipError_t launch_xcf_scores(int n, const float2* spec_p, int64_t p, const float
   return hipGetLastError();
 }
 
-// Scores of each pattern against its own list of k candidate templates
-// (scores[p k + j] for template cand[p k + j]), by the library search kernel
-// (128 only; other sizes return hipErrorInvalidValue and the caller takes
-// the single-pair kernel).
+// Scores of each pattern against its own k templates, scores[p k + j] for template cand[p k + j], by the
+// library search kernel (96, 128 and 160)
 hipError_t launch_xcf_scores_cand(int n, const float2* spec_p, int64_t p, const float2* spec_l, int64_t l,
                                   const int32_t* cand, int k, int max_shift, float* scores, hipStream_t stream) {
   if (p <= 0 || k <= 0) return hipSuccess;
   if (l <= 0) return hipErrorInvalidValue;
-  if (n != 128) return hipErrorInvalidValue;
   const int lchunk = search_lchunk(n, p, k);
   const int64_t nchunk = (k + lchunk - 1) / lchunk;
   const int64_t pmax = (kMaxItems / 1024 - 8) / nchunk;
   if (pmax < 1) return hipErrorInvalidValue;
-  if (p > pmax) {
-    const int64_t sc = (int64_t)(band_of(n) + 1) * (2 * band_of(n) + 1);
-    for (int64_t s = 0; s < p; s += pmax) {
-      const hipError_t e = launch_xcf_scores_cand(n, spec_p + s * sc, p - s < pmax ? p - s : pmax, spec_l, l,
-                                                  cand + s * k, k, max_shift, scores + s * k, stream);
-      if (e != hipSuccess) return e;
-    }
-    return hipSuccess;
+  const int64_t sc = (int64_t)(band_of(n) + 1) * (2 * band_of(n) + 1);
+  for (int64_t s = 0; s < p; s += pmax) {
+    const int64_t pc = p - s < pmax ? p - s : pmax, nblk = pc * nchunk;
+    const dim3 grid((unsigned)((nblk + 7) / 8 * 8));
+    const auto run = [&](auto kernel, int threads) {
+      hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, (const cf*)spec_p + s * sc, pc, (const cf*)spec_l,
+                         (int64_t)k, lchunk, nblk, max_shift, scores + s * k, (int*)nullptr, cand + s * k, l,
+                         (const int32_t*)nullptr, (const int2*)nullptr);
+      return hipGetLastError();
+    };
+    const bool w = max_shift >= 0;
+    hipError_t e = hipErrorInvalidValue;
+    if (n == 96)
+      e = w ? run(k_xcf_scoresf<96, true, false, true>, FLay<96>::NT) : run(k_xcf_scoresf<96, false, false, true>, FLay<96>::NT);
+    else if (n == 128)
+      e = w ? run(k_xcf_scores128<true, false, true>, 512) : run(k_xcf_scores128<false, false, true>, 512);
+    else if (n == 160)
+      e = w ? run(k_xcf_scoresf<160, true, false, true>, FLay<160>::NT) : run(k_xcf_scoresf<160, false, false, true>, FLay<160>::NT);
+    if (e != hipSuccess) return e;
   }
-  const int64_t nblk = p * nchunk;
-  const int64_t grid = ((nblk + 7) / 8) * 8;
-  if (max_shift < 0)
-    hipLaunchKernelGGL((k_xcf_scores128<false, false, true>), dim3((unsigned)grid), dim3(512), 0, stream,
-                       (const cf*)spec_p, p, (const cf*)spec_l, (int64_t)k, lchunk, nblk, max_shift, scores, nullptr,
-                       cand, l);
-  else
-    hipLaunchKernelGGL((k_xcf_scores128<true, false, true>), dim3((unsigned)grid), dim3(512), 0, stream,
-                       (const cf*)spec_p, p, (const cf*)spec_l, (int64_t)k, lchunk, nblk, max_shift, scores, nullptr,
-                       cand, l);
-  return hipGetLastError();
+  return hipSuccess;
+}
+
+// The same for lists of count[p] templates in rows of l, in chunks items[g] = (pattern, first entry),
+// g < queue[1], of kListChunk entries; queue[0] counts the chunks taken and is 0 at entry.  The lists'
+// lengths differ by two orders of magnitude and only the device knows them: a resident grid takes short
+// chunks from the queue.
+hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_items, const float2* spec_l, int64_t l,
+                                   const int32_t* cand, const int32_t* count, const int2* items, int* queue,
+                                   int max_shift, float* scores, hipStream_t stream) {
+  if (max_items <= 0) return hipSuccess;
+  const dim3 grid((unsigned)(max_items < 1024 ? max_items : 1024));  // 4 blocks for each of 256 CUs
+  const auto run = [&](auto kernel, int threads) {
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, (const cf*)spec_p, int64_t(1), (const cf*)spec_l, l,
+                       kListChunk, int64_t(0), max_shift, scores, queue, cand, l, count, items);
+    return hipGetLastError();
+  };
+  const bool w = max_shift >= 0;
+  if (n == 96)
+    return w ? run(k_xcf_scoresf<96, true, true, true>, FLay<96>::NT) : run(k_xcf_scoresf<96, false, true, true>, FLay<96>::NT);
+  if (n == 128) return w ? run(k_xcf_scores128<true, true, true>, 512) : run(k_xcf_scores128<false, true, true>, 512);
+  if (n == 160)
+    return w ? run(k_xcf_scoresf<160, true, true, true>, FLay<160>::NT) : run(k_xcf_scoresf<160, false, true, true>, FLay<160>::NT);
+  return hipErrorInvalidValue;
 }
 
 hipError_t xcf_persistent_occupancy(int n, int max_shift, int* blocks_per_cu) {

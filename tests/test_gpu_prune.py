@@ -1,0 +1,68 @@
+"""Searches that keep no score matrix drop templates by a bound: their picks are the largest of the whole score
+matrix, ties to the smallest index, for patterns that match, that match nothing, and that are not finite."""
+
+import numpy as np
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+PC = (0.48, 0.55, 0.62)
+
+
+def _setup(n, p, l):
+    import torch
+    import paper_1807_11313_amd as tm
+
+    g = torch.Generator(device="cuda:0").manual_seed(n + p + l)
+    coarse = torch.rand((1, 1, 24, 24), generator=g, device="cuda:0")
+    master = torch.nn.functional.interpolate(coarse, size=(129, 129), mode="bicubic", align_corners=True)
+    master = master[0, 0].contiguous()
+    q = torch.randn((l, 4), generator=g, device="cuda:0", dtype=torch.float64)
+    q = torch.nn.functional.normalize(q, dim=1)
+    q = torch.where(q[:, :1] < 0, -q, q).contiguous()
+    return tm, g, master, q
+
+
+def _picks(scores):
+    s = scores.cpu().numpy()
+    s = np.where(np.isnan(s), -np.inf, s)
+    return s.argmax(1)
+
+
+@pytest.mark.parametrize("n, p, l", [(96, 17, 964), (96, 128, 128), (128, 9, 911), (128, 70, 129), (160, 8, 1024),
+                                     (160, 8192, 1), (160, 33, 257)])
+def test_picks_are_the_largest_scores(n, p, l):
+    import torch
+
+    tm, g, master, q = _setup(n, p, l)
+    q[l // 2:l // 2 + l // 4] = q[:l // 4]                               # exact ties
+    img = tm.project_templates(master, q, n, PC)
+    x = img[torch.arange(p, device="cuda:0") * 7 % l].clone()
+    x += (0.1 + torch.arange(p, device="cuda:0") % 5)[:, None, None] * x.std() * torch.randn(x.shape, generator=g,
+                                                                                            device="cuda:0")
+    x[1] = torch.randn((n, n), generator=g, device="cuda:0")             # matches nothing
+    x[2] = 3.0                                                           # constant
+    x[3, 1, 1] = float("nan")
+    x[4, 0, 0] = float("inf")
+    x[5] = -x[5]
+    x[6] *= 1e18
+    plans = {}
+    for window in (-1, 0, 7, n // 3):
+        prm = tm.params_default(max_shift=window)
+        want = _picks(tm.index_patterns(x, master, PC, q, prm=prm, scores=True)["scores"])
+        got = tm.index_patterns(x, master, PC, q, prm=prm)
+        assert np.array_equal(got["best_idx"].cpu().numpy(), want), window
+        plans[window] = tm.LibraryPlan(master, PC, q, n, prm=prm)
+        again = plans[window].index(x)
+        for k in got:
+            assert torch.equal(torch.nan_to_num(got[k].double()), torch.nan_to_num(again[k].double())), (window, k)
+
+
+def test_more_pairs_than_a_slab():
+    import torch
+
+    tm, g, master, q = _setup(96, 1700, 40000)
+    x = tm.project_templates(master, q[::24][:1700 - 33].contiguous(), 96, PC)
+    x = torch.cat([x, torch.randn((33, 96, 96), generator=g, device="cuda:0")]).contiguous()
+    plan = tm.LibraryPlan(master, PC, q, 96)
+    assert np.array_equal(plan.index(x)["best_idx"].cpu().numpy(), _picks(plan.index(x, scores=True)["scores"]))
