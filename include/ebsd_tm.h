@@ -449,7 +449,8 @@ int ebsd_timing_read(double* total_ms, int64_t* launches);
  * fastest (EBSD_RAGGED_NO_AUTOTUNE keeps 16 templates and the resident
  * capacity).  The chosen tiles are kept for the life of the process, keyed by
  * the device architecture, compute-unit count, size and shift window, and
- * reused by later plans.
+ * reused by later plans.  Sizes with enough pairs for the search that drops
+ * templates by a bound (see ebsd_index_patterns) run it with its fixed tile.
  *
  * ebsd_ragged_run indexes the batch against the library (method of
  * ebsd_index_patterns, each pattern against templates projected at its own

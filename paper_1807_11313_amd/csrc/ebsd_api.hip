@@ -278,25 +278,12 @@ hipError_t timed_scores(int n, const ebsd_params& prm, const float2* sp, int64_t
   return timed(st, [&] { return launch_search(n, prm, sp, p, sl, l, frag, disc, out, st); });
 }
 
-// Whether a search takes the bound-pruned argmax: the FFT form where no score
-// matrix is wanted, at the sizes whose search kernel reads lists, from 2^13
-// pairs on (2^14 at 96, whose full search is the cheapest).  Below that the
-// pruned search's six launches and its lists cost more than they save: a plan's
-// call with 4,000 pairs 121 -> 152 us at 128, 200 -> 200 at 160; 8,000 pairs
-// 174 -> 166 and 309 -> 205, 118 -> 130 at 96; 16,000 pairs 178 -> 134 at 96,
-// 261 -> 163 at 128, 514 -> 206 at 160.
-constexpr int64_t kPruneSlab = int64_t(1) << 26;  // score and list entries held at a time
-bool prunes(int n, const ebsd_params& p) { return p.form == EBSD_FORM_FFT && (n == 96 || n == 128 || n == 160); }
-bool prunes(int n, const ebsd_params& p, int64_t pairs) {
-  return prunes(n, p) && pairs >= (int64_t(1) << (n == 96 ? 14 : 13));
-}
-
 // Best template of every pattern by the pruned search, in slabs of patterns.
 // low_l / stat_l: the library's low parts (a plan keeps them), or null.
 int pruned_best(int n, const ebsd_params& p, const float2* spec_p, int64_t P, const float2* spec_l, int64_t L,
                 const float2* low_l, const float2* stat_l, int32_t* best, ScratchSource& ws, hipStream_t st) {
   const int64_t sc = spec_complex(n), lc = low_spec_complex();
-  const int64_t slab = std::max<int64_t>(1, std::min({P, kPruneSlab / L, int64_t(1) << 22}));
+  const int64_t slab = prune_slab(P, L);
   if (!low_l) {
     EBSD_ALLOC(lo, float2, lc * L, ws);
     EBSD_ALLOC(sl, float2, L, ws);
@@ -310,7 +297,7 @@ int pruned_best(int n, const ebsd_params& p, const float2* spec_p, int64_t P, co
   EBSD_ALLOC(cand, int32_t, slab * L, ws);
   EBSD_ALLOC(count, int32_t, slab, ws);
   EBSD_ALLOC(h0, float, slab, ws);
-  EBSD_ALLOC(items, int2, slab * ((L + kListChunk - 1) / kListChunk), ws);
+  EBSD_ALLOC(items, int2, slab * list_chunks(L), ws);
   EBSD_ALLOC(queue, int, 2, ws);
   const PruneScratch t{scores, cand, count, h0, items, queue};
   for (int64_t s = 0; s < P; s += slab) {
@@ -338,7 +325,7 @@ int index_against(int n, const ebsd_params& p, const float* pats, int64_t P, con
   const FilterParams fp = filter_of(p, n);
   EBSD_ALLOC(spec_p, float2, sc * P, ws);
   float* sc_out = scores;
-  const bool prune = !scores && prunes(n, p, P * L);
+  const bool prune = !scores && p.form == EBSD_FORM_FFT && prune_pays(n, P * L);
   if (!sc_out && !prune) {
     EBSD_ALLOC(tmp_scores, float, P * L, ws);
     sc_out = tmp_scores;
@@ -649,7 +636,7 @@ int ebsd_plan_create(const ebsd_master* mp, const ebsd_geometry* geo, const doub
   auto* pl = new (std::nothrow) ebsd_plan_s{n, p, L, nullptr, nullptr, nullptr, nullptr};
   if (!pl) return fail(EBSD_E_NOMEM, "plan allocation failed");
   const int64_t sc = spec_complex(n);
-  const bool prune = prunes(n, p);
+  const bool prune = p.form == EBSD_FORM_FFT && prune_supported(n);
   if (hipMalloc(&pl->spec_l, sizeof(float2) * sc * L) != hipSuccess ||
       hipMalloc(&pl->lib_q, sizeof(double) * 4 * L) != hipSuccess ||
       (prune && (hipMalloc(&pl->low_l, sizeof(float2) * low_spec_complex() * L) != hipSuccess ||

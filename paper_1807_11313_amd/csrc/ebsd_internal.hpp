@@ -74,7 +74,8 @@ hipError_t launch_xcf_scores(int n, const float2* spec_p, int64_t p, const float
 // first entry) of up to kListChunk entries; queue[0] is 0 at entry.
 hipError_t launch_xcf_scores_cand(int n, const float2* spec_p, int64_t p, const float2* spec_l, int64_t l,
                                   const int32_t* cand, int k, int max_shift, float* scores, hipStream_t stream);
-constexpr int kListChunk = 8;
+constexpr int kListChunk = 8, kListBlocks = 1024;  // blocks: 4 for each of 256 CUs
+inline int64_t list_chunks(int64_t l) { return (l + kListChunk - 1) / kListChunk; }
 hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_items, const float2* spec_l, int64_t l,
                                    const int32_t* cand, const int32_t* count, const int2* items, int* queue,
                                    int max_shift, float* scores, hipStream_t stream);
@@ -83,7 +84,7 @@ hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_item
 // (k_prune.hip; n = 96, 128, 160).  low and stat of both sides come from
 // launch_low_spectra (low_spec_complex() values and one float2 per spectrum).
 // PruneScratch: scores and cand [p][l], count and h0 [p], items
-// [p][ceil(l / kListChunk)], queue [2].
+// [p][list_chunks(l)], queue [2].
 struct PruneScratch {
   float* scores;
   int32_t* cand;
@@ -92,6 +93,11 @@ struct PruneScratch {
   int2* items;
   int* queue;
 };
+bool prune_supported(int n);
+// Whether a search of that many pairs without a score matrix is pruned
+bool prune_pays(int n, int64_t pairs);
+// Patterns of one launch_pruned_best: its scratch stays below 2^26 pairs
+int64_t prune_slab(int64_t p, int64_t l);
 int64_t low_spec_complex();
 hipError_t launch_low_spectra(int n, const float2* spec, int64_t k, float2* low, float2* stat, hipStream_t stream);
 hipError_t launch_pruned_best(int n, const float2* spec_p, const float2* low_p, const float2* stat_p, int64_t p,

@@ -190,6 +190,11 @@ struct ClassPlan {
   float2* sub_tab = nullptr;
   int64_t* img_off = nullptr;
   int* queue = nullptr;
+  float* scores = nullptr;  // of every row, or of one slab of the pruned search
+  bool prune = false;
+  int64_t slab = 0;         // patterns per pruned search
+  float2 *low_l = nullptr, *stat_l = nullptr, *low_p = nullptr, *stat_p = nullptr;
+  PruneScratch pr{};
   hipStream_t branch = nullptr;
   hipEvent_t done = nullptr;
 };
@@ -210,7 +215,6 @@ struct ebsd_ragged_plan_s {
   void* mem = nullptr;
   // rows (class-major)
   int32_t* row_pat = nullptr;
-  float* scores = nullptr;
   int32_t* best_row = nullptr;
   float* hint_row = nullptr;
   int32_t* sint_row = nullptr;
@@ -272,6 +276,21 @@ int plan_layout(ebsd_ragged_plan_s* pl, Arena& a) {
     c.pat_spec = a.take<float2>((size_t)(c.count * sc));
     c.sub_tab = a.take<float2>((size_t)subpixel_table_size(c.n, pl->prm.upsample));
     c.img_off = a.take<int64_t>((size_t)c.count);
+    c.prune = prune_pays(c.n, c.count * L);
+    c.slab = c.prune ? prune_slab(c.count, L) : c.count;
+    c.scores = a.take<float>((size_t)(c.slab * L));
+    if (c.prune) {
+      c.low_l = a.take<float2>((size_t)(L * low_spec_complex()));
+      c.stat_l = a.take<float2>((size_t)L);
+      c.low_p = a.take<float2>((size_t)(c.slab * low_spec_complex()));
+      c.stat_p = a.take<float2>((size_t)c.slab);
+      c.pr.scores = c.scores;
+      c.pr.cand = a.take<int32_t>((size_t)(c.slab * L));
+      c.pr.count = a.take<int32_t>((size_t)c.slab);
+      c.pr.h0 = a.take<float>((size_t)c.slab);
+      c.pr.items = a.take<int2>((size_t)(c.slab * list_chunks(L)));
+      c.pr.queue = a.take<int>(2);
+    }
     img_floats = std::max(img_floats, (size_t)(L * c.n * c.n));
     if (pl->flags & EBSD_RAGGED_STENCIL) {
       const size_t per = (size_t)kStencil * ((size_t)c.n * c.n * 4 + (size_t)sc * 8);
@@ -282,7 +301,6 @@ int plan_layout(ebsd_ragged_plan_s* pl, Arena& a) {
     }
   }
   pl->row_pat = a.take<int32_t>((size_t)P);
-  pl->scores = a.take<float>((size_t)(P * L));
   pl->best_row = a.take<int32_t>((size_t)P);
   pl->hint_row = a.take<float>((size_t)P);
   pl->sint_row = a.take<int32_t>((size_t)(2 * P));
@@ -335,6 +353,11 @@ TuneKey tune_key(const ebsd_ragged_plan_s* pl, const ClassPlan& c) {
 // grids on synthetic spectra of the class's size; keeps the fastest (once per
 // process for each key).
 int autotune_class(ebsd_ragged_plan_s* pl, ClassPlan& c) {
+  if (c.prune) {  // lists of the templates that are kept, in chunks of a fixed length
+    c.lchunk = kListChunk;
+    c.grid = kListBlocks;
+    return EBSD_OK;
+  }
   int occ = 0;
   RG_TRY(xcf_persistent_occupancy(c.n, pl->prm.max_shift, &occ), "occupancy");
   occ = std::max(1, std::min(occ, 4));
@@ -437,14 +460,28 @@ int enqueue(ebsd_ragged_plan_s* pl, const float* data, const ebsd_master* mp, co
   for (auto& c : pl->cls) {
     if (!c.count) continue;
     RG_TRY(hipStreamWaitEvent(c.branch, pl->fork, 0), "fork wait");
-    RG_TRY(launch_xcf_scores_persistent(c.n, c.pat_spec, c.count, c.lib_spec, L, p.max_shift,
-                                        pl->scores + c.row0 * L, c.lchunk, c.grid, c.queue, c.branch),
-           "ragged search");
+    if (c.prune) {
+      const int64_t sc = spec_complex(c.n);
+      RG_TRY(launch_low_spectra(c.n, c.lib_spec, L, c.low_l, c.stat_l, c.branch), "ragged low spectra(library)");
+      for (int64_t i0 = 0; i0 < c.count; i0 += c.slab) {
+        const int64_t cc = std::min(c.slab, c.count - i0);
+        RG_TRY(launch_low_spectra(c.n, c.pat_spec + i0 * sc, cc, c.low_p, c.stat_p, c.branch),
+               "ragged low spectra(patterns)");
+        RG_TRY(launch_pruned_best(c.n, c.pat_spec + i0 * sc, c.low_p, c.stat_p, cc, c.lib_spec, c.low_l, c.stat_l, L,
+                                  p.max_shift, c.pr, pl->best_row + c.row0 + i0, c.branch),
+               "ragged pruned search");
+      }
+    } else {
+      RG_TRY(launch_xcf_scores_persistent(c.n, c.pat_spec, c.count, c.lib_spec, L, p.max_shift, c.scores, c.lchunk,
+                                          c.grid, c.queue, c.branch),
+             "ragged search");
+      RG_TRY(launch_library_argmax(c.scores, c.count, L, pl->best_row + c.row0, pl->hint_row + c.row0, c.branch),
+             "ragged argmax");
+    }
     RG_TRY(hipEventRecord(c.done, c.branch), "join record");
   }
   for (auto& c : pl->cls)
     if (c.count) RG_TRY(hipStreamWaitEvent(st, c.done, 0), "join wait");
-  RG_TRY(launch_library_argmax(pl->scores, P, L, pl->best_row, pl->hint_row, st), "ragged argmax");
   RG_TRY(launch_gather_q(lib_q, pl->best_row, P, pl->q_row, st), "ragged gather q");
   for (auto& c : pl->cls) {
     if (!c.count) continue;

@@ -238,6 +238,22 @@ __global__ __launch_bounds__(256) void k_prune_argmax(const float* __restrict__ 
 
 }  // namespace
 
+bool prune_supported(int n) { return n == 96 || n == 128 || n == 160; }
+
+// At the sizes whose search kernel reads lists, from 2^13 pairs on (2^14 at 96,
+// whose full search is the cheapest).  Below that the pruned search's six
+// launches and its lists cost more than they save: a plan's call with 4,000
+// pairs 121 -> 152 us at 128, 200 -> 200 at 160; 8,000 pairs 174 -> 166 and
+// 309 -> 205, 118 -> 130 at 96; 16,000 pairs 178 -> 134 at 96, 261 -> 163 at
+// 128, 514 -> 206 at 160.
+bool prune_pays(int n, int64_t pairs) {
+  return prune_supported(n) && pairs >= (int64_t(1) << (n == 96 ? 14 : 13));
+}
+
+int64_t prune_slab(int64_t p, int64_t l) {
+  return std::max<int64_t>(1, std::min({p, (int64_t(1) << 26) / l, int64_t(1) << 22}));
+}
+
 int64_t low_spec_complex() { return FRAG * 2; }
 
 hipError_t launch_low_spectra(int n, const float2* spec, int64_t k, float2* low, float2* stat, hipStream_t stream) {
@@ -278,7 +294,7 @@ hipError_t launch_pruned_best(int n, const float2* spec_p, const float2* low_p, 
   hipLaunchKernelGGL(k_prune_select, dim3((unsigned)p), dim3(256), 0, stream, ws.scores, l, 0.125f * h * h, stat_p,
                      stat_l, ws.h0, ws.cand, ws.count, ws.items, ws.queue);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = launch_xcf_scores_lists(n, spec_p, p * ((l + kListChunk - 1) / kListChunk), spec_l, l, ws.cand, ws.count,
+  if ((e = launch_xcf_scores_lists(n, spec_p, p * list_chunks(l), spec_l, l, ws.cand, ws.count,
                                    ws.items, ws.queue, max_shift, ws.scores, stream)) != hipSuccess)
     return e;
   hipLaunchKernelGGL(k_prune_argmax, dim3((unsigned)p), dim3(256), 0, stream, ws.scores, ws.cand, ws.count, l, best);

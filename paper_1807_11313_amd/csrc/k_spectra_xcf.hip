@@ -1475,7 +1475,7 @@ hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_item
                                    const int32_t* cand, const int32_t* count, const int2* items, int* queue,
                                    int max_shift, float* scores, hipStream_t stream) {
   if (max_items <= 0) return hipSuccess;
-  const dim3 grid((unsigned)(max_items < 1024 ? max_items : 1024));  // 4 blocks for each of 256 CUs
+  const dim3 grid((unsigned)(max_items < kListBlocks ? max_items : kListBlocks));
   const auto run = [&](auto kernel, int threads) {
     hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, (const cf*)spec_p, int64_t(1), (const cf*)spec_l, l,
                        kListChunk, int64_t(0), max_shift, scores, queue, cand, l, count, items);

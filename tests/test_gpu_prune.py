@@ -66,3 +66,32 @@ def test_more_pairs_than_a_slab():
     x = torch.cat([x, torch.randn((33, 96, 96), generator=g, device="cuda:0")]).contiguous()
     plan = tm.LibraryPlan(master, PC, q, 96)
     assert np.array_equal(plan.index(x)["best_idx"].cpu().numpy(), _picks(plan.index(x, scores=True)["scores"]))
+
+
+@pytest.mark.parametrize("eager", [False, True])
+def test_ragged_picks(eager):
+    import torch
+
+    l, per = 830, 20                                                     # 16,600 pairs of each size
+    data, ns, offs, want, at = [], [], [], [], 0
+    for n in (160, 96, 64, 128):
+        tm, g, master, q = _setup(64, 1, l)
+        x = tm.project_templates(master, q[5:5 + 3 * per:3].contiguous(), n, PC)
+        x[-1] = torch.randn((n, n), generator=g, device="cuda:0")
+        want += _picks(tm.index_patterns(x, master, PC, q, scores=True)["scores"]).tolist()
+        ns += [n] * per
+        offs += [at + i * n * n for i in range(per)]
+        at += per * n * n
+        data.append(x.reshape(-1))
+    order = np.random.default_rng(3).permutation(len(ns))
+    ns, offs, want = np.array(ns)[order], np.array(offs)[order], np.array(want)[order]
+    plan = tm.RaggedPlan(ns, offs, l, stencil=False, eager=eager)
+    data = torch.cat(data)
+    out = plan.run(data, master, PC, q)
+    for rep in range(3):                                                 # replays, with other work between
+        torch.cuda.synchronize()
+        assert np.array_equal(out["best_idx"].cpu().numpy(), want), rep
+        out["best_idx"].fill_(-1)
+        data.mul_(1.0)
+        plan.run_into(data, master, PC, q, out)
+    plan.close()
