@@ -15,8 +15,8 @@
 // that match it, SNR 5) get their full-size score from the search kernel itself, so the pick is that of
 // the whole score matrix, bit for bit, ties included.  Patterns that match nothing keep most of their
 // templates; then the coarse values and the lists come on top of the full search: 200 patterns of noise
-// against 3,000 templates 4.28 -> 5.10 ms at 96, 6.66 -> 7.28 at 128, 14.4 -> 15.5 at 160, where 200
-// patterns of the library's material take 4.28 -> 0.56, 6.66 -> 0.61 and 14.4 -> 0.74 ms (whole calls).
+// against 3,000 templates 4.26 -> 4.81 ms at 96, 6.63 -> 6.98 at 128, 14.4 -> 15.2 at 160, where 200
+// patterns of the library's material take 4.26 -> 0.28, 6.63 -> 0.33 and 14.4 -> 0.48 ms (whole calls).
 #include "ebsd_common.hpp"
 #include "ebsd_internal.hpp"
 
@@ -29,25 +29,41 @@ namespace ebsd {
 namespace {
 
 typedef float f4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h8 __attribute__((ext_vector_type(8)));
 
 constexpr int BL = 15, G = 32;       // low band, grid points per axis
-constexpr int FRAG = 4 * 64;         // float4 values of one spectrum's low part
-constexpr int PT = 16, TC = 16;      // patterns per block, most templates per wave of the coarse kernel
+constexpr int FRAG = 2 * 64;         // h8 values of one spectrum's low part
+constexpr int PT = 32, TC = 16;      // patterns per block, most templates per wave of the coarse kernel
+constexpr float kScale = 64.0f;      // of the FP16 low parts: products to 4096, sums to 11586, nothing subnormal that counts
 
-// Both evaluations round: each transform's error is a few ulp of sum |Z| <= 1 per pass
-constexpr float kRound = 1e-5f;
+// The coarse values are a filter, not a result, and their error is part of the bound: with u = 2^-11
+// each product of the low parts carries 2 u of its operands' and 5 u of its own rounding, u of the
+// first constant, u of the conversion between the stages and u of the second constant, all against
+// |E||T| (|c1| + |s1|) (|c2| + |s2|) <= 2 |E||T|, and sum |E||T| <= 1: 20 u = 0.0098.  The FP32 sums and the
+// exact score add a few ulp.  (On the bounds' own slack of 0.11 to 0.14 this keeps 1.1x the templates.)
+constexpr float kRound = 0.0102f;
 
-// The low part of each spectrum in the coarse kernel's order, (X(u), X(-u)) of u = 4 (lane / 16) + j,
-// v = lane % 16 at [j][lane] (X(-0) = 0), and stat = (sqrt(eh), sqrt(k)); one block per spectrum
+// The low part of each spectrum in the coarse kernel's order, FP16 times kScale: X(u), X(-u) of
+// u = 4 (lane / 16) + j, v = lane % 16 (X(-0) = 0), j < 4, as re, im of u at [0][lane] and of -u at
+// [1][lane]; and stat = (sqrt(eh), sqrt(k)); one block per spectrum
 __global__ __launch_bounds__(256) void k_low_spectra(const cf* __restrict__ spec, int n, int bnd,
-                                                     f4* __restrict__ low, float2* __restrict__ stat) {
+                                                     h8* __restrict__ low, float2* __restrict__ stat) {
   const int nv = bnd + 1, nk = 2 * bnd + 1, spec_n = nv * nk;
   const int64_t k = blockIdx.x;
   const int tid = threadIdx.x, lane = tid & 63;
   const cf* S = spec + k * spec_n;
-  const int u0 = 4 * (lane >> 4) + (tid >> 6), v0 = lane & 15;
-  const cf xp = S[u0 * nv + v0], xm = u0 ? S[(nk - u0) * nv + v0] : cf{0.f, 0.f};
-  low[k * FRAG + tid] = f4{xp.x, xp.y, xm.x, xm.y};
+  if (tid < 128) {
+    h8 o;
+#pragma unroll
+    for (int j = 0; j < 4; ++j) {
+      const int u = 4 * (lane >> 4) + j, v = lane & 15;
+      const cf x = tid < 64 ? S[u * nv + v] : (u ? S[(nk - u) * nv + v] : cf{0.f, 0.f});
+      o[j] = (_Float16)(kScale * x.x);
+      o[4 + j] = (_Float16)(kScale * x.y);
+    }
+    low[k * FRAG + tid] = o;
+  }
   float eh = 0.0f, kl = 0.0f;
   for (int t = tid; t < spec_n; t += 256) {
     const int kk = t / nv, v = t - kk * nv;
@@ -72,36 +88,31 @@ __global__ __launch_bounds__(256) void k_low_spectra(const cf* __restrict__ spec
   }
 }
 
-// Largest value of the wave's 64 lanes in lane 63 (NaN is passed over)
+// The larger of a lane's and another lane's value (NaN is passed over)
 template <int CTRL>
 __device__ __forceinline__ float dpp_max(float v) {
-  const int o = __builtin_amdgcn_update_dpp(__builtin_bit_cast(int, -INFINITY), __builtin_bit_cast(int, v), CTRL, 0xf,
-                                            0xf, false);
-  return fmaxf(v, __builtin_bit_cast(float, o));
-}
-__device__ __forceinline__ float wave_max_last(float v) {
-  v = dpp_max<0x111>(v);  // row_shr 1, 2, 4, 8: lane 15 of each row
-  v = dpp_max<0x112>(v);
-  v = dpp_max<0x114>(v);
-  v = dpp_max<0x118>(v);
-  v = dpp_max<0x142>(v);  // row_bcast 15, 31
-  return dpp_max<0x143>(v);
+  return fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true)));
 }
 
 // coarse[p][l] = the largest low value over the grid points t h, t = +-(j + 1/2), j <= last (both axes), by
-// the +-u, +-s symmetric products of k_xcf_even.hip in FP32: one 16 x 16 tile per stage (u and j below
-// 16, v and j below 16), 32 of v_mfma_f32_16x16x4_f32 a pair, which with about 100 vector instructions is
-// what bounds it.  A block holds PT patterns in LDS; each of its 8 waves takes tc templates in turn,
+// the +-u, +-s symmetric products of k_xcf_even.hip.  One 16 x 16 tile per stage (u and j below 16, v
+// and j below 16): with A = Z(u) + Z(-u), D = Z(u) - Z(-u) the first stage's four sums
+//   F1, F2 = sum_u Re A cos -+ Im D sin,   F3, F4 = sum_u Im A cos +- Re D sin
+// are one product of depth 32 each, the second stage's four of depth 16 give
+//   max(cos F1 + |sin F3|, cos F2 + |sin F4|)
+// over the four sign pairs.  A block holds PT patterns in LDS; each of its 8 waves takes tc templates in turn,
 // a template's 16 values per lane serving all the patterns; every phase constant stays in registers.
-// 200 x 3,000 pairs take 424 us (1.4e9 pairs/s; 381 us is 1,400 cycles a pair and SIMD); a 64 x 64 FFT search
-// of wider low parts (|u|, |v| <= 24) in its place ran at 4.2e8 pairs/s.  4 KB a spectrum are read
-// once per block of 16 patterns and 128 templates: 2 % of the time.
-__global__ __launch_bounds__(512, 4) void k_coarse(const f4* __restrict__ low_p, int64_t np,
-                                                   const f4* __restrict__ low_l, int64_t nl, int64_t npt,
+// Bound by issue: 8 matrix products (about 130 cycles) and 50 vector instructions a pair.  200 x 3,000 pairs
+// take 119 us, 5,000 x 4,000 3.1 ms (6.5e9 pairs/s); with FP32 products (32 of 16x16x4) 424 us and 12.0 ms; a
+// 64 x 64 FFT search of wider low parts (|u|, |v| <= 24) ran at 4.2e8 pairs/s.  2 KB a spectrum are read once
+// per block of 32 patterns and 128 templates.  Fewer templates per wave (tc) fill the chip for few pairs: 11 x
+// 3,000 pairs 230 -> 34 us (measured on the FP32 form).
+__global__ __launch_bounds__(512, 4) void k_coarse(const h8* __restrict__ low_p, int64_t np,
+                                                   const h8* __restrict__ low_l, int64_t nl, int64_t npt,
                                                    int64_t nblk, int tc, int last, float* __restrict__ coarse,
                                                    int* __restrict__ queue) {
-  __shared__ f4 ep[PT * FRAG];
-  __shared__ float out[PT][8 * TC];
+  __shared__ h8 ep[PT * FRAG];
+  __shared__ float out[8 * TC * PT];
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, q4 = lane >> 4;
   if (blockIdx.x == 0 && tid < 2) queue[tid] = 0;  // for the lists of the templates that are kept
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
@@ -111,65 +122,77 @@ __global__ __launch_bounds__(512, 4) void k_coarse(const f4* __restrict__ low_p,
   const int64_t chunk = g / npt, p0 = (g - chunk * npt) * PT, l0 = chunk * (8 * tc);
   const int pc = (int)(np - p0 < PT ? np - p0 : PT);
   for (int i = tid; i < pc * FRAG; i += 512) ep[i] = low_p[p0 * FRAG + i];
-  // stage 1: cos, sin of 2 pi u (j + 1/2) / G for this lane's column j = r16 and rows u = 4 q + i; stage 2: the
+  // stage 1: cos, +-sin of 2 pi u (j + 1/2) / G for this lane's column j = r16 and rows u = 4 q4 + i; stage 2: the
   // same with v in the place of u and the Hermitian weight
-  float c1[4], s1[4], c2[4], s2[4];
+  h8 cp, cm;
+  h4 c2, s2;
 #pragma unroll
   for (int i = 0; i < 4; ++i) {
     const int f = 4 * q4 + i;
-    sincospif((float)(f * (2 * r16 + 1)) / (float)G, &s1[i], &c1[i]);
-    c2[i] = f ? 2.0f * c1[i] : c1[i];
-    s2[i] = f ? 2.0f * s1[i] : s1[i];
+    float s, c;
+    sincospif((float)(f * (2 * r16 + 1)) / (float)G, &s, &c);
+    cp[i] = cm[i] = (_Float16)c;
+    cp[4 + i] = (_Float16)s;
+    cm[4 + i] = (_Float16)(-s);
+    c2[i] = (_Float16)(f ? 2.0f * c : c);
+    s2[i] = (_Float16)(f ? 2.0f * s : s);
   }
+  const bool col = r16 <= last;
   __syncthreads();
 #pragma unroll 1
   for (int t = 0; t < tc; ++t) {
     const int64_t l = l0 + wave * tc + t;
     if (l >= nl) break;
-    f4 tv[4];
-#pragma unroll
-    for (int j = 0; j < 4; ++j) tv[j] = low_l[l * FRAG + j * 64 + lane];
-#pragma unroll 1
-    for (int pb = 0; pb < pc; ++pb) {
-      f4 acc[4], r[4];
-#pragma unroll
-      for (int c = 0; c < 4; ++c) {
-        acc[c] = f4{0.f, 0.f, 0.f, 0.f};
-        r[c] = f4{0.f, 0.f, 0.f, 0.f};
-      }
-#pragma unroll
-      for (int j = 0; j < 4; ++j) {
-        const f4 e = ep[pb * FRAG + j * 64 + lane], x = tv[j];
-        const float mr = __fmaf_rn(e[2], x[2], e[3] * x[3]), mi = __fmaf_rn(e[3], x[2], -(e[2] * x[3]));
-        const float ar = __fmaf_rn(e[0], x[0], __fmaf_rn(e[1], x[1], mr));
-        const float ai = __fmaf_rn(e[1], x[0], __fmaf_rn(-e[0], x[1], mi));
-        acc[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(ar, c1[j], acc[0], 0, 0, 0);
-        acc[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(ai, c1[j], acc[1], 0, 0, 0);
-        acc[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(__fmaf_rn(-2.0f, mr, ar), s1[j], acc[2], 0, 0, 0);
-        acc[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(__fmaf_rn(-2.0f, mi, ai), s1[j], acc[3], 0, 0, 0);
-      }
-#pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        r[0] = __builtin_amdgcn_mfma_f32_16x16x4f32(c2[i], acc[0][i], r[0], 0, 0, 0);
-        r[1] = __builtin_amdgcn_mfma_f32_16x16x4f32(c2[i], acc[3][i], r[1], 0, 0, 0);
-        r[2] = __builtin_amdgcn_mfma_f32_16x16x4f32(s2[i], acc[1][i], r[2], 0, 0, 0);
-        r[3] = __builtin_amdgcn_mfma_f32_16x16x4f32(s2[i], acc[2][i], r[3], 0, 0, 0);
-      }
+    const h8 xp = low_l[l * FRAG + lane], xm = low_l[l * FRAG + 64 + lane];
+    const h4 xpr = xp.lo, xpi = xp.hi, xmr = xm.lo, xmi = xm.hi;
+    float* const o = out + (wave * tc + t) * PT;
+    const auto best_of = [&](int pb) {
+      const h8 ea = ep[pb * FRAG + lane], eb = ep[pb * FRAG + 64 + lane];
+      const h4 er = ea.lo, ei = ea.hi, fr = eb.lo, fi = eb.hi;
+      const h4 mr = __builtin_elementwise_fma(fr, xmr, fi * xmi), mi = __builtin_elementwise_fma(fi, xmr, -(fr * xmi));
+      const h4 ar = __builtin_elementwise_fma(er, xpr, __builtin_elementwise_fma(ei, xpi, mr));
+      const h4 ai = __builtin_elementwise_fma(ei, xpr, __builtin_elementwise_fma(-er, xpi, mi));
+      const h4 two = {(_Float16)-2.0f, (_Float16)-2.0f, (_Float16)-2.0f, (_Float16)-2.0f};
+      const h4 dr = __builtin_elementwise_fma(two, mr, ar), di = __builtin_elementwise_fma(two, mi, ai);
+      const h8 ad = __builtin_shufflevector(ar, di, 0, 1, 2, 3, 4, 5, 6, 7);
+      const h8 bd = __builtin_shufflevector(ai, dr, 0, 1, 2, 3, 4, 5, 6, 7);
+      const f4 z = {0.f, 0.f, 0.f, 0.f};
+      const f4 f1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ad, cm, z, 0, 0, 0);
+      const f4 f2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ad, cp, z, 0, 0, 0);
+      const f4 f3 = __builtin_amdgcn_mfma_f32_16x16x32_f16(bd, cp, z, 0, 0, 0);
+      const f4 f4_ = __builtin_amdgcn_mfma_f32_16x16x32_f16(bd, cm, z, 0, 0, 0);
+      const f4 u1 = __builtin_amdgcn_mfma_f32_16x16x16f16(c2, __builtin_convertvector(f1, h4), z, 0, 0, 0);
+      const f4 u2 = __builtin_amdgcn_mfma_f32_16x16x16f16(c2, __builtin_convertvector(f2, h4), z, 0, 0, 0);
+      const f4 w1 = __builtin_amdgcn_mfma_f32_16x16x16f16(s2, __builtin_convertvector(f3, h4), z, 0, 0, 0);
+      const f4 w2 = __builtin_amdgcn_mfma_f32_16x16x16f16(s2, __builtin_convertvector(f4_, h4), z, 0, 0, 0);
       float m = -INFINITY;
+      if (last == 15) {
 #pragma unroll
-      for (int i = 0; i < 4; ++i) {
-        const float v = fmaxf((r[0][i] - r[1][i]) + fabsf(r[2][i] + r[3][i]),
-                              (r[0][i] + r[1][i]) + fabsf(r[2][i] - r[3][i]));
-        m = fmaxf(m, 4 * q4 + i <= last ? v : -INFINITY);
+        for (int i = 0; i < 4; ++i) m = fmaxf(m, fmaxf(u1[i] + fabsf(w1[i]), u2[i] + fabsf(w2[i])));
+      } else {
+#pragma unroll
+        for (int i = 0; i < 4; ++i)
+          if (col && 4 * q4 + i <= last) m = fmaxf(m, fmaxf(u1[i] + fabsf(w1[i]), u2[i] + fabsf(w2[i])));
       }
-      m = wave_max_last(r16 <= last ? m : -INFINITY);
-      if (lane == 63) out[pb][wave * tc + t] = m;
+      m = dpp_max<0x128>(m);  // row_ror 8, 4, 2, 1
+      m = dpp_max<0x124>(m);
+      m = dpp_max<0x122>(m);
+      m = dpp_max<0x121>(m);
+      m = dpp_max<0x142>(m);  // row_bcast 15, 31: of the wave, in its last lane
+      m = dpp_max<0x143>(m);
+      if (lane == 63) o[pb] = m;
+    };
+    // two patterns at a time, independent of each other (an odd count's last one pairs with unused LDS)
+#pragma unroll 1
+    for (int pb = 0; pb < pc; pb += 2) {
+      best_of(pb);
+      best_of(pb + 1);
     }
   }
   __syncthreads();
   for (int i = tid; i < pc * 8 * tc; i += 512) {
     const int pb = i / (8 * tc), c = i - pb * (8 * tc);
-    if (l0 + c < nl) coarse[(p0 + pb) * nl + l0 + c] = out[pb][c];
+    if (l0 + c < nl) coarse[(p0 + pb) * nl + l0 + c] = out[c * PT + pb] * (1.0f / (kScale * kScale));
   }
 }
 
@@ -243,9 +266,9 @@ bool prune_supported(int n) { return n == 96 || n == 128 || n == 160; }
 // At the sizes whose search kernel reads lists, from 2^13 pairs on (2^14 at 96,
 // whose full search is the cheapest).  Below that the pruned search's six
 // launches and its lists cost more than they save: a plan's call with 4,000
-// pairs 121 -> 152 us at 128, 200 -> 200 at 160; 8,000 pairs 174 -> 166 and
-// 309 -> 205, 118 -> 130 at 96; 16,000 pairs 178 -> 134 at 96, 261 -> 163 at
-// 128, 514 -> 206 at 160.
+// pairs 122 -> 140 us at 128, 197 -> 184 at 160 (noise 247); 8,000 pairs 174 ->
+// 157 and 298 -> 195, 116 -> 122 at 96; 16,000 pairs 174 -> 118 at 96, 262 ->
+// 147 at 128, 491 -> 191 at 160.
 bool prune_pays(int n, int64_t pairs) {
   return prune_supported(n) && pairs >= (int64_t(1) << (n == 96 ? 14 : 13));
 }
@@ -254,7 +277,7 @@ int64_t prune_slab(int64_t p, int64_t l) {
   return std::max<int64_t>(1, std::min({p, (int64_t(1) << 26) / l, int64_t(1) << 22}));
 }
 
-int64_t low_spec_complex() { return FRAG * 2; }
+int64_t low_spec_complex() { return FRAG * (int)sizeof(h8) / (int)sizeof(float2); }
 
 hipError_t launch_low_spectra(int n, const float2* spec, int64_t k, float2* low, float2* stat, hipStream_t stream) {
   if (k <= 0) return hipSuccess;
@@ -263,7 +286,7 @@ hipError_t launch_low_spectra(int n, const float2* spec, int64_t k, float2* low,
   const int64_t sc = (int64_t)(bnd + 1) * (2 * bnd + 1), kmax = (int64_t(1) << 31) / 256;
   for (int64_t s = 0; s < k; s += kmax) {
     hipLaunchKernelGGL(k_low_spectra, dim3((unsigned)(k - s < kmax ? k - s : kmax)), dim3(256), 0, stream,
-                       (const cf*)spec + s * sc, n, bnd, (f4*)low + s * FRAG, stat + s);
+                       (const cf*)spec + s * sc, n, bnd, (h8*)low + s * FRAG, stat + s);
     const hipError_t e = hipGetLastError();
     if (e != hipSuccess) return e;
   }
@@ -285,8 +308,8 @@ hipError_t launch_pruned_best(int n, const float2* spec_p, const float2* low_p, 
   const int64_t nch = (l + 8 * tc - 1) / (8 * tc), pmax = std::max<int64_t>(1, ((int64_t(1) << 31) / 512 - 8) / nch) * PT;
   for (int64_t s = 0; s < p; s += pmax) {
     const int64_t pc = p - s < pmax ? p - s : pmax, npt = (pc + PT - 1) / PT, nblk = npt * nch;
-    hipLaunchKernelGGL(k_coarse, dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(512), 0, stream, (const f4*)low_p + s * FRAG,
-                       pc, (const f4*)low_l, l, npt, nblk, tc, last, ws.scores + s * l, ws.queue);
+    hipLaunchKernelGGL(k_coarse, dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(512), 0, stream, (const h8*)low_p + s * FRAG,
+                       pc, (const h8*)low_l, l, npt, nblk, tc, last, ws.scores + s * l, ws.queue);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = launch_library_argmax(ws.scores, p, l, best, ws.h0, stream)) != hipSuccess) return e;
