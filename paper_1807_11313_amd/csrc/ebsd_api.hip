@@ -278,6 +278,14 @@ hipError_t timed_scores(int n, const ebsd_params& prm, const float2* sp, int64_t
   return timed(st, [&] { return launch_search(n, prm, sp, p, sl, l, frag, disc, out, st); });
 }
 
+// The lists that a search without a score matrix can prune by: its own products
+// for every form but the BF16 ones and the wide exact windows.
+PruneBy prune_by(const ebsd_params& p) {
+  if (p.form == EBSD_FORM_FFT) return PruneBy::Fft;
+  if (p.form == EBSD_FORM_DFT) return PruneBy::EvenFp32;
+  return p.precision == EBSD_PREC_FP16X2 ? PruneBy::EvenSplit : PruneBy::None;
+}
+
 // Best template of every pattern by the pruned search, in slabs of patterns.
 // low_l / stat_l: the library's low parts (a plan keeps them), or null.
 int pruned_best(int n, const ebsd_params& p, const float2* spec_p, int64_t P, const float2* spec_l, int64_t L,
@@ -298,16 +306,22 @@ int pruned_best(int n, const ebsd_params& p, const float2* spec_p, int64_t P, co
   EBSD_ALLOC(count, int32_t, slab, ws);
   EBSD_ALLOC(h0, float, slab, ws);
   EBSD_ALLOC(items, int2, slab * list_chunks(L), ws);
-  EBSD_ALLOC(queue, int, 2, ws);
-  const PruneScratch t{scores, cand, count, h0, items, queue};
+  EBSD_ALLOC(queue, int, 8, ws);
+  PruneScratch t{scores, cand, count, h0, items, queue, nullptr, nullptr};
+  if (p.form != EBSD_FORM_FFT) {
+    EBSD_ALLOC(frag, unsigned char, even_frag_bytes(n, p.max_shift), ws);
+    EBSD_ALLOC(rows, int32_t, slab, ws);
+    t.frag = frag;
+    t.rows = rows;
+  }
   for (int64_t s = 0; s < P; s += slab) {
     const int64_t pc = std::min(slab, P - s);
     EBSD_TRY(timed(st,
                    [&] {
                      const hipError_t e = launch_low_spectra(n, spec_p + s * sc, pc, low_p, stat_p, st);
                      if (e != hipSuccess) return e;
-                     return launch_pruned_best(n, spec_p + s * sc, low_p, stat_p, pc, spec_l, low_l, stat_l, L,
-                                               p.max_shift, t, best + s, st);
+                     return launch_pruned_best(n, prune_by(p), spec_p + s * sc, low_p, stat_p, pc, spec_l, low_l,
+                                               stat_l, L, p.max_shift, t, best + s, st);
                    }),
              "pruned search");
   }
@@ -325,7 +339,7 @@ int index_against(int n, const ebsd_params& p, const float* pats, int64_t P, con
   const FilterParams fp = filter_of(p, n);
   EBSD_ALLOC(spec_p, float2, sc * P, ws);
   float* sc_out = scores;
-  const bool prune = !scores && p.form == EBSD_FORM_FFT && prune_pays(n, P * L);
+  const bool prune = !scores && prune_pays(n, prune_by(p), p.max_shift, P * L);
   if (!sc_out && !prune) {
     EBSD_ALLOC(tmp_scores, float, P * L, ws);
     sc_out = tmp_scores;
@@ -636,7 +650,7 @@ int ebsd_plan_create(const ebsd_master* mp, const ebsd_geometry* geo, const doub
   auto* pl = new (std::nothrow) ebsd_plan_s{n, p, L, nullptr, nullptr, nullptr, nullptr};
   if (!pl) return fail(EBSD_E_NOMEM, "plan allocation failed");
   const int64_t sc = spec_complex(n);
-  const bool prune = p.form == EBSD_FORM_FFT && prune_supported(n);
+  const bool prune = prune_supported(n, prune_by(p), p.max_shift);
   if (hipMalloc(&pl->spec_l, sizeof(float2) * sc * L) != hipSuccess ||
       hipMalloc(&pl->lib_q, sizeof(double) * 4 * L) != hipSuccess ||
       (prune && (hipMalloc(&pl->low_l, sizeof(float2) * low_spec_complex() * L) != hipSuccess ||

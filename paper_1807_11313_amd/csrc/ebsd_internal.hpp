@@ -75,16 +75,19 @@ hipError_t launch_xcf_scores(int n, const float2* spec_p, int64_t p, const float
 hipError_t launch_xcf_scores_cand(int n, const float2* spec_p, int64_t p, const float2* spec_l, int64_t l,
                                   const int32_t* cand, int k, int max_shift, float* scores, hipStream_t stream);
 constexpr int kListChunk = 8, kListBlocks = 1024;  // blocks: 4 for each of 256 CUs
+// Entries of a chunk: more where a pattern keeps many, which then cost what they do in the full search
+__host__ __device__ inline int list_chunk(int64_t count) { return count >= 1024 ? 2 * kListChunk : kListChunk; }
 inline int64_t list_chunks(int64_t l) { return (l + kListChunk - 1) / kListChunk; }
 hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_items, const float2* spec_l, int64_t l,
                                    const int32_t* cand, const int32_t* count, const int2* items, int* queue,
                                    int max_shift, float* scores, hipStream_t stream);
 
-// Best template of every pattern under the FFT search without the score matrix
-// (k_prune.hip; n = 96, 128, 160).  low and stat of both sides come from
-// launch_low_spectra (low_spec_complex() values and one float2 per spectrum).
-// PruneScratch: scores and cand [p][l], count and h0 [p], items
-// [p][list_chunks(l)], queue [2].
+// Best template of every pattern without the score matrix (k_prune.hip), by one
+// of the searches below: the scores that decide are that search's own.  low and
+// stat of both sides come from launch_low_spectra (low_spec_complex() values and
+// one float2 per spectrum).  PruneScratch: scores and cand [p][l], count and h0
+// [p], items [p][list_chunks(l)], queue [8], frag and rows [p] for the even forms.
+enum class PruneBy { None, Fft, EvenFp32, EvenSplit };
 struct PruneScratch {
   float* scores;
   int32_t* cand;
@@ -92,16 +95,19 @@ struct PruneScratch {
   float* h0;
   int2* items;
   int* queue;
+  void* frag;
+  int32_t* rows;
 };
-bool prune_supported(int n);
+// Whether lists of that search exist at size n
+bool prune_supported(int n, PruneBy by, int max_shift);
 // Whether a search of that many pairs without a score matrix is pruned
-bool prune_pays(int n, int64_t pairs);
+bool prune_pays(int n, PruneBy by, int max_shift, int64_t pairs);
 // Patterns of one launch_pruned_best: its scratch stays below 2^26 pairs
 int64_t prune_slab(int64_t p, int64_t l);
 int64_t low_spec_complex();
 hipError_t launch_low_spectra(int n, const float2* spec, int64_t k, float2* low, float2* stat, hipStream_t stream);
-hipError_t launch_pruned_best(int n, const float2* spec_p, const float2* low_p, const float2* stat_p, int64_t p,
-                              const float2* spec_l, const float2* low_l, const float2* stat_l, int64_t l,
+hipError_t launch_pruned_best(int n, PruneBy by, const float2* spec_p, const float2* low_p, const float2* stat_p,
+                              int64_t p, const float2* spec_l, const float2* low_l, const float2* stat_l, int64_t l,
                               int max_shift, const PruneScratch& ws, int32_t* best, hipStream_t stream);
 
 // Integer peak (value, signed shift) for K explicit pairs (pi[k], li[k]),
@@ -151,6 +157,17 @@ bool even_supported(int n, int max_shift);
 size_t even_frag_bytes(int n, int max_shift);
 hipError_t launch_xcf_even(int n, bool split, bool disc, const float2* spec_p, int64_t p, const float2* spec_l,
                            int64_t l, int max_shift, void* frag, float* scores, hipStream_t stream);
+// Its products for lists (launch_xcf_scores_lists) of templates, PB = 1, spectra
+// zero outside the disc; rows of `row` entries; consts: build frag first.
+hipError_t launch_xcf_even_lists(int n, bool split, const float2* spec_p, int64_t max_items, const float2* spec_l,
+                                 int64_t lib_n, int64_t row, const int32_t* cand, const int32_t* count,
+                                 const int2* items, int* queue, int max_shift, void* frag, bool consts,
+                                 float* scores, hipStream_t stream);
+// And for whole rows: patterns rows[0 .. queue[1]), at most `most`, against all l
+// templates, scores[row][l]; queue[0] is 0 at entry, frag is built.
+hipError_t launch_xcf_even_rows(int n, bool split, const float2* spec_p, int64_t most, const int32_t* rows,
+                                const float2* spec_l, int64_t l, int* queue, int max_shift, const void* frag,
+                                float* scores, hipStream_t stream);
 
 // Best template per pattern from the score matrix (ties: smallest index).
 hipError_t launch_library_argmax(const float* scores, int64_t p, int64_t l, int32_t* best,

@@ -276,7 +276,7 @@ int plan_layout(ebsd_ragged_plan_s* pl, Arena& a) {
     c.pat_spec = a.take<float2>((size_t)(c.count * sc));
     c.sub_tab = a.take<float2>((size_t)subpixel_table_size(c.n, pl->prm.upsample));
     c.img_off = a.take<int64_t>((size_t)c.count);
-    c.prune = prune_pays(c.n, c.count * L);
+    c.prune = prune_pays(c.n, PruneBy::Fft, pl->prm.max_shift, c.count * L);
     c.slab = c.prune ? prune_slab(c.count, L) : c.count;
     c.scores = a.take<float>((size_t)(c.slab * L));
     if (c.prune) {
@@ -289,7 +289,7 @@ int plan_layout(ebsd_ragged_plan_s* pl, Arena& a) {
       c.pr.count = a.take<int32_t>((size_t)c.slab);
       c.pr.h0 = a.take<float>((size_t)c.slab);
       c.pr.items = a.take<int2>((size_t)(c.slab * list_chunks(L)));
-      c.pr.queue = a.take<int>(2);
+      c.pr.queue = a.take<int>(8);
     }
     img_floats = std::max(img_floats, (size_t)(L * c.n * c.n));
     if (pl->flags & EBSD_RAGGED_STENCIL) {
@@ -467,8 +467,8 @@ int enqueue(ebsd_ragged_plan_s* pl, const float* data, const ebsd_master* mp, co
         const int64_t cc = std::min(c.slab, c.count - i0);
         RG_TRY(launch_low_spectra(c.n, c.pat_spec + i0 * sc, cc, c.low_p, c.stat_p, c.branch),
                "ragged low spectra(patterns)");
-        RG_TRY(launch_pruned_best(c.n, c.pat_spec + i0 * sc, c.low_p, c.stat_p, cc, c.lib_spec, c.low_l, c.stat_l, L,
-                                  p.max_shift, c.pr, pl->best_row + c.row0 + i0, c.branch),
+        RG_TRY(launch_pruned_best(c.n, PruneBy::Fft, c.pat_spec + i0 * sc, c.low_p, c.stat_p, cc, c.lib_spec, c.low_l,
+                                  c.stat_l, L, p.max_shift, c.pr, pl->best_row + c.row0 + i0, c.branch),
                "ragged pruned search");
       }
     } else {

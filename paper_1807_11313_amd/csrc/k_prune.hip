@@ -1,5 +1,5 @@
-// Bound-pruned library argmax (gfx950): the best template of every pattern under the FP32 FFT
-// search, without the full-size transform of the pairs that cannot win.
+// Bound-pruned library argmax (gfx950): the best template of every pattern under the FP32 FFT search (or
+// the windowed forms of k_xcf_even.hip), without the full correlation of the pairs that cannot win.
 //
 // For band-limited spectra the correlation splits into rho = low + high, low the part of the
 // coefficients with |u|, |v| <= 15:
@@ -114,7 +114,7 @@ __global__ __launch_bounds__(512, 4) void k_coarse(const h8* __restrict__ low_p,
   __shared__ h8 ep[PT * FRAG];
   __shared__ float out[8 * TC * PT];
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, q4 = lane >> 4;
-  if (blockIdx.x == 0 && tid < 2) queue[tid] = 0;  // for the lists of the templates that are kept
+  if (blockIdx.x == 0 && tid < 8) queue[tid] = 0;  // for the lists of the templates that are kept
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const int64_t per = (nblk + 7) / 8;
   const int64_t g = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
@@ -196,14 +196,26 @@ __global__ __launch_bounds__(512, 4) void k_coarse(const h8* __restrict__ low_p,
   }
 }
 
+// Lists of one template per pattern (its list is the argmax itself, rows of 1), queue[2 ..]
+__global__ __launch_bounds__(256) void k_one_each(int64_t p, int32_t* __restrict__ count, int2* __restrict__ items,
+                                                  int* __restrict__ queue) {
+  const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
+  if (i == 0) queue[3] = (int)p;
+  if (i >= p) return;
+  count[i] = 1;
+  items[i] = make_int2((int)i, 0);
+}
+
 // The templates of each pattern that its bound keeps: cand[p l ..] (any order) and count[p], and their chunks
-// in the queue
+// (of list_chunk(count), or of kListChunk where rows is given) in the queue.  With rows, a pattern that keeps
+// more than a third of the library goes there instead (queue[5] counts them) and its count is -1: lists of the
+// even forms cost up to three times a row's pair, as one pattern shares nothing.
 __global__ __launch_bounds__(256) void k_prune_select(const float* __restrict__ coarse, int64_t l, float h28,
                                                       const float2* __restrict__ stat_p,
                                                       const float2* __restrict__ stat_l,
                                                       const float* __restrict__ h0, int32_t* __restrict__ cand,
                                                       int32_t* __restrict__ count, int2* __restrict__ items,
-                                                      int* __restrict__ queue) {
+                                                      int* __restrict__ queue, int32_t* __restrict__ rows) {
   const int64_t p = blockIdx.x;
   const int lane = threadIdx.x & 63;
   __shared__ int kept;
@@ -226,17 +238,25 @@ __global__ __launch_bounds__(256) void k_prune_select(const float* __restrict__ 
     if (keep) cand[p * l + at] = (int32_t)i;
   }
   __syncthreads();
-  const int nc = (kept + kListChunk - 1) / kListChunk;
+  if (rows && kept > l / 3) {
+    if (threadIdx.x == 0) {
+      count[p] = -1;
+      rows[atomicAdd(queue + 5, 1)] = (int)p;
+    }
+    return;
+  }
+  const int ch = rows ? kListChunk : list_chunk(kept), nc = (kept + ch - 1) / ch;
   __shared__ int first;
   if (threadIdx.x == 0) {
     count[p] = kept;
     first = nc ? atomicAdd(queue + 1, nc) : 0;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < nc; i += 256) items[first + i] = make_int2((int)p, i * kListChunk);
+  for (int i = threadIdx.x; i < nc; i += 256) items[first + i] = make_int2((int)p, i * ch);
 }
 
-// Best of the kept templates (ties: smallest index; none kept, every score NaN: 0)
+// Best of the kept templates, or of the whole row where count is -1 (ties: smallest index; none kept, every
+// score NaN: 0)
 __global__ __launch_bounds__(256) void k_prune_argmax(const float* __restrict__ scores,
                                                       const int32_t* __restrict__ cand,
                                                       const int32_t* __restrict__ count, int64_t l,
@@ -244,7 +264,10 @@ __global__ __launch_bounds__(256) void k_prune_argmax(const float* __restrict__ 
   const int64_t p = blockIdx.x;
   float bv = -INFINITY;
   int bi = 0x7fffffff;
-  for (int i = threadIdx.x; i < count[p]; i += 256) argmax_merge(bv, bi, scores[p * l + i], cand[p * l + i]);
+  const int c = count[p];
+  const int64_t m = c < 0 ? l : c;
+  for (int64_t i = threadIdx.x; i < m; i += 256)
+    argmax_merge(bv, bi, scores[p * l + i], c < 0 ? (int)i : cand[p * l + i]);
   wave_argmax(bv, bi);
   __shared__ float rv[4];
   __shared__ int ri[4];
@@ -261,7 +284,10 @@ __global__ __launch_bounds__(256) void k_prune_argmax(const float* __restrict__ 
 
 }  // namespace
 
-bool prune_supported(int n) { return n == 96 || n == 128 || n == 160; }
+bool prune_supported(int n, PruneBy by, int max_shift) {
+  if (by == PruneBy::Fft) return n == 96 || n == 128 || n == 160;
+  return by != PruneBy::None && even_supported(n, max_shift);
+}
 
 // At the sizes whose search kernel reads lists, from 2^13 pairs on (2^14 at 96,
 // whose full search is the cheapest).  Below that the pruned search's six
@@ -269,8 +295,14 @@ bool prune_supported(int n) { return n == 96 || n == 128 || n == 160; }
 // pairs 122 -> 140 us at 128, 197 -> 184 at 160 (noise 247); 8,000 pairs 174 ->
 // 157 and 298 -> 195, 116 -> 122 at 96; 16,000 pairs 174 -> 118 at 96, 262 ->
 // 147 at 128, 491 -> 191 at 160.
-bool prune_pays(int n, int64_t pairs) {
-  return prune_supported(n) && pairs >= (int64_t(1) << (n == 96 ? 14 : 13));
+// The windowed forms' own products (k_xcf_even.hip) are cheaper and their lists dearer: from 2^14 pairs on,
+// 2^15 at 64 and 2^13 at 256.  Whole calls, +-15 px, split / FP32: 17,000 pairs at 128 140 -> 129 / 198 ->
+// 135 us, 33,000 205 -> 142 / 289 -> 148; 33,000 at 64 103 -> 96 / 133 -> 99; at 256 9,000 439 -> 423 / 562
+// -> 447, 60,000 891 -> 467 / 1,301 -> 487.  Noise: 33,000 pairs at 128 205 -> 290 / 289 -> 368.
+bool prune_pays(int n, PruneBy by, int max_shift, int64_t pairs) {
+  if (!prune_supported(n, by, max_shift)) return false;
+  if (by == PruneBy::Fft) return pairs >= (int64_t(1) << (n == 96 ? 14 : 13));
+  return pairs >= (int64_t(1) << (n == 256 ? 13 : n == 64 ? 15 : 14));
 }
 
 int64_t prune_slab(int64_t p, int64_t l) {
@@ -293,8 +325,8 @@ hipError_t launch_low_spectra(int n, const float2* spec, int64_t k, float2* low,
   return hipSuccess;
 }
 
-hipError_t launch_pruned_best(int n, const float2* spec_p, const float2* low_p, const float2* stat_p, int64_t p,
-                              const float2* spec_l, const float2* low_l, const float2* stat_l, int64_t l,
+hipError_t launch_pruned_best(int n, PruneBy by, const float2* spec_p, const float2* low_p, const float2* stat_p,
+                              int64_t p, const float2* spec_l, const float2* low_l, const float2* stat_l, int64_t l,
                               int max_shift, const PruneScratch& ws, int32_t* best, hipStream_t stream) {
   if (p <= 0) return hipSuccess;
   if (p > (int64_t(1) << 31) / 256) return hipErrorInvalidValue;
@@ -313,12 +345,30 @@ hipError_t launch_pruned_best(int n, const float2* spec_p, const float2* low_p, 
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = launch_library_argmax(ws.scores, p, l, best, ws.h0, stream)) != hipSuccess) return e;
-  if ((e = launch_xcf_scores_cand(n, spec_p, p, spec_l, l, best, 1, max_shift, ws.h0, stream)) != hipSuccess) return e;
+  const bool split = by == PruneBy::EvenSplit;
+  if (by == PruneBy::Fft) {
+    e = launch_xcf_scores_cand(n, spec_p, p, spec_l, l, best, 1, max_shift, ws.h0, stream);
+  } else {
+    hipLaunchKernelGGL(k_one_each, dim3((unsigned)((p + 255) / 256)), dim3(256), 0, stream, p, ws.count, ws.items,
+                       ws.queue);
+    if ((e = hipGetLastError()) != hipSuccess) return e;
+    e = launch_xcf_even_lists(n, split, spec_p, p, spec_l, l, 1, best, ws.count, ws.items, ws.queue + 2, max_shift,
+                              ws.frag, true, ws.h0, stream);
+  }
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_prune_select, dim3((unsigned)p), dim3(256), 0, stream, ws.scores, l, 0.125f * h * h, stat_p,
-                     stat_l, ws.h0, ws.cand, ws.count, ws.items, ws.queue);
+                     stat_l, ws.h0, ws.cand, ws.count, ws.items, ws.queue,
+                     by == PruneBy::Fft ? nullptr : ws.rows);
   if ((e = hipGetLastError()) != hipSuccess) return e;
-  if ((e = launch_xcf_scores_lists(n, spec_p, p * list_chunks(l), spec_l, l, ws.cand, ws.count,
-                                   ws.items, ws.queue, max_shift, ws.scores, stream)) != hipSuccess)
+  const int64_t most = p * list_chunks(l);
+  e = by == PruneBy::Fft
+          ? launch_xcf_scores_lists(n, spec_p, most, spec_l, l, ws.cand, ws.count, ws.items, ws.queue, max_shift,
+                                    ws.scores, stream)
+          : launch_xcf_even_lists(n, split, spec_p, most, spec_l, l, l, ws.cand, ws.count, ws.items, ws.queue,
+                                  max_shift, ws.frag, false, ws.scores, stream);
+  if (e != hipSuccess) return e;
+  if (by != PruneBy::Fft && (e = launch_xcf_even_rows(n, split, spec_p, p, ws.rows, spec_l, l, ws.queue + 4, max_shift,
+                                                      ws.frag, ws.scores, stream)) != hipSuccess)
     return e;
   hipLaunchKernelGGL(k_prune_argmax, dim3((unsigned)p), dim3(256), 0, stream, ws.scores, ws.cand, ws.count, l, best);
   return hipGetLastError();

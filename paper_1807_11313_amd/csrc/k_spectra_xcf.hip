@@ -310,6 +310,7 @@ __global__ __launch_bounds__(512, 4) void k_xcf_scores128(const cf* __restrict__
     p = it.x;
     l0 = it.y;
     ln = count[p];
+    lchunk = list_chunk(ln);
   } else {
     const int64_t chunk = g / np;
     p = g - chunk * np;
@@ -866,6 +867,7 @@ __global__ __launch_bounds__(FLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresf(cons
       p = it.x;
       l0 = it.y;
       ln = count[p];
+      lchunk = list_chunk(ln);
     } else {
       const int64_t chunk = g / np;
       p = g - chunk * np;
@@ -1468,7 +1470,7 @@ hipError_t launch_xcf_scores_cand(int n, const float2* spec_p, int64_t p, const 
 }
 
 // The same for lists of count[p] templates in rows of l, in chunks items[g] = (pattern, first entry),
-// g < queue[1], of kListChunk entries; queue[0] counts the chunks taken and is 0 at entry.  The lists'
+// g < queue[1], of list_chunk(count) entries; queue[0] counts the chunks taken and is 0 at entry.  The lists'
 // lengths differ by two orders of magnitude and only the device knows them: a resident grid takes short
 // chunks from the queue.
 hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_items, const float2* spec_l, int64_t l,

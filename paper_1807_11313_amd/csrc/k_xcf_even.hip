@@ -44,6 +44,8 @@ typedef float f4 __attribute__((ext_vector_type(4)));
 constexpr float kScale = 4096.0f;
 constexpr float kUnscale = 1.0f / 4096.0f;
 
+constexpr int kRing = 4 * 8 * 64 * 16;  // bytes of LDS per pattern of a block
+
 // ST: tiles of 16 shifts s >= 0 (max_shift < 16 ST).  DISC: the spectra are zero outside the filter's
 // disc, as every spectrum this library writes is
 template <int N, int ST, bool DISC>
@@ -162,47 +164,40 @@ __device__ __forceinline__ void chunk_offsets(int vt, int kc, int r16, int q4, i
 // products of 32 cycles (FP32), 73 % of the SIMD cycles busy.  Measured, max_shift 15, 2,000 x 2,000 pairs at 128 and
 // 600 x 2,000 at 256: split 3.0e8 / 1.07e8 pairs/s (complex products over every u and s: 2.4e8 / 0.65e8), FP32
 // 1.99e8 / 0.72e8 (one block per pair on the vector ALU: 0.31e8 / 0.09e8).
-template <int N, int ST, int PB, bool SPLIT, bool DISC>
-__global__ __launch_bounds__(512) void k_xcf_even(const cf* __restrict__ spec_p, int64_t np,
-                                                  const cf* __restrict__ spec_l, int64_t nl, int64_t npb,
-                                                  int64_t nblk, int max_shift,
-                                                  const unsigned char* __restrict__ frag_g,
-                                                  float* __restrict__ scores) {
+// Super-tiles of TS template blocks: consecutive blocks (running at one time on an XCD) cycle through
+// the TS template blocks of one pattern block, so both stay in that XCD's L2
+template <int N>
+__device__ __forceinline__ void tile_of(int64_t g, int64_t npb, int64_t nl, int64_t* tb, int64_t* pbk) {
+  constexpr int TS = N >= 256 ? 2 : 4;
+  const int64_t ntb = (nl + 7) / 8;
+  const int64_t tb0 = g / (TS * npb) * TS;
+  const int64_t ts = ntb - tb0 < TS ? ntb - tb0 : TS;
+  const int64_t r = g - tb0 * npb;
+  *pbk = r / ts;
+  *tb = tb0 + (r - *pbk * ts);
+}
+
+// One wave's part: the PB patterns pat(0 .. cnt - 1) (cnt >= 1) against template T (any valid one where !lok),
+// scores to out[pattern * row].  smem: the constants, loaded before or by the same block without a
+// barrier since, then the ring.
+template <int N, int ST, int PB, bool SPLIT, bool DISC, class Pat>
+__device__ __forceinline__ void even_tile(unsigned char* smem, const cf* __restrict__ spec_p, Pat pat, int64_t cnt,
+                                          const cf* __restrict__ T, bool lok, int max_shift, float* __restrict__ out,
+                                          int64_t row) {
   using L = EvenLay<N, ST, DISC>;
   constexpr int VT = L::VT, KC = L::KC, NV = L::NV, NSTEP = VT * KC, ROW = NV * (int)sizeof(cf);
   constexpr int NSLOT = 4, AHEAD = 2;
   constexpr float SCALE = SPLIT ? kScale : 1.0f, UNSCALE = SPLIT ? kUnscale : 1.0f;
-  __shared__ __align__(16) unsigned char smem[L::FRAG_BYTES + NSLOT * PB * 8 * 64 * 16];
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, q4 = lane >> 4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
-  const int64_t per = (nblk + 7) / 8;
-  const int64_t g = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
-  if (g >= nblk) return;
-  // super-tiles of TS template blocks: consecutive blocks (running at one time on an XCD) cycle through
-  // the TS template blocks of one pattern block, so both stay in that XCD's L2
-  int64_t tb, pbk;
-  {
-    constexpr int TS = N >= 256 ? 2 : 4;
-    const int64_t ntb = (nl + 7) / 8;
-    const int64_t tb0 = g / (TS * npb) * TS;
-    const int64_t ts = ntb - tb0 < TS ? ntb - tb0 : TS;
-    const int64_t r = g - tb0 * npb;
-    pbk = r / ts;
-    tb = tb0 + (r - pbk * ts);
-  }
-  const int64_t p0 = pbk * PB, l = tb * 8 + wave;
-  const bool lok = l < nl;
-  for (int i = tid; i < L::FRAG_BYTES / 16; i += 512)
-    reinterpret_cast<uint4*>(smem)[i] = reinterpret_cast<const uint4*>(frag_g)[i];
   const u4v* wf = reinterpret_cast<const u4v*>(smem);
   const unsigned char* cfr = smem + L::W_BYTES;
   f4* ring = reinterpret_cast<f4*>(smem + L::FRAG_BYTES);  // [slot][pb][j][lane] (E(u), E(-u))
-  const cf* T = spec_l + (lok ? l : 0) * L::SPEC;
   const __amdgpu_buffer_rsrc_t tr = rsrc_of(T, L::SPEC * (int)sizeof(cf));
   __amdgpu_buffer_rsrc_t er[PB];
 #pragma unroll
   for (int pb = 0; pb < PB; ++pb)
-    er[pb] = rsrc_of(spec_p + (p0 + pb < np ? p0 + pb : p0) * L::SPEC, L::SPEC * (int)sizeof(cf));
+    er[pb] = rsrc_of(spec_p + pat(pb < cnt ? pb : 0) * L::SPEC, L::SPEC * (int)sizeof(cf));
 
   cf es[PB][2];
   auto stage_load = [&](int pos, int neg) {
@@ -393,8 +388,8 @@ __global__ __launch_bounds__(512) void k_xcf_even(const cf* __restrict__ spec_p,
   if (!lok) return;
 #pragma unroll
   for (int pb = 0; pb < PB; ++pb) {
-    if (p0 + pb >= np) break;
-    const cf* E = spec_p + (p0 + pb) * L::SPEC;
+    if (pb >= cnt) break;
+    const cf* E = spec_p + pat(pb) * L::SPEC;
     cf za{0.f, 0.f}, zd{0.f, 0.f}, zc{0.f, 0.f};
     if constexpr (L::UTOP) {
       const cf zp = cmulc(E[L::B * NV], T[L::B * NV]), zm = cmulc(E[(L::B + 1) * NV], T[(L::B + 1) * NV]);
@@ -422,7 +417,97 @@ __global__ __launch_bounds__(512) void k_xcf_even(const cf* __restrict__ spec_p,
         }
       }
     m = wave_max(m);
-    if (lane == 0) scores[(p0 + pb) * nl + l] = m * UNSCALE;
+    if (lane == 0) out[pat(pb) * row] = m * UNSCALE;
+  }
+}
+
+template <int N, int ST, int PB, bool SPLIT, bool DISC>
+__global__ __launch_bounds__(512) void k_xcf_even(const cf* __restrict__ spec_p, int64_t np,
+                                                  const cf* __restrict__ spec_l, int64_t nl, int64_t npb,
+                                                  int64_t nblk, int max_shift,
+                                                  const unsigned char* __restrict__ frag_g,
+                                                  float* __restrict__ scores) {
+  using L = EvenLay<N, ST, DISC>;
+  __shared__ __align__(16) unsigned char smem[L::FRAG_BYTES + kRing * PB];
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int64_t per = (nblk + 7) / 8;
+  const int64_t g = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
+  if (g >= nblk) return;
+  int64_t tb, pbk;
+  tile_of<N>(g, npb, nl, &tb, &pbk);
+  const int64_t p0 = pbk * PB, l = tb * 8 + wave;
+  const bool lok = l < nl;
+  for (int i = tid; i < L::FRAG_BYTES / 16; i += 512)
+    reinterpret_cast<uint4*>(smem)[i] = reinterpret_cast<const uint4*>(frag_g)[i];
+  even_tile<N, ST, PB, SPLIT, DISC>(smem, spec_p, [p0](int pb) { return p0 + pb; }, np - p0,
+                                    spec_l + (lok ? l : 0) * L::SPEC, lok, max_shift, scores + l, nl);
+}
+
+// The same for lists: scores[p nl + j] for template cand[p nl + j], j < count[p], in chunks of 8 templates
+// items[g] = (pattern, first entry), g < queue[1], which a resident grid takes from queue[0].  A chunk's
+// templates share one pattern only, so a pair costs up to three times k_xcf_even's.
+template <int N, int ST, bool SPLIT>
+__global__ __launch_bounds__(512) void k_xcf_even_lists(const cf* __restrict__ spec_p, const cf* __restrict__ spec_l,
+                                                        int64_t lib_n, int64_t nl, const int32_t* __restrict__ cand,
+                                                        const int32_t* __restrict__ count,
+                                                        const int2* __restrict__ items, int* __restrict__ queue,
+                                                        int max_shift, const unsigned char* __restrict__ frag_g,
+                                                        float* __restrict__ scores) {
+  using L = EvenLay<N, ST, true>;
+  __shared__ __align__(16) unsigned char smem[L::FRAG_BYTES + kRing];
+  __shared__ int item;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int total = queue[1];
+  for (int i = tid; i < L::FRAG_BYTES / 16; i += 512)
+    reinterpret_cast<uint4*>(smem)[i] = reinterpret_cast<const uint4*>(frag_g)[i];
+  for (;;) {
+    __syncthreads();
+    if (tid == 0) item = atomicAdd(queue, 1);
+    __syncthreads();
+    const int g = __builtin_amdgcn_readfirstlane(item);
+    if (g >= total) return;
+    const int64_t p = items[g].x, j = items[g].y + wave;
+    const bool lok = j < count[p];
+    int64_t tl = lok ? cand[p * nl + j] : 0;
+    tl = tl < 0 ? 0 : (tl >= lib_n ? lib_n - 1 : tl);
+    even_tile<N, ST, 1, SPLIT, true>(smem, spec_p, [p](int) { return p; }, 1, spec_l + tl * L::SPEC, lok, max_shift,
+                                     scores + j, nl);
+  }
+}
+
+// And for patterns that keep most of the library: rows[0 .. queue[1]) against all of it, PB patterns a block
+// as in k_xcf_even, tiles taken from queue[0] by a resident grid
+template <int N, int ST, int PB, bool SPLIT>
+__global__ __launch_bounds__(512) void k_xcf_even_rows(const cf* __restrict__ spec_p, const int32_t* __restrict__ rows,
+                                                       const cf* __restrict__ spec_l, int64_t nl,
+                                                       int* __restrict__ queue, int max_shift,
+                                                       const unsigned char* __restrict__ frag_g,
+                                                       float* __restrict__ scores) {
+  using L = EvenLay<N, ST, true>;
+  __shared__ __align__(16) unsigned char smem[L::FRAG_BYTES + kRing * PB];
+  __shared__ int item;
+  const int tid = threadIdx.x;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  const int nr = queue[1];
+  const int64_t npb = (nr + PB - 1) / PB, nblk = npb * ((nl + 7) / 8);
+  if (nblk == 0) return;
+  for (int i = tid; i < L::FRAG_BYTES / 16; i += 512)
+    reinterpret_cast<uint4*>(smem)[i] = reinterpret_cast<const uint4*>(frag_g)[i];
+  for (;;) {
+    __syncthreads();
+    if (tid == 0) item = atomicAdd(queue, 1);
+    __syncthreads();
+    const int g = __builtin_amdgcn_readfirstlane(item);
+    if (g >= nblk) return;
+    int64_t tb, pbk;
+    tile_of<N>(g, npb, nl, &tb, &pbk);
+    const int64_t l = tb * 8 + wave;
+    const bool lok = l < nl;
+    const int32_t* r = rows + pbk * PB;
+    even_tile<N, ST, PB, SPLIT, true>(smem, spec_p, [r](int pb) { return (int64_t)r[pb]; }, nr - pbk * PB,
+                                      spec_l + (lok ? l : 0) * L::SPEC, lok, max_shift, scores + l, nl);
   }
 }
 
@@ -451,11 +536,40 @@ hipError_t run_even(const float2* spec_p, int64_t p, const float2* spec_l, int64
 // Patterns per block: as many as the registers of two waves per SIMD hold.  Split 2 / 3 / 4 patterns: 2.72 /
 // 3.00 / 2.56e8 pairs/s at 128, 0.98 / 1.07 / 0.92e8 at 256 (four spill); FP32 2 / 4 / 5: 1.85 / 1.99 / 1.93e8
 // and 0.66 / 0.72 / 0.68e8.  Two tiles of shifts (16 <= max_shift) take a quarter as many accumulators' patterns: one.
+template <bool SPLIT, int ST>
+constexpr int even_pb() { return ST == 2 ? 1 : SPLIT ? 3 : 4; }
 template <int N, bool SPLIT, bool DISC>
 hipError_t pick_even(const float2* spec_p, int64_t p, const float2* spec_l, int64_t l, int max_shift,
                      unsigned char* frag, float* scores, hipStream_t stream) {
-  if (max_shift >= 16) return run_even<N, 2, 1, SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
-  return run_even<N, 1, SPLIT ? 3 : 4, SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
+  if (max_shift >= 16)
+    return run_even<N, 2, even_pb<SPLIT, 2>(), SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
+  return run_even<N, 1, even_pb<SPLIT, 1>(), SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
+}
+
+template <int N, int ST, bool SPLIT>
+hipError_t run_lists(const float2* spec_p, int64_t max_items, const float2* spec_l, int64_t lib_n, int64_t row,
+                     const int32_t* cand, const int32_t* count, const int2* items, int* queue, int max_shift,
+                     unsigned char* frag, bool consts, float* scores, hipStream_t stream) {
+  using L = EvenLay<N, ST, true>;
+  if (consts)
+    hipLaunchKernelGGL((k_even_consts<N, ST, SPLIT, true>), dim3((L::FRAG_BYTES / 4 + 255) / 256), dim3(256), 0,
+                       stream, frag);
+  hipLaunchKernelGGL((k_xcf_even_lists<N, ST, SPLIT>),
+                     dim3((unsigned)(max_items < kListBlocks ? max_items : kListBlocks)), dim3(512), 0, stream,
+                     (const cf*)spec_p, (const cf*)spec_l, lib_n, row, cand, count, items, queue, max_shift, frag,
+                     scores);
+  return hipGetLastError();
+}
+
+template <int N, int ST, int PB, bool SPLIT>
+hipError_t run_rows(const float2* spec_p, int64_t most, const int32_t* rows, const float2* spec_l, int64_t l,
+                    int* queue, int max_shift, const unsigned char* frag, float* scores, hipStream_t stream) {
+  const int64_t tiles = (most + PB - 1) / PB * ((l + 7) / 8);
+  if (tiles > 0x7ffffff0LL) return hipErrorInvalidValue;
+  hipLaunchKernelGGL((k_xcf_even_rows<N, ST, PB, SPLIT>), dim3((unsigned)(tiles < kListBlocks ? tiles : kListBlocks)),
+                     dim3(512), 0, stream, (const cf*)spec_p, rows, (const cf*)spec_l, l, queue, max_shift, frag,
+                     scores);
+  return hipGetLastError();
 }
 
 }  // namespace
@@ -487,6 +601,45 @@ hipError_t launch_xcf_even(int n, bool split, bool disc, const float2* spec_p, i
                ? pick_even<NN, false, true>(spec_p, p, spec_l, l, max_shift, frag, scores, stream)       \
                : pick_even<NN, false, Plan<NN>::B % 16 != 0>(spec_p, p, spec_l, l, max_shift, frag,      \
                                                              scores, stream);                            \
+  }
+  EBSD_EVEN_SIZES(EBSD_EL)
+#undef EBSD_EL
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_xcf_even_lists(int n, bool split, const float2* spec_p, int64_t max_items, const float2* spec_l,
+                                 int64_t lib_n, int64_t row, const int32_t* cand, const int32_t* count,
+                                 const int2* items, int* queue, int max_shift, void* frag_v, bool consts,
+                                 float* scores, hipStream_t stream) {
+  if (max_items <= 0) return hipSuccess;
+  if (!even_supported(n, max_shift)) return hipErrorInvalidValue;
+  unsigned char* frag = static_cast<unsigned char*>(frag_v);
+#define EBSD_EL(NN)                                                                                                 \
+  if (n == NN) {                                                                                                    \
+    const auto run = [&](auto f) {                                                                                  \
+      return f(spec_p, max_items, spec_l, lib_n, row, cand, count, items, queue, max_shift, frag, consts, scores,   \
+               stream);                                                                                             \
+    };                                                                                                              \
+    if (max_shift >= 16) return split ? run(run_lists<NN, 2, true>) : run(run_lists<NN, 2, false>);                 \
+    return split ? run(run_lists<NN, 1, true>) : run(run_lists<NN, 1, false>);                                      \
+  }
+  EBSD_EVEN_SIZES(EBSD_EL)
+#undef EBSD_EL
+  return hipErrorInvalidValue;
+}
+
+hipError_t launch_xcf_even_rows(int n, bool split, const float2* spec_p, int64_t most, const int32_t* rows,
+                                const float2* spec_l, int64_t l, int* queue, int max_shift, const void* frag_v,
+                                float* scores, hipStream_t stream) {
+  if (most <= 0 || l <= 0) return hipSuccess;
+  if (!even_supported(n, max_shift)) return hipErrorInvalidValue;
+  const unsigned char* frag = static_cast<const unsigned char*>(frag_v);
+#define EBSD_EL(NN)                                                                                              \
+  if (n == NN) {                                                                                                 \
+    const auto run = [&](auto f) { return f(spec_p, most, rows, spec_l, l, queue, max_shift, frag, scores, stream); }; \
+    if (max_shift >= 16)                                                                                         \
+      return split ? run(run_rows<NN, 2, even_pb<true, 2>(), true>) : run(run_rows<NN, 2, even_pb<false, 2>(), false>); \
+    return split ? run(run_rows<NN, 1, even_pb<true, 1>(), true>) : run(run_rows<NN, 1, even_pb<false, 1>(), false>); \
   }
   EBSD_EVEN_SIZES(EBSD_EL)
 #undef EBSD_EL

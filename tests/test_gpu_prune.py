@@ -58,6 +58,31 @@ def test_picks_are_the_largest_scores(n, p, l):
             assert torch.equal(torch.nan_to_num(got[k].double()), torch.nan_to_num(again[k].double())), (window, k)
 
 
+@pytest.mark.parametrize("n, p, l", [(64, 33, 1000), (96, 17, 1024), (128, 16, 1031), (160, 67, 250), (256, 9, 911)])
+@pytest.mark.parametrize("form, precision", [(2, 1), (3, 0)])             # split FP16 products, exact FP32 products
+@pytest.mark.parametrize("window", [4, 20])
+def test_windowed_picks(n, p, l, form, precision, window):
+    import torch
+
+    tm, g, master, q = _setup(n, p, l)
+    q[l // 2:l // 2 + l // 4] = q[:l // 4]
+    img = tm.project_templates(master, q, n, PC)
+    x = img[torch.arange(p, device="cuda:0") * 7 % l].clone()
+    x += 0.3 * x.std() * torch.randn(x.shape, generator=g, device="cuda:0")
+    x[1:5] = torch.randn((4, n, n), generator=g, device="cuda:0")         # whole rows, one block and a part
+    x[5] = 3.0
+    x[6, 1, 1] = float("nan")
+    x[7] = -x[7]
+    prm = tm.params_default(form=form, precision=precision, max_shift=window)
+    want = tm.index_patterns(x, master, PC, q, prm=prm, scores=True)
+    got = tm.index_patterns(x, master, PC, q, prm=prm)
+    again = tm.LibraryPlan(master, PC, q, n, prm=prm).index(x)
+    assert np.array_equal(got["best_idx"].cpu().numpy(), _picks(want["scores"]))
+    for k in got:
+        for other in (want, again):
+            assert torch.equal(torch.nan_to_num(got[k].double()), torch.nan_to_num(other[k].double())), k
+
+
 def test_more_pairs_than_a_slab():
     import torch
 
