@@ -307,12 +307,11 @@ int pruned_best(int n, const ebsd_params& p, const float2* spec_p, int64_t P, co
   EBSD_ALLOC(h0, float, slab, ws);
   EBSD_ALLOC(items, int2, slab * list_chunks(L), ws);
   EBSD_ALLOC(queue, int, 8, ws);
-  PruneScratch t{scores, cand, count, h0, items, queue, nullptr, nullptr};
+  EBSD_ALLOC(rows, int32_t, slab, ws);
+  PruneScratch t{scores, cand, count, h0, items, queue, rows, nullptr};
   if (p.form != EBSD_FORM_FFT) {
     EBSD_ALLOC(frag, unsigned char, even_frag_bytes(n, p.max_shift), ws);
-    EBSD_ALLOC(rows, int32_t, slab, ws);
     t.frag = frag;
-    t.rows = rows;
   }
   for (int64_t s = 0; s < P; s += slab) {
     const int64_t pc = std::min(slab, P - s);

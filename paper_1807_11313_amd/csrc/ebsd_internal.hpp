@@ -68,8 +68,8 @@ hipError_t launch_xcf_scores_persistent(int n, const float2* spec_p, int64_t p, 
 hipError_t launch_xcf_scores(int n, const float2* spec_p, int64_t p, const float2* spec_l,
                              int64_t l, int max_shift, float* scores, hipStream_t stream);
 // The same for each pattern's own k candidates among l templates: scores[p][j]
-// for template cand[p][j], clamped to [0, l) (n = 96, 128, 160;
-// hipErrorInvalidValue for other sizes), and for lists of their own lengths,
+// for template cand[p][j], clamped to [0, l) (the sizes of the FFT search;
+// hipErrorInvalidValue for others), and for lists of their own lengths,
 // cand[p][j], j < count[p] <= l, in rows of l, as queue[1] chunks (pattern,
 // first entry) of up to kListChunk entries; queue[0] is 0 at entry.
 hipError_t launch_xcf_scores_cand(int n, const float2* spec_p, int64_t p, const float2* spec_l, int64_t l,
@@ -82,11 +82,16 @@ hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_item
                                    const int32_t* cand, const int32_t* count, const int2* items, int* queue,
                                    int max_shift, float* scores, hipStream_t stream);
 
+// And for whole rows at 64: patterns rows[0 .. queue[1]), at most `most`, against
+// all l templates, scores[row][l]; queue[0] is 0 at entry.
+hipError_t launch_xcf_scores_rows64(const float2* spec_p, int64_t most, const int32_t* rows, const float2* spec_l,
+                                    int64_t l, int* queue, int max_shift, float* scores, hipStream_t stream);
+
 // Best template of every pattern without the score matrix (k_prune.hip), by one
 // of the searches below: the scores that decide are that search's own.  low and
 // stat of both sides come from launch_low_spectra (low_spec_complex() values and
 // one float2 per spectrum).  PruneScratch: scores and cand [p][l], count and h0
-// [p], items [p][list_chunks(l)], queue [8], frag and rows [p] for the even forms.
+// [p], items [p][list_chunks(l)], queue [8], rows [p], frag for the even forms.
 enum class PruneBy { None, Fft, EvenFp32, EvenSplit };
 struct PruneScratch {
   float* scores;
@@ -95,8 +100,8 @@ struct PruneScratch {
   float* h0;
   int2* items;
   int* queue;
-  void* frag;
   int32_t* rows;
+  void* frag;
 };
 // Whether lists of that search exist at size n
 bool prune_supported(int n, PruneBy by, int max_shift);

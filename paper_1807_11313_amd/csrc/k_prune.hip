@@ -207,9 +207,10 @@ __global__ __launch_bounds__(256) void k_one_each(int64_t p, int32_t* __restrict
 }
 
 // The templates of each pattern that its bound keeps: cand[p l ..] (any order) and count[p], and their chunks
-// (of list_chunk(count), or of kListChunk where rows is given) in the queue.  With rows, a pattern that keeps
-// more than a third of the library goes there instead (queue[5] counts them) and its count is -1: lists of the
-// even forms cost up to three times a row's pair, as one pattern shares nothing.
+// in the queue, of list_chunk(count) entries or, with rows, of kListChunk.  With rows, a pattern that keeps
+// more than a third of the library goes there instead (queue[5] counts them) and its count is -1: a pair of a
+// list costs up to 3 times one of a row in the even forms, whose rows share patterns, and 1.4 times at 64, whose
+// rows share a template load; at 96 to 160 it is 1.05 and a row launch would not pay.
 __global__ __launch_bounds__(256) void k_prune_select(const float* __restrict__ coarse, int64_t l, float h28,
                                                       const float2* __restrict__ stat_p,
                                                       const float2* __restrict__ stat_l,
@@ -285,23 +286,23 @@ __global__ __launch_bounds__(256) void k_prune_argmax(const float* __restrict__ 
 }  // namespace
 
 bool prune_supported(int n, PruneBy by, int max_shift) {
-  if (by == PruneBy::Fft) return n == 96 || n == 128 || n == 160;
+  if (by == PruneBy::Fft) return fft_supported(n);
   return by != PruneBy::None && even_supported(n, max_shift);
 }
 
-// At the sizes whose search kernel reads lists, from 2^13 pairs on (2^14 at 96,
-// whose full search is the cheapest).  Below that the pruned search's six
+// From 2^13 pairs on, 2^14 at 96 and 2^15 at 64, whose full searches are cheaper.  Below that the pruned search's six
 // launches and its lists cost more than they save: a plan's call with 4,000
 // pairs 122 -> 140 us at 128, 197 -> 184 at 160 (noise 247); 8,000 pairs 174 ->
 // 157 and 298 -> 195, 116 -> 122 at 96; 16,000 pairs 174 -> 118 at 96, 262 ->
-// 147 at 128, 491 -> 191 at 160.
+// 147 at 128, 491 -> 191 at 160; at 64 16,000 90 -> 107, 33,000 141 -> 122 (noise
+// 241), 6,000,000 15.0 -> 1.4 ms (noise 16.8).
 // The windowed forms' own products (k_xcf_even.hip) are cheaper and their lists dearer: from 2^14 pairs on,
 // 2^15 at 64 and 2^13 at 256.  Whole calls, +-15 px, split / FP32: 17,000 pairs at 128 140 -> 129 / 198 ->
 // 135 us, 33,000 205 -> 142 / 289 -> 148; 33,000 at 64 103 -> 96 / 133 -> 99; at 256 9,000 439 -> 423 / 562
 // -> 447, 60,000 891 -> 467 / 1,301 -> 487.  Noise: 33,000 pairs at 128 205 -> 290 / 289 -> 368.
 bool prune_pays(int n, PruneBy by, int max_shift, int64_t pairs) {
   if (!prune_supported(n, by, max_shift)) return false;
-  if (by == PruneBy::Fft) return pairs >= (int64_t(1) << (n == 96 ? 14 : 13));
+  if (by == PruneBy::Fft) return pairs >= (int64_t(1) << (n == 64 ? 15 : n == 96 ? 14 : 13));
   return pairs >= (int64_t(1) << (n == 256 ? 13 : n == 64 ? 15 : 14));
 }
 
@@ -358,7 +359,7 @@ hipError_t launch_pruned_best(int n, PruneBy by, const float2* spec_p, const flo
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_prune_select, dim3((unsigned)p), dim3(256), 0, stream, ws.scores, l, 0.125f * h * h, stat_p,
                      stat_l, ws.h0, ws.cand, ws.count, ws.items, ws.queue,
-                     by == PruneBy::Fft ? nullptr : ws.rows);
+                     by == PruneBy::Fft && n != 64 ? nullptr : ws.rows);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int64_t most = p * list_chunks(l);
   e = by == PruneBy::Fft
@@ -367,9 +368,11 @@ hipError_t launch_pruned_best(int n, PruneBy by, const float2* spec_p, const flo
           : launch_xcf_even_lists(n, split, spec_p, most, spec_l, l, l, ws.cand, ws.count, ws.items, ws.queue,
                                   max_shift, ws.frag, false, ws.scores, stream);
   if (e != hipSuccess) return e;
-  if (by != PruneBy::Fft && (e = launch_xcf_even_rows(n, split, spec_p, p, ws.rows, spec_l, l, ws.queue + 4, max_shift,
-                                                      ws.frag, ws.scores, stream)) != hipSuccess)
-    return e;
+  if (by != PruneBy::Fft)
+    e = launch_xcf_even_rows(n, split, spec_p, p, ws.rows, spec_l, l, ws.queue + 4, max_shift, ws.frag, ws.scores, stream);
+  else if (n == 64)
+    e = launch_xcf_scores_rows64(spec_p, p, ws.rows, spec_l, l, ws.queue + 4, max_shift, ws.scores, stream);
+  if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_prune_argmax, dim3((unsigned)p), dim3(256), 0, stream, ws.scores, ws.cand, ws.count, l, best);
   return hipGetLastError();
 }

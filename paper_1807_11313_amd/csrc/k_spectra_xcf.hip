@@ -529,11 +529,17 @@ struct WLay {
   static constexpr bool BUFLOAD = N != 96;
 };
 
-template <int N, bool WINDOW, bool PERSIST>
+// CAND as in k_xcf_scores128; PERSIST without CAND and with cand: the patterns
+// are cand[0 .. queue[1])
+template <int N, bool WINDOW, bool PERSIST, bool CAND = false>
 __global__ __launch_bounds__(WLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresw(const cf* __restrict__ spec_p, int64_t np,
                                                              const cf* __restrict__ spec_l, int64_t nl, int lchunk,
                                                              int64_t nblk, int max_shift, float* __restrict__ scores,
-                                                             int* __restrict__ queue) {
+                                                             int* __restrict__ queue,
+                                                             const int32_t* __restrict__ cand = nullptr,
+                                                             int64_t lib_n = 0,
+                                                             const int32_t* __restrict__ count = nullptr,
+                                                             const int2* __restrict__ items = nullptr) {
   using L = WLay<N>;
   constexpr int R1 = L::R1, R2 = L::R2, B = L::B, NV = L::NV, SPEC = L::SPEC, AV = L::AV;
   constexpr int NQ = L::NQ, QB = L::QB, NQB = L::NQB, JC = L::JC;
@@ -559,11 +565,30 @@ __global__ __launch_bounds__(WLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresw(cons
     const int64_t per = (nblk + 7) / 8;
     g = (int64_t)(blockIdx.x % 8) * per + blockIdx.x / 8;
   }
+  if constexpr (CAND && PERSIST) nblk = queue[1];
+  if constexpr (!CAND && PERSIST) {
+    if (cand) {
+      np = queue[1];
+      nblk = np * ((nl + lchunk - 1) / lchunk);
+    }
+  }
   if (g >= nblk) return;
   const bool vlane = sl < NV;
 
   while (g < nblk) {
-    const int64_t chunk = g / np, p = g - chunk * np;
+    int64_t p, l0, ln = nl;
+    if constexpr (CAND && PERSIST) {
+      const int2 it = items[g];
+      p = it.x;
+      l0 = it.y;
+      ln = count[p];
+      lchunk = kListChunk;
+    } else {
+      const int64_t chunk = g / np;
+      p = g - chunk * np;
+      if (PERSIST && cand) p = cand[p];
+      l0 = chunk * lchunk;
+    }
     const cf* E = spec_p + p * SPEC;
     // the pattern's phase-1 values, held in registers across the template loop
     cf ev[R1];
@@ -573,14 +598,19 @@ __global__ __launch_bounds__(WLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresw(cons
       const int kk = u <= B ? u : (u >= N - B ? u - N + 2 * B + 1 : -1);
       ev[a] = (kk >= 0 && vlane) ? E[kk * NV + sl] : cf{0.f, 0.f};
     }
-    const int64_t l0 = chunk * lchunk;
-    const int64_t l1 = l0 + lchunk < nl ? l0 + lchunk : nl;
+    const int64_t l1 = l0 + lchunk < ln ? l0 + lchunk : ln;
     for (int64_t l = l0; l < l1; l += TPW) {
       // at TPW = 2 the halves take templates l and l + 1; past the end of the
       // chunk both take l (the second result is not written)
       const bool two = TPW == 2 && l + 1 < l1;
       const int th = two ? half : 0;
-      const cf* T = spec_l + l * SPEC;
+      const cf* T = spec_l;
+      if constexpr (CAND) {  // this lane's own template
+        const int64_t tl = cand[p * nl + l + th];
+        T += (tl < 0 ? 0 : (tl >= lib_n ? lib_n - 1 : tl)) * SPEC;
+      } else {
+        T += l * SPEC;
+      }
       // phase 1: wave b, lane v: radix R1 over u = R2 a + b, twiddle.  The
       // cached pattern values are zero outside the band, so every lane loads
       // its template values from a clamped in-band address without a branch
@@ -588,13 +618,15 @@ __global__ __launch_bounds__(WLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresw(cons
       {
         cf x[R1];
         const unsigned voff = (unsigned)(th * SPEC + (vlane ? sl : NV - 1)) * (unsigned)sizeof(cf);
-        const __amdgpu_buffer_rsrc_t Tr = spectrum_rsrc(T, (two ? 2 : 1) * SPEC * (int)sizeof(cf));
+        // (in lists the halves' templates lie apart: plain loads)
+        const __amdgpu_buffer_rsrc_t Tr = spectrum_rsrc(CAND ? spec_l : T, (two ? 2 : 1) * SPEC * (int)sizeof(cf));
 #pragma unroll
         for (int a = 0; a < R1; ++a) {
           if (L::ZGAP && ((L::GAP >> a) & 1)) continue;  // neither loaded nor added
           const int u = R2 * a + wave;
           const int kk = u <= B ? u : (u >= N - B ? u - N + 2 * B + 1 : 0);
-          if constexpr (L::BUFLOAD) x[a] = buffer_cf(Tr, voff, kk * NV * (int)sizeof(cf));
+          if constexpr (CAND) x[a] = T[kk * NV + (vlane ? sl : NV - 1)];
+          else if constexpr (L::BUFLOAD) x[a] = buffer_cf(Tr, voff, kk * NV * (int)sizeof(cf));
           else x[a] = *reinterpret_cast<const cf*>(reinterpret_cast<const char*>(T + kk * NV) + voff);
         }
 #pragma unroll
@@ -871,7 +903,7 @@ __global__ __launch_bounds__(FLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresf(cons
     } else {
       const int64_t chunk = g / np;
       p = g - chunk * np;
-      l0 = chunk * lchunk;
+        l0 = chunk * lchunk;
     }
     const cf* E = spec_p + p * SPEC;
     cf ev[R1];
@@ -1437,7 +1469,7 @@ hipError_t launch_xcf_scores(int n, const float2* spec_p, int64_t p, const float
 }
 
 // Scores of each pattern against its own k templates, scores[p k + j] for template cand[p k + j], by the
-// library search kernel (96, 128 and 160)
+// library search kernel
 hipError_t launch_xcf_scores_cand(int n, const float2* spec_p, int64_t p, const float2* spec_l, int64_t l,
                                   const int32_t* cand, int k, int max_shift, float* scores, hipStream_t stream) {
   if (p <= 0 || k <= 0) return hipSuccess;
@@ -1458,7 +1490,9 @@ hipError_t launch_xcf_scores_cand(int n, const float2* spec_p, int64_t p, const 
     };
     const bool w = max_shift >= 0;
     hipError_t e = hipErrorInvalidValue;
-    if (n == 96)
+    if (n == 64)
+      e = w ? run(k_xcf_scoresw<64, true, false, true>, WLay<64>::NT) : run(k_xcf_scoresw<64, false, false, true>, WLay<64>::NT);
+    else if (n == 96)
       e = w ? run(k_xcf_scoresf<96, true, false, true>, FLay<96>::NT) : run(k_xcf_scoresf<96, false, false, true>, FLay<96>::NT);
     else if (n == 128)
       e = w ? run(k_xcf_scores128<true, false, true>, 512) : run(k_xcf_scores128<false, false, true>, 512);
@@ -1484,12 +1518,32 @@ hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_item
     return hipGetLastError();
   };
   const bool w = max_shift >= 0;
+  if (n == 64)
+    return w ? run(k_xcf_scoresw<64, true, true, true>, WLay<64>::NT) : run(k_xcf_scoresw<64, false, true, true>, WLay<64>::NT);
   if (n == 96)
     return w ? run(k_xcf_scoresf<96, true, true, true>, FLay<96>::NT) : run(k_xcf_scoresf<96, false, true, true>, FLay<96>::NT);
   if (n == 128) return w ? run(k_xcf_scores128<true, true, true>, 512) : run(k_xcf_scores128<false, true, true>, 512);
   if (n == 160)
     return w ? run(k_xcf_scoresf<160, true, true, true>, FLay<160>::NT) : run(k_xcf_scoresf<160, false, true, true>, FLay<160>::NT);
   return hipErrorInvalidValue;
+}
+
+// Whole rows at 64: patterns rows[0 .. queue[1]), at most `most`, against all l templates, scores[row][l], by
+// the blocks that 256 CUs hold; queue[0] is 0 at entry
+hipError_t launch_xcf_scores_rows64(const float2* spec_p, int64_t most, const int32_t* rows, const float2* spec_l,
+                                    int64_t l, int* queue, int max_shift, float* scores, hipStream_t stream) {
+  if (most <= 0 || l <= 0) return hipSuccess;
+  const int lchunk = 32;
+  const int64_t chunks = most * ((l + lchunk - 1) / lchunk);
+  if (chunks > 0x7ffffff0LL) return hipErrorInvalidValue;
+  const dim3 grid((unsigned)(chunks < 768 ? chunks : 768));
+  const auto run = [&](auto kernel) {
+    hipLaunchKernelGGL(kernel, grid, dim3(WLay<64>::NT), 0, stream, (const cf*)spec_p, int64_t(1), (const cf*)spec_l, l,
+                       lchunk, int64_t(0), max_shift, scores, queue, rows, l, (const int32_t*)nullptr,
+                       (const int2*)nullptr);
+    return hipGetLastError();
+  };
+  return max_shift >= 0 ? run(k_xcf_scoresw<64, true, true>) : run(k_xcf_scoresw<64, false, true>);
 }
 
 hipError_t xcf_persistent_occupancy(int n, int max_shift, int* blocks_per_cu) {
