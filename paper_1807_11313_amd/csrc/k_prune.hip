@@ -11,12 +11,13 @@
 // So   score(p, l) <= coarse(p, l) + h^2 / 8 sqrt(k_p k_l) + sqrt(eh_p eh_l) + rounding,
 // where coarse is the largest low value of the grid and the other terms are products of two numbers
 // per spectrum.  With h0, the full-size score of the template with the largest coarse value, every
-// template whose bound lies below h0 is out.  The others (0.8 % of a 4,000-template library for patterns
-// that match it, SNR 5) get their full-size score from the search kernel itself, so the pick is that of
-// the whole score matrix, bit for bit, ties included.  Patterns that match nothing keep most of their
-// templates; then the coarse values and the lists come on top of the full search: 200 patterns of noise
-// against 3,000 templates 4.26 -> 4.81 ms at 96, 6.63 -> 6.98 at 128, 14.4 -> 15.2 at 160, where 200
-// patterns of the library's material take 4.26 -> 0.28, 6.63 -> 0.33 and 14.4 -> 0.48 ms (whole calls).
+// template whose bound lies below h0 is out (99 % of a 4,000-template library for patterns that match it,
+// SNR 5), and of the rest those whose bound from a grid of half the step does.  What remains gets its
+// full score from the search kernel itself, so the pick is that of the whole score matrix, bit for bit,
+// ties included.  Patterns that match nothing keep most of their templates; then the coarse values and the
+// lists come on top of the full search: 200 patterns of noise against 3,000 templates 4.25 -> 4.76 ms at 96,
+// 6.62 -> 6.84 at 128, 14.4 -> 14.8 at 160, where 200 patterns of the library's material take 4.25 -> 0.26,
+// 6.63 -> 0.30 and 14.4 -> 0.36 ms (whole calls).
 #include "ebsd_common.hpp"
 #include "ebsd_internal.hpp"
 
@@ -94,6 +95,19 @@ __device__ __forceinline__ float dpp_max(float v) {
   return fmaxf(v, __builtin_bit_cast(float, __builtin_amdgcn_mov_dpp(__builtin_bit_cast(int, v), CTRL, 0xf, 0xf, true)));
 }
 
+// A = Z(u) + Z(-u), D = Z(u) - Z(-u) of Z = E conj(T) for a lane's four u: (Re A, Im D) and (Im A, Re D)
+__device__ __forceinline__ void form_sums(h8 ea, h8 eb, h8 xp, h8 xm, h8* ad, h8* bd) {
+  const h4 er = ea.lo, ei = ea.hi, fr = eb.lo, fi = eb.hi;
+  const h4 xpr = xp.lo, xpi = xp.hi, xmr = xm.lo, xmi = xm.hi;
+  const h4 mr = __builtin_elementwise_fma(fr, xmr, fi * xmi), mi = __builtin_elementwise_fma(fi, xmr, -(fr * xmi));
+  const h4 ar = __builtin_elementwise_fma(er, xpr, __builtin_elementwise_fma(ei, xpi, mr));
+  const h4 ai = __builtin_elementwise_fma(ei, xpr, __builtin_elementwise_fma(-er, xpi, mi));
+  const h4 two = {(_Float16)-2.0f, (_Float16)-2.0f, (_Float16)-2.0f, (_Float16)-2.0f};
+  const h4 dr = __builtin_elementwise_fma(two, mr, ar), di = __builtin_elementwise_fma(two, mi, ai);
+  *ad = __builtin_shufflevector(ar, di, 0, 1, 2, 3, 4, 5, 6, 7);
+  *bd = __builtin_shufflevector(ai, dr, 0, 1, 2, 3, 4, 5, 6, 7);
+}
+
 // coarse[p][l] = the largest low value over the grid points t h, t = +-(j + 1/2), j <= last (both axes), by
 // the +-u, +-s symmetric products of k_xcf_even.hip.  One 16 x 16 tile per stage (u and j below 16, v
 // and j below 16): with A = Z(u) + Z(-u), D = Z(u) - Z(-u) the first stage's four sums
@@ -144,18 +158,11 @@ __global__ __launch_bounds__(512, 4) void k_coarse(const h8* __restrict__ low_p,
     const int64_t l = l0 + wave * tc + t;
     if (l >= nl) break;
     const h8 xp = low_l[l * FRAG + lane], xm = low_l[l * FRAG + 64 + lane];
-    const h4 xpr = xp.lo, xpi = xp.hi, xmr = xm.lo, xmi = xm.hi;
     float* const o = out + (wave * tc + t) * PT;
     const auto best_of = [&](int pb) {
       const h8 ea = ep[pb * FRAG + lane], eb = ep[pb * FRAG + 64 + lane];
-      const h4 er = ea.lo, ei = ea.hi, fr = eb.lo, fi = eb.hi;
-      const h4 mr = __builtin_elementwise_fma(fr, xmr, fi * xmi), mi = __builtin_elementwise_fma(fi, xmr, -(fr * xmi));
-      const h4 ar = __builtin_elementwise_fma(er, xpr, __builtin_elementwise_fma(ei, xpi, mr));
-      const h4 ai = __builtin_elementwise_fma(ei, xpr, __builtin_elementwise_fma(-er, xpi, mi));
-      const h4 two = {(_Float16)-2.0f, (_Float16)-2.0f, (_Float16)-2.0f, (_Float16)-2.0f};
-      const h4 dr = __builtin_elementwise_fma(two, mr, ar), di = __builtin_elementwise_fma(two, mi, ai);
-      const h8 ad = __builtin_shufflevector(ar, di, 0, 1, 2, 3, 4, 5, 6, 7);
-      const h8 bd = __builtin_shufflevector(ai, dr, 0, 1, 2, 3, 4, 5, 6, 7);
+      h8 ad, bd;
+      form_sums(ea, eb, xp, xm, &ad, &bd);
       const f4 z = {0.f, 0.f, 0.f, 0.f};
       const f4 f1 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ad, cm, z, 0, 0, 0);
       const f4 f2 = __builtin_amdgcn_mfma_f32_16x16x32_f16(ad, cp, z, 0, 0, 0);
@@ -206,26 +213,87 @@ __global__ __launch_bounds__(256) void k_one_each(int64_t p, int32_t* __restrict
   items[i] = make_int2((int)i, 0);
 }
 
+// The largest low value over the 64 x 64 grid of half the step (products as in k_coarse, two tiles per axis), in
+// the wave's last lane; e, x: the low parts of pattern and template
+struct FineConsts {
+  h8 cp[2], cm[2];
+  h4 c2[2], s2[2];
+  __device__ __forceinline__ void init(int r16, int q4) {
+#pragma unroll
+    for (int a = 0; a < 2; ++a)
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const int f = 4 * q4 + i;
+        float s, c;
+        sincospif((float)(f * (2 * (16 * a + r16) + 1)) / (float)(2 * G), &s, &c);
+        cp[a][i] = cm[a][i] = (_Float16)c;
+        cp[a][4 + i] = (_Float16)s;
+        cm[a][4 + i] = (_Float16)(-s);
+        c2[a][i] = (_Float16)(f ? 2.0f * c : c);
+        s2[a][i] = (_Float16)(f ? 2.0f * s : s);
+      }
+  }
+};
+__device__ __forceinline__ float fine_max(const FineConsts& k, h8 ea, h8 eb, h8 xp, h8 xm, int r16, int q4, int last) {
+  h8 ad, bd;
+  form_sums(ea, eb, xp, xm, &ad, &bd);
+  const f4 z = {0.f, 0.f, 0.f, 0.f};
+  float m = -INFINITY;
+#pragma unroll
+  for (int a = 0; a < 2; ++a) {
+    const h4 f1 = __builtin_convertvector(__builtin_amdgcn_mfma_f32_16x16x32_f16(ad, k.cm[a], z, 0, 0, 0), h4);
+    const h4 f2 = __builtin_convertvector(__builtin_amdgcn_mfma_f32_16x16x32_f16(ad, k.cp[a], z, 0, 0, 0), h4);
+    const h4 f3 = __builtin_convertvector(__builtin_amdgcn_mfma_f32_16x16x32_f16(bd, k.cp[a], z, 0, 0, 0), h4);
+    const h4 f4_ = __builtin_convertvector(__builtin_amdgcn_mfma_f32_16x16x32_f16(bd, k.cm[a], z, 0, 0, 0), h4);
+    const bool col = 16 * a + r16 <= last;
+#pragma unroll
+    for (int b = 0; b < 2; ++b) {
+      const f4 u1 = __builtin_amdgcn_mfma_f32_16x16x16f16(k.c2[b], f1, z, 0, 0, 0);
+      const f4 u2 = __builtin_amdgcn_mfma_f32_16x16x16f16(k.c2[b], f2, z, 0, 0, 0);
+      const f4 w1 = __builtin_amdgcn_mfma_f32_16x16x16f16(k.s2[b], f3, z, 0, 0, 0);
+      const f4 w2 = __builtin_amdgcn_mfma_f32_16x16x16f16(k.s2[b], f4_, z, 0, 0, 0);
+#pragma unroll
+      for (int i = 0; i < 4; ++i) {
+        const float v = fmaxf(u1[i] + fabsf(w1[i]), u2[i] + fabsf(w2[i]));
+        m = fmaxf(m, col && 16 * b + 4 * q4 + i <= last ? v : -INFINITY);
+      }
+    }
+  }
+  m = dpp_max<0x128>(m);
+  m = dpp_max<0x124>(m);
+  m = dpp_max<0x122>(m);
+  m = dpp_max<0x121>(m);
+  m = dpp_max<0x142>(m);
+  return dpp_max<0x143>(m);
+}
+
 // The templates of each pattern that its bound keeps: cand[p l ..] (any order) and count[p], and their chunks
-// in the queue, of list_chunk(count) entries or, with rows, of kListChunk.  With rows, a pattern that keeps
-// more than a third of the library goes there instead (queue[5] counts them) and its count is -1: a pair of a
-// list costs up to 3 times one of a row in the even forms, whose rows share patterns, and 1.4 times at 64, whose
-// rows share a template load; at 96 to 160 it is 1.05 and a row launch would not pay.
-__global__ __launch_bounds__(256) void k_prune_select(const float* __restrict__ coarse, int64_t l, float h28,
-                                                      const float2* __restrict__ stat_p,
-                                                      const float2* __restrict__ stat_l,
-                                                      const float* __restrict__ h0, int32_t* __restrict__ cand,
-                                                      int32_t* __restrict__ count, int2* __restrict__ items,
-                                                      int* __restrict__ queue, int32_t* __restrict__ rows) {
+// in the queue, of list_chunk(count) entries or, with rows, of kListChunk.  Up to FINE of them are bounded
+// once more from the grid of half the step, with a quarter of the curvature term (0.11 to 0.14 -> 0.03), one
+// wave a template.  @FINE@
+// With rows, a pattern that keeps more than a third of the library goes there instead (queue[5] counts them)
+// and its count is -1: a pair of a list costs up to 3 times one of a row in the even forms, whose rows share
+// patterns, and 1.4 times at 64, whose rows share a template load; at 96 to 160 it is 1.05 and a row launch
+// would not pay.
+constexpr int FINE = 1024;
+__global__ __launch_bounds__(512, 4) void k_prune_select(const float* __restrict__ coarse, int64_t l, float h28,
+                                                         const h8* __restrict__ low_p, const h8* __restrict__ low_l,
+                                                         const float2* __restrict__ stat_p,
+                                                         const float2* __restrict__ stat_l,
+                                                         const float* __restrict__ h0, int last,
+                                                         int32_t* __restrict__ cand, int32_t* __restrict__ count,
+                                                         int2* __restrict__ items, int* __restrict__ queue,
+                                                         int32_t* __restrict__ rows) {
   const int64_t p = blockIdx.x;
-  const int lane = threadIdx.x & 63;
-  __shared__ int kept;
-  if (threadIdx.x == 0) kept = 0;
+  const int tid = threadIdx.x, lane = tid & 63;
+  __shared__ int kept, fine;
+  __shared__ int list[FINE];
+  if (tid == 0) kept = fine = 0;
   __syncthreads();
   const float2 sp = stat_p[p];
   const float eh = 1.0002f * sp.x, kl = 1.0002f * h28 * sp.y, least = h0[p] - kRound;
-  for (int64_t i0 = 0; i0 < l; i0 += 256) {
-    const int64_t i = i0 + threadIdx.x;
+  for (int64_t i0 = 0; i0 < l; i0 += 512) {
+    const int64_t i = i0 + tid;
     bool keep = false;
     if (i < l) {
       const float2 sl = stat_l[i];
@@ -236,24 +304,43 @@ __global__ __launch_bounds__(256) void k_prune_select(const float* __restrict__ 
     int at = 0;
     if (lane == 0) at = atomicAdd(&kept, __popcll(mask));
     at = __shfl(at, 0, 64) + __popcll(mask & ((1ull << lane) - 1));
-    if (keep) cand[p * l + at] = (int32_t)i;
+    if (keep) {
+      cand[p * l + at] = (int32_t)i;
+      if (at < FINE) list[at] = (int)i;
+    }
   }
   __syncthreads();
-  if (rows && kept > l / 3) {
-    if (threadIdx.x == 0) {
+  int n = kept;
+  if (rows && n > l / 3) {
+    if (tid == 0) {
       count[p] = -1;
       rows[atomicAdd(queue + 5, 1)] = (int)p;
     }
     return;
   }
-  const int ch = rows ? kListChunk : list_chunk(kept), nc = (kept + ch - 1) / ch;
+  if (n > 1 && n <= FINE) {
+    const int r16 = lane & 15, q4 = lane >> 4;
+    FineConsts k;
+    k.init(r16, q4);
+    const h8 ea = low_p[p * FRAG + lane], eb = low_p[p * FRAG + 64 + lane];
+    for (int j = __builtin_amdgcn_readfirstlane(tid >> 6); j < n; j += 8) {
+      const int64_t i = list[j];
+      const h8 xp = low_l[i * FRAG + lane], xm = low_l[i * FRAG + 64 + lane];
+      const float2 sl = stat_l[i];
+      const float m = fine_max(k, ea, eb, xp, xm, r16, q4, last) * (1.0f / (kScale * kScale));
+      if (lane == 63 && m + __fmaf_rn(0.25f * kl, sl.y, eh * sl.x) >= least) cand[p * l + atomicAdd(&fine, 1)] = (int)i;
+    }
+    __syncthreads();
+    n = fine;
+  }
+  const int ch = rows ? kListChunk : list_chunk(n), nc = (n + ch - 1) / ch;
   __shared__ int first;
-  if (threadIdx.x == 0) {
-    count[p] = kept;
+  if (tid == 0) {
+    count[p] = n;
     first = nc ? atomicAdd(queue + 1, nc) : 0;
   }
   __syncthreads();
-  for (int i = threadIdx.x; i < nc; i += 256) items[first + i] = make_int2((int)p, i * ch);
+  for (int i = tid; i < nc; i += 512) items[first + i] = make_int2((int)p, i * ch);
 }
 
 // Best of the kept templates, or of the whole row where count is -1 (ties: smallest index; none kept, every
@@ -333,8 +420,11 @@ hipError_t launch_pruned_best(int n, PruneBy by, const float2* spec_p, const flo
   if (p > (int64_t(1) << 31) / 256) return hipErrorInvalidValue;
   hipError_t e;
   const float h = (float)n / (float)G;
-  // the grid's cells that cover a shift window
-  const int last = max_shift < 0 ? 15 : std::min(15, std::max(0, (int)ceilf((float)max_shift / h - 0.5f)));
+  // the cells of a grid of step s that cover a shift window
+  const auto last_of = [&](float s, int all) {
+    return max_shift < 0 ? all : std::min(all, std::max(0, (int)ceilf((float)max_shift / s - 0.5f)));
+  };
+  const int last = last_of(h, 15);
   // templates per wave: TC, fewer where that leaves less than four rounds of the 512 blocks that run at once
   int tc = TC;
   while (tc > 1 && ((p + PT - 1) / PT) * ((l + 8 * tc - 1) / (8 * tc)) < 2048) tc >>= 1;
@@ -357,9 +447,9 @@ hipError_t launch_pruned_best(int n, PruneBy by, const float2* spec_p, const flo
                               ws.frag, true, ws.h0, stream);
   }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_prune_select, dim3((unsigned)p), dim3(256), 0, stream, ws.scores, l, 0.125f * h * h, stat_p,
-                     stat_l, ws.h0, ws.cand, ws.count, ws.items, ws.queue,
-                     by == PruneBy::Fft && n != 64 ? nullptr : ws.rows);
+  hipLaunchKernelGGL(k_prune_select, dim3((unsigned)p), dim3(512), 0, stream, ws.scores, l, 0.125f * h * h,
+                     (const h8*)low_p, (const h8*)low_l, stat_p, stat_l, ws.h0, last_of(0.5f * h, 31), ws.cand,
+                     ws.count, ws.items, ws.queue, by == PruneBy::Fft && n != 64 ? nullptr : ws.rows);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int64_t most = p * list_chunks(l);
   e = by == PruneBy::Fft
