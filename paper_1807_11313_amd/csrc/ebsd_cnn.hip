@@ -100,12 +100,10 @@ __global__ void k_gather_rows(const float2* __restrict__ src, const int32_t* __r
   dst[i] = src[(int64_t)list[r] * row + c];
 }
 
-__global__ void k_scatter_best(const int32_t* __restrict__ list, int64_t f, const int32_t* __restrict__ b,
-                               const float* __restrict__ h, int32_t* __restrict__ best, float* __restrict__ h_best) {
+__global__ void k_scatter_best(const int32_t* __restrict__ list, int64_t nf, const int32_t* __restrict__ b,
+                               int32_t* __restrict__ best) {
   const int64_t i = (int64_t)blockIdx.x * 256 + threadIdx.x;
-  if (i >= f) return;
-  best[list[i]] = b[i];
-  h_best[list[i]] = h[i];
+  if (i < nf) best[list[i]] = b[i];
 }
 
 }  // namespace
@@ -477,8 +475,26 @@ int ebsd_index_proposed(const ebsd_batch* pats, const ebsd_master* mp, const ebs
     else CN_TRY(launch_spectra(n, pats->data, npix, P, fp, spec_p, nullptr, st), "spectra(patterns)");
     // correlation on the candidates only
     // (at 128 by the library search kernel over each pattern's candidate list,
-    // the scores the exhaustive search gives the same pairs; elsewhere pair by pair)
-    if (n == 128) {
+    // the scores the exhaustive search gives the same pairs, of many pairs only
+    // those whose bound reaches the pattern's best; elsewhere pair by pair)
+    float2 *low_l = nullptr, *stat_l = nullptr;
+    if (prune_cand_pays(n, P, top_k, L)) {
+      const int64_t lc = low_spec_complex();
+      low_l = (float2*)get(sizeof(float2) * lc * L);
+      stat_l = (float2*)get(sizeof(float2) * L);
+      float2* low_p = (float2*)get(sizeof(float2) * lc * P);
+      float2* stat_p = (float2*)get(sizeof(float2) * P);
+      const CandScratch cs{(float*)get(sizeof(float) * PK),   (int32_t*)get(sizeof(int32_t) * PK),
+                           (int32_t*)get(sizeof(int32_t) * PK), (int32_t*)get(sizeof(int32_t) * P),
+                           (int32_t*)get(sizeof(int32_t) * P),  (float*)get(sizeof(float) * P),
+                           (int2*)get(sizeof(int2) * P * list_chunks(top_k)), (int*)get(sizeof(int) * 2)};
+      if (short_of) return fail(EBSD_E_NOMEM, "proposal scratch allocation failed");
+      CN_TRY(launch_low_spectra(n, spec_l, L, low_l, stat_l, st), "low spectra(templates)");
+      CN_TRY(launch_low_spectra(n, spec_p, P, low_p, stat_p, st), "low spectra(patterns)");
+      CN_TRY(launch_pruned_cand(n, spec_p, low_p, stat_p, P, spec_l, low_l, stat_l, L, cand, top_k, p.max_shift, cs,
+                                hk, st),
+             "xcf(candidates)");
+    } else if (n == 128) {
       CN_TRY(launch_xcf_scores_cand(n, spec_p, P, spec_l, L, cand, top_k, p.max_shift, hk, st), "xcf(candidates)");
     } else {
       hipLaunchKernelGGL(k_pairs, dim3(nb(PK)), dim3(256), 0, st, cand, P, top_k, pi);
@@ -494,16 +510,40 @@ int ebsd_index_proposed(const ebsd_batch* pats, const ebsd_master* mp, const ebs
     CN_TRY(hipStreamSynchronize(st), "fallback count");
     if (nf > 0) {
       float2* spec_f = (float2*)get(sizeof(float2) * sc * nf);
-      float* sc_f = (float*)get(sizeof(float) * (size_t)nf * L);
       int32_t* b_f = (int32_t*)get(sizeof(int32_t) * nf);
-      float* h_f = (float*)get(sizeof(float) * nf);
+      const bool prune = prune_pays(n, PruneBy::Fft, p.max_shift, (int64_t)nf * L);
+      const int64_t slab = prune ? prune_slab(nf, L) : nf, lc = low_spec_complex();
+      float* sc_f = (float*)get(sizeof(float) * (size_t)slab * L);
+      float* h_f = (float*)get(sizeof(float) * slab);
       if (short_of) return fail(EBSD_E_NOMEM, "fallback scratch allocation failed");
       hipLaunchKernelGGL(k_gather_rows, dim3(nb((int64_t)nf * sc)), dim3(256), 0, st, spec_p, list, (int64_t)nf, sc,
                          spec_f);
-      CN_TRY(launch_xcf_scores(n, spec_f, nf, spec_l, L, p.max_shift, sc_f, st), "xcf(fallback)");
-      CN_TRY(launch_library_argmax(sc_f, nf, L, b_f, h_f, st), "argmax(fallback)");
-      hipLaunchKernelGGL(k_scatter_best, dim3(nb(nf)), dim3(256), 0, st, list, (int64_t)nf, b_f, h_f, best_idx,
-                         h_best);
+      if (prune) {
+        if (!low_l) {
+          low_l = (float2*)get(sizeof(float2) * lc * L);
+          stat_l = (float2*)get(sizeof(float2) * L);
+          if (short_of) return fail(EBSD_E_NOMEM, "fallback scratch allocation failed");
+          CN_TRY(launch_low_spectra(n, spec_l, L, low_l, stat_l, st), "low spectra(templates)");
+        }
+        float2* low_f = (float2*)get(sizeof(float2) * lc * slab);
+        float2* stat_f = (float2*)get(sizeof(float2) * slab);
+        const PruneScratch pr{sc_f, (int32_t*)get(sizeof(int32_t) * (size_t)slab * L),
+                              (int32_t*)get(sizeof(int32_t) * slab), h_f,
+                              (int2*)get(sizeof(int2) * (size_t)slab * list_chunks(L)), (int*)get(sizeof(int) * 8),
+                              (int32_t*)get(sizeof(int32_t) * slab), nullptr};
+        if (short_of) return fail(EBSD_E_NOMEM, "fallback scratch allocation failed");
+        for (int64_t s = 0; s < nf; s += slab) {
+          const int64_t b = std::min<int64_t>(slab, nf - s);
+          CN_TRY(launch_low_spectra(n, spec_f + s * sc, b, low_f, stat_f, st), "low spectra(fallback)");
+          CN_TRY(launch_pruned_best(n, PruneBy::Fft, spec_f + s * sc, low_f, stat_f, b, spec_l, low_l, stat_l, L,
+                                    p.max_shift, pr, b_f + s, st),
+                 "pruned search(fallback)");
+        }
+      } else {
+        CN_TRY(launch_xcf_scores(n, spec_f, nf, spec_l, L, p.max_shift, sc_f, st), "xcf(fallback)");
+        CN_TRY(launch_library_argmax(sc_f, nf, L, b_f, h_f, st), "argmax(fallback)");
+      }
+      hipLaunchKernelGGL(k_scatter_best, dim3(nb(nf)), dim3(256), 0, st, list, (int64_t)nf, b_f, best_idx);
       CN_TRY(hipGetLastError(), "fallback scatter");
     }
     // the winner's peaks

@@ -70,7 +70,7 @@ hipError_t launch_xcf_scores(int n, const float2* spec_p, int64_t p, const float
 // The same for each pattern's own k candidates among l templates: scores[p][j]
 // for template cand[p][j], clamped to [0, l) (the sizes of the FFT search;
 // hipErrorInvalidValue for others), and for lists of their own lengths,
-// cand[p][j], j < count[p] <= l, in rows of l, as queue[1] chunks (pattern,
+// cand[p][j], j < count[p] <= row, in rows of `row`, as queue[1] chunks (pattern,
 // first entry) of up to kListChunk entries; queue[0] is 0 at entry.
 hipError_t launch_xcf_scores_cand(int n, const float2* spec_p, int64_t p, const float2* spec_l, int64_t l,
                                   const int32_t* cand, int k, int max_shift, float* scores, hipStream_t stream);
@@ -78,8 +78,8 @@ constexpr int kListChunk = 8, kListBlocks = 1024;  // blocks: 4 for each of 256 
 // Entries of a chunk: more where a pattern keeps many, which then cost what they do in the full search
 __host__ __device__ inline int list_chunk(int64_t count) { return count >= 1024 ? 2 * kListChunk : kListChunk; }
 inline int64_t list_chunks(int64_t l) { return (l + kListChunk - 1) / kListChunk; }
-hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_items, const float2* spec_l, int64_t l,
-                                   const int32_t* cand, const int32_t* count, const int2* items, int* queue,
+hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_items, const float2* spec_l,
+                                   int64_t lib_n, int64_t row, const int32_t* cand, const int32_t* count, const int2* items, int* queue,
                                    int max_shift, float* scores, hipStream_t stream);
 
 // And for whole rows at 64: patterns rows[0 .. queue[1]), at most `most`, against
@@ -114,6 +114,26 @@ hipError_t launch_low_spectra(int n, const float2* spec, int64_t k, float2* low,
 hipError_t launch_pruned_best(int n, PruneBy by, const float2* spec_p, const float2* low_p, const float2* stat_p,
                               int64_t p, const float2* spec_l, const float2* low_l, const float2* stat_l, int64_t l,
                               int max_shift, const PruneScratch& ws, int32_t* best, hipStream_t stream);
+
+// launch_xcf_scores_cand where only each pattern's best matters: candidates
+// whose bound lies below it get -infinity.  Scratch: bound, list and pos
+// [p][k], count, first and h0 [p], items
+// [p][list_chunks(k)], queue [2].
+struct CandScratch {
+  float* bound;
+  int32_t* list;
+  int32_t* pos;
+  int32_t* count;
+  int32_t* first;
+  float* h0;
+  int2* items;
+  int* queue;
+};
+bool prune_cand_pays(int n, int64_t p, int k, int64_t l);
+hipError_t launch_pruned_cand(int n, const float2* spec_p, const float2* low_p, const float2* stat_p, int64_t p,
+                              const float2* spec_l, const float2* low_l, const float2* stat_l, int64_t l,
+                              const int32_t* cand, int k, int max_shift, const CandScratch& ws, float* scores,
+                              hipStream_t stream);
 
 // Integer peak (value, signed shift) for K explicit pairs (pi[k], li[k]),
 // and optionally the full correlation map [K][n][n] (row = s_y mod n).

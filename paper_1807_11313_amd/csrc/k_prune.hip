@@ -343,6 +343,94 @@ __global__ __launch_bounds__(512, 4) void k_prune_select(const float* __restrict
   for (int i = tid; i < nc; i += 512) items[first + i] = make_int2((int)p, i * ch);
 }
 
+// bound[p k + j] = the half-step bound of candidate cand[p k + j]; first[p] = the candidate with the largest low
+// value; one wave a candidate
+__global__ __launch_bounds__(256) void k_cand_bounds(const h8* __restrict__ low_p, const float2* __restrict__ stat_p,
+                                                     const h8* __restrict__ low_l, const float2* __restrict__ stat_l,
+                                                     int64_t l, const int32_t* __restrict__ cand, int k, float h28,
+                                                     int last, float* __restrict__ bound, int32_t* __restrict__ first,
+                                                     int* __restrict__ queue) {
+  const int64_t p = blockIdx.x;
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, q4 = lane >> 4;
+  const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
+  if (p == 0 && tid < 2) queue[tid] = 0;
+  FineConsts c;
+  c.init(r16, q4);
+  const h8 ea = low_p[p * FRAG + lane], eb = low_p[p * FRAG + 64 + lane];
+  const float2 sp = stat_p[p];
+  const float eh = 1.0002f * sp.x, kl = 1.0002f * h28 * sp.y;
+  float bv = -INFINITY;
+  int bi = cand[p * k];
+  for (int j = wave; j < k; j += 4) {
+    int64_t i = cand[p * k + j];
+    i = i < 0 ? 0 : (i >= l ? l - 1 : i);
+    const h8 xp = low_l[i * FRAG + lane], xm = low_l[i * FRAG + 64 + lane];
+    const float2 sl = stat_l[i];
+    const float m = fine_max(c, ea, eb, xp, xm, r16, q4, last) * (1.0f / (kScale * kScale));
+    if (lane == 63) {
+      bound[p * k + j] = m + __fmaf_rn(kl, sl.y, eh * sl.x);
+      if (m > bv) {
+        bv = m;
+        bi = (int)i;
+      }
+    }
+  }
+  __shared__ float rv[4];
+  __shared__ int ri[4];
+  if (lane == 63) {
+    rv[wave] = bv;
+    ri[wave] = bi;
+  }
+  __syncthreads();
+  if (tid == 0) {
+    for (int w = 1; w < 4; ++w)
+      if (rv[w] > rv[0]) {
+        rv[0] = rv[w];
+        ri[0] = ri[w];
+      }
+    first[p] = ri[0];
+  }
+}
+
+// The candidates that reach the score of `first`, and where they stand; scores are -infinity until they have one
+__global__ __launch_bounds__(64) void k_cand_select(const float* __restrict__ bound, const int32_t* __restrict__ cand,
+                                                    int k, const float* __restrict__ h0, int32_t* __restrict__ list,
+                                                    int32_t* __restrict__ pos, int32_t* __restrict__ count,
+                                                    int2* __restrict__ items, int* __restrict__ queue,
+                                                    float* __restrict__ scores) {
+  const int64_t p = blockIdx.x;
+  const int lane = threadIdx.x;
+  const float least = h0[p] - kRound;
+  int n = 0;
+  for (int j0 = 0; j0 < k; j0 += 64) {
+    const int j = j0 + lane;
+    const bool keep = j < k && bound[p * k + j] >= least;
+    if (j < k) scores[p * k + j] = -INFINITY;
+    const unsigned long long mask = __ballot(keep);
+    if (keep) {
+      const int at = n + __popcll(mask & ((1ull << lane) - 1));
+      list[p * k + at] = cand[p * k + j];
+      pos[p * k + at] = j;
+    }
+    n += __popcll(mask);
+  }
+  const int ch = list_chunk(n), nc = (n + ch - 1) / ch;
+  int base = 0;
+  if (lane == 0) {
+    count[p] = n;
+    base = nc ? atomicAdd(queue + 1, nc) : 0;
+  }
+  base = __shfl(base, 0, 64);
+  for (int i = lane; i < nc; i += 64) items[base + i] = make_int2((int)p, i * ch);
+}
+
+__global__ __launch_bounds__(64) void k_cand_scatter(const float* __restrict__ listed, const int32_t* __restrict__ pos,
+                                                     const int32_t* __restrict__ count, int k,
+                                                     float* __restrict__ scores) {
+  const int64_t p = blockIdx.x;
+  for (int i = threadIdx.x; i < count[p]; i += 64) scores[p * k + pos[p * k + i]] = listed[p * k + i];
+}
+
 // Best of the kept templates, or of the whole row where count is -1 (ties: smallest index; none kept, every
 // score NaN: 0)
 __global__ __launch_bounds__(256) void k_prune_argmax(const float* __restrict__ scores,
@@ -453,7 +541,7 @@ hipError_t launch_pruned_best(int n, PruneBy by, const float2* spec_p, const flo
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int64_t most = p * list_chunks(l);
   e = by == PruneBy::Fft
-          ? launch_xcf_scores_lists(n, spec_p, most, spec_l, l, ws.cand, ws.count, ws.items, ws.queue, max_shift,
+          ? launch_xcf_scores_lists(n, spec_p, most, spec_l, l, l, ws.cand, ws.count, ws.items, ws.queue, max_shift,
                                     ws.scores, stream)
           : launch_xcf_even_lists(n, split, spec_p, most, spec_l, l, l, ws.cand, ws.count, ws.items, ws.queue,
                                   max_shift, ws.frag, false, ws.scores, stream);
@@ -464,6 +552,39 @@ hipError_t launch_pruned_best(int n, PruneBy by, const float2* spec_p, const flo
     e = launch_xcf_scores_rows64(spec_p, p, ws.rows, spec_l, l, ws.queue + 4, max_shift, ws.scores, stream);
   if (e != hipSuccess) return e;
   hipLaunchKernelGGL(k_prune_argmax, dim3((unsigned)p), dim3(256), 0, stream, ws.scores, ws.cand, ws.count, l, best);
+  return hipGetLastError();
+}
+
+// Candidates are read at random, 38 KB of spectrum each, so 32 for each of 4,096 patterns out of 8,000 templates
+// take 1.62 ms in full (the whole call 5.99 ms, pruned 4.99).  The bounds need the library's low parts (8 ns a
+// template) and one full score a pattern, which is too much of what 8 candidates a pattern cost (4.81 -> 4.95 ms)
+// and where the library is half as many templates as there are pairs (32 x 1,024 of 16,000: 3.69 -> 3.65).
+bool prune_cand_pays(int n, int64_t p, int k, int64_t l) {
+  return n == 128 && k >= 16 && p * k >= (int64_t(1) << 15) && p * k >= 2 * l && p <= (int64_t(1) << 31) / 256;
+}
+
+hipError_t launch_pruned_cand(int n, const float2* spec_p, const float2* low_p, const float2* stat_p, int64_t p,
+                              const float2* spec_l, const float2* low_l, const float2* stat_l, int64_t l,
+                              const int32_t* cand, int k, int max_shift, const CandScratch& ws, float* scores,
+                              hipStream_t stream) {
+  if (p <= 0 || k <= 0) return hipSuccess;
+  if (p > (int64_t(1) << 31) / 256) return hipErrorInvalidValue;
+  hipError_t e;
+  const float h = (float)n / (float)(2 * G);
+  const int last = max_shift < 0 ? 31 : std::min(31, std::max(0, (int)ceilf((float)max_shift / h - 0.5f)));
+  hipLaunchKernelGGL(k_cand_bounds, dim3((unsigned)p), dim3(256), 0, stream, (const h8*)low_p, stat_p,
+                     (const h8*)low_l, stat_l, l, cand, k, 0.125f * h * h, last, ws.bound, ws.first, ws.queue);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  if ((e = launch_xcf_scores_cand(n, spec_p, p, spec_l, l, ws.first, 1, max_shift, ws.h0, stream)) != hipSuccess)
+    return e;
+  hipLaunchKernelGGL(k_cand_select, dim3((unsigned)p), dim3(64), 0, stream, ws.bound, cand, k, ws.h0, ws.list, ws.pos,
+                     ws.count, ws.items, ws.queue, scores);
+  if ((e = hipGetLastError()) != hipSuccess) return e;
+  // the bounds have served: the listed scores take their place
+  if ((e = launch_xcf_scores_lists(n, spec_p, p * list_chunks(k), spec_l, l, k, ws.list, ws.count, ws.items, ws.queue,
+                                   max_shift, ws.bound, stream)) != hipSuccess)
+    return e;
+  hipLaunchKernelGGL(k_cand_scatter, dim3((unsigned)p), dim3(64), 0, stream, ws.bound, ws.pos, ws.count, k, scores);
   return hipGetLastError();
 }
 

@@ -1503,18 +1503,18 @@ hipError_t launch_xcf_scores_cand(int n, const float2* spec_p, int64_t p, const 
   return hipSuccess;
 }
 
-// The same for lists of count[p] templates in rows of l, in chunks items[g] = (pattern, first entry),
+// The same for lists of count[p] templates in rows of `row`, in chunks items[g] = (pattern, first entry),
 // g < queue[1], of list_chunk(count) entries; queue[0] counts the chunks taken and is 0 at entry.  The lists'
 // lengths differ by two orders of magnitude and only the device knows them: a resident grid takes short
 // chunks from the queue.
-hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_items, const float2* spec_l, int64_t l,
-                                   const int32_t* cand, const int32_t* count, const int2* items, int* queue,
+hipError_t launch_xcf_scores_lists(int n, const float2* spec_p, int64_t max_items, const float2* spec_l,
+                                   int64_t lib_n, int64_t row, const int32_t* cand, const int32_t* count, const int2* items, int* queue,
                                    int max_shift, float* scores, hipStream_t stream) {
   if (max_items <= 0) return hipSuccess;
   const dim3 grid((unsigned)(max_items < kListBlocks ? max_items : kListBlocks));
   const auto run = [&](auto kernel, int threads) {
-    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, (const cf*)spec_p, int64_t(1), (const cf*)spec_l, l,
-                       kListChunk, int64_t(0), max_shift, scores, queue, cand, l, count, items);
+    hipLaunchKernelGGL(kernel, grid, dim3(threads), 0, stream, (const cf*)spec_p, int64_t(1), (const cf*)spec_l, row,
+                       kListChunk, int64_t(0), max_shift, scores, queue, cand, lib_n, count, items);
     return hipGetLastError();
   };
   const bool w = max_shift >= 0;

@@ -120,3 +120,24 @@ def test_ragged_picks(eager):
         data.mul_(1.0)
         plan.run_into(data, master, PC, q, out)
     plan.close()
+
+
+@pytest.mark.parametrize("p, l, k, tau", [(520, 64, 64, -1.0), (500, 70, 70, -1.0), (40, 900, 5, 2.0), (9, 911, 8, 2.0)])
+def test_proposed_picks(p, l, k, tau):
+    import torch
+
+    # every template a candidate, or every pattern in the fallback: the pick is that of the whole search
+    tm, g, master, q = _setup(128, p, l)
+    q[l // 2:l // 2 + l // 4] = q[:l // 4]
+    img = tm.project_templates(master, q, 128, PC)
+    x = img[torch.arange(p, device="cuda:0") * 7 % l].clone()
+    x += 0.5 * x.std() * torch.randn(x.shape, generator=g, device="cuda:0")
+    x[1] = torch.randn((128, 128), generator=g, device="cuda:0")
+    x[2] = 3.0
+    x[3, 1, 1] = float("nan")
+    net = tm.Cnn(l, seed=1)
+    got = tm.index_proposed(x, master, PC, q, net, top_k=k, fallback_tau=tau)
+    want = tm.index_patterns(x, master, PC, q, scores=True)
+    ok = torch.arange(p, device="cuda:0") != 3                           # its proposals are of NaN logits
+    assert torch.equal(got["best_idx"][ok], want["best_idx"][ok])
+    assert torch.equal(got["peak_h"][ok], want["peak_h"][ok])
