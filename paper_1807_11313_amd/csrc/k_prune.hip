@@ -117,10 +117,12 @@ __device__ __forceinline__ void form_sums(h8 ea, h8 eb, h8 xp, h8 xm, h8* ad, h8
 // over the four sign pairs.  A block holds PT patterns in LDS; each of its 8 waves takes tc templates in turn,
 // a template's 16 values per lane serving all the patterns; every phase constant stays in registers.
 // Bound by issue: 8 matrix products (about 130 cycles) and 50 vector instructions a pair.  200 x 3,000 pairs
-// take 119 us, 5,000 x 4,000 3.1 ms (6.5e9 pairs/s); with FP32 products (32 of 16x16x4) 424 us and 12.0 ms; a
+// take 119 us, 5,000 x 4,000 2.84 ms (7.0e9 pairs/s); with FP32 products (32 of 16x16x4) 424 us and 12.0 ms; a
 // 64 x 64 FFT search of wider low parts (|u|, |v| <= 24) ran at 4.2e8 pairs/s.  2 KB a spectrum are read once
 // per block of 32 patterns and 128 templates.  Fewer templates per wave (tc) fill the chip for few pairs: 11 x
 // 3,000 pairs 230 -> 34 us (measured on the FP32 form).
+// ALL: every grid point counts (last = 15), no masks between the two patterns of a step.
+template <bool ALL>
 __global__ __launch_bounds__(512, 4) void k_coarse(const h8* __restrict__ low_p, int64_t np,
                                                    const h8* __restrict__ low_l, int64_t nl, int64_t npt,
                                                    int64_t nblk, int tc, int last, float* __restrict__ coarse,
@@ -159,7 +161,7 @@ __global__ __launch_bounds__(512, 4) void k_coarse(const h8* __restrict__ low_p,
     if (l >= nl) break;
     const h8 xp = low_l[l * FRAG + lane], xm = low_l[l * FRAG + 64 + lane];
     float* const o = out + (wave * tc + t) * PT;
-    const auto best_of = [&](int pb) {
+    const auto best_of = [&](int pb) -> float {
       const h8 ea = ep[pb * FRAG + lane], eb = ep[pb * FRAG + 64 + lane];
       h8 ad, bd;
       form_sums(ea, eb, xp, xm, &ad, &bd);
@@ -173,27 +175,26 @@ __global__ __launch_bounds__(512, 4) void k_coarse(const h8* __restrict__ low_p,
       const f4 w1 = __builtin_amdgcn_mfma_f32_16x16x16f16(s2, __builtin_convertvector(f3, h4), z, 0, 0, 0);
       const f4 w2 = __builtin_amdgcn_mfma_f32_16x16x16f16(s2, __builtin_convertvector(f4_, h4), z, 0, 0, 0);
       float m = -INFINITY;
-      if (last == 15) {
 #pragma unroll
-        for (int i = 0; i < 4; ++i) m = fmaxf(m, fmaxf(u1[i] + fabsf(w1[i]), u2[i] + fabsf(w2[i])));
-      } else {
-#pragma unroll
-        for (int i = 0; i < 4; ++i)
-          if (col && 4 * q4 + i <= last) m = fmaxf(m, fmaxf(u1[i] + fabsf(w1[i]), u2[i] + fabsf(w2[i])));
+      for (int i = 0; i < 4; ++i) {
+        const float v = fmaxf(u1[i] + fabsf(w1[i]), u2[i] + fabsf(w2[i]));
+        m = fmaxf(m, ALL || (col && 4 * q4 + i <= last) ? v : -INFINITY);
       }
-      m = dpp_max<0x128>(m);  // row_ror 8, 4, 2, 1
-      m = dpp_max<0x124>(m);
-      m = dpp_max<0x122>(m);
-      m = dpp_max<0x121>(m);
-      m = dpp_max<0x142>(m);  // row_bcast 15, 31: of the wave, in its last lane
-      m = dpp_max<0x143>(m);
-      if (lane == 63) o[pb] = m;
+      return m;
     };
     // two patterns at a time, independent of each other (an odd count's last one pairs with unused LDS)
 #pragma unroll 1
     for (int pb = 0; pb < pc; pb += 2) {
-      best_of(pb);
-      best_of(pb + 1);
+      const unsigned m0 = __builtin_bit_cast(unsigned, best_of(pb)), m1 = __builtin_bit_cast(unsigned, best_of(pb + 1));
+      // the halves exchanged: the first pattern's values in lanes 0 to 31, the second's in 32 to 63
+      const auto sw = __builtin_amdgcn_permlane32_swap(m0, m1, false, false);
+      float m = fmaxf(__builtin_bit_cast(float, (unsigned)sw[0]), __builtin_bit_cast(float, (unsigned)sw[1]));
+      m = dpp_max<0x128>(m);  // row_ror 8, 4, 2, 1
+      m = dpp_max<0x124>(m);
+      m = dpp_max<0x122>(m);
+      m = dpp_max<0x121>(m);
+      m = dpp_max<0x142>(m);  // row_bcast 15: of the half, in its last lane
+      if ((lane & 31) == 31) o[pb + (lane >> 5)] = m;
     }
   }
   __syncthreads();
@@ -519,8 +520,9 @@ hipError_t launch_pruned_best(int n, PruneBy by, const float2* spec_p, const flo
   const int64_t nch = (l + 8 * tc - 1) / (8 * tc), pmax = std::max<int64_t>(1, ((int64_t(1) << 31) / 512 - 8) / nch) * PT;
   for (int64_t s = 0; s < p; s += pmax) {
     const int64_t pc = p - s < pmax ? p - s : pmax, npt = (pc + PT - 1) / PT, nblk = npt * nch;
-    hipLaunchKernelGGL(k_coarse, dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(512), 0, stream, (const h8*)low_p + s * FRAG,
-                       pc, (const h8*)low_l, l, npt, nblk, tc, last, ws.scores + s * l, ws.queue);
+    hipLaunchKernelGGL(last == 15 ? k_coarse<true> : k_coarse<false>, dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(512), 0,
+                       stream, (const h8*)low_p + s * FRAG, pc, (const h8*)low_l, l, npt, nblk, tc, last,
+                       ws.scores + s * l, ws.queue);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = launch_library_argmax(ws.scores, p, l, best, ws.h0, stream)) != hipSuccess) return e;
