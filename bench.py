@@ -48,6 +48,16 @@ def gemm_pair_flops(n, s, precision):
     return one * (1 if precision == 3 else 3)
 
 
+# Matrix flops per pair that k_xcf_even issues: 16 x 16 tiles over the band rows in chunks of 32 and columns in
+# chunks of 16 (the last row and column of a band that fills them are added apart), with the +-u and +-s symmetries.
+def even_pair_flops(n, s, split):
+    b, st = 3 * n // 8, 1 if s < 16 else 2
+    kc, vt = b // 32 + (b % 32 != 0), b // 16 + (b % 16 != 0)
+    if split:
+        return vt * (kc * 12 * 16384 * st + 12 * 8192 * st * st)
+    return vt * (kc * 32 * st + 16 * st * st) * 2048
+
+
 def kernel_source_hash(prof):
     """sha256 prefix of the profiled kernel's definition and of its launcher
     (each from its marker to the closing brace at column 0; the launcher
@@ -719,7 +729,8 @@ def precision_256(tm, patterns, library, steps, window=15, sample=3, n_sub=96, f
         picks_equal = bool(torch.equal(full["best_idx"], idx["best_idx"]))
         del full
         search_s = ms / 1e3 / max(cnt, 1)
-        flops = P * L * gemm_pair_flops(n, window, 3 if prec == 0 else prec)
+        pair = even_pair_flops(n, window, prec == 1) if prec < 2 else gemm_pair_flops(n, window, prec)
+        flops = P * L * pair
         best = idx["best_idx"].cpu().numpy()
         if ref_best is None:
             ref_best = best
@@ -752,12 +763,11 @@ def precision_256(tm, patterns, library, steps, window=15, sample=3, n_sub=96, f
         if prec == 0:
             roof = {"bound": "mfma", "kernel": "k_xcf_even<256> (FP32 products)", "achieved": flops / search_s / 1e12,
                     "peak": PEAK_MFMA_FP32 / 1e12, "unit": "TFLOP/s", "frac": flops / search_s / PEAK_MFMA_FP32,
-                    "note": "flops of the products without the kernel's symmetries, which do a third of them",
-                    "flops_per_pair": gemm_pair_flops(n, window, 3)}
+                    "flops_per_pair": pair}
         else:
             roof = {"bound": "mfma", "kernel": "k_xcf_even<256>" if prec == 1 else "k_xcf_gemm<256>", "achieved": flops / search_s / 1e12,
                     "peak": PEAK_MFMA_16BIT / 1e12, "unit": "TFLOP/s", "frac": flops / search_s / PEAK_MFMA_16BIT,
-                    "flops_per_pair": gemm_pair_flops(n, window, prec)}
+                    "flops_per_pair": pair}
         res[name] = {"patterns_per_s": P * n_steps / (t1 - t0), "xcf_pairs_per_s": P * L / search_s,
                      "exhaustive_search_ms": search_s * 1e3, "search_ms": step_search_ms,
                      "picks_equal_exhaustive": picks_equal, "roofline": roof,
