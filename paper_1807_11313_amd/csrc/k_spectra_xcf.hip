@@ -188,18 +188,28 @@ __device__ __forceinline__ void xcf_core(const cf* __restrict__ E, const cf* __r
   }
 }
 
+// MAP, WINDOW: whether the map is wanted and the shifts may be limited.  Without either the merge is a
+// select, not a branch, per value; a window's test is worth its branch (8,100 pairs at 128, +-9 px, 3 % slower as
+// a select).
+template <bool MAP, bool WINDOW>
 struct ArgmaxEpi {
   float m;
   int i, n, s;
   float* map;
   __device__ __forceinline__ void operator()(int y, int x, float v) {
-    if (map) map[y * n + x] = v;
-    if (s < 0 || (abs(signed_shift(y, n)) <= s && abs(signed_shift(x, n)) <= s))
-      argmax_merge(m, i, v, y * n + x);
+    const int at = y * n + x;
+    if constexpr (MAP) map[at] = v;
+    if constexpr (WINDOW) {
+      if (s < 0 || (abs(signed_shift(y, n)) <= s && abs(signed_shift(x, n)) <= s)) argmax_merge(m, i, v, at);
+    } else {
+      const bool take = (v > m) | ((v == m) & (at < i));
+      m = take ? v : m;
+      i = take ? at : i;
+    }
   }
 };
 
-template <int N, int NT>
+template <int N, int NT, bool MAP, bool WINDOW>
 __global__ __launch_bounds__(NT) void k_xcf_peak(const cf* __restrict__ spec_p, const cf* __restrict__ spec_l,
                                                  const int32_t* __restrict__ pi, const int32_t* __restrict__ li,
                                                  int max_shift, float* __restrict__ h_int,
@@ -213,7 +223,7 @@ __global__ __launch_bounds__(NT) void k_xcf_peak(const cf* __restrict__ spec_p, 
   const int64_t k = blockIdx.x;
   load_roots<N, NT>(tw, tid);
   __syncthreads();
-  ArgmaxEpi epi{-INFINITY, 0x7fffffff, N, max_shift, map ? map + k * N * N : nullptr};
+  ArgmaxEpi<MAP, WINDOW> epi{-INFINITY, 0x7fffffff, N, max_shift, map ? map + k * N * N : nullptr};
   const int64_t ip = pi ? pi[k] : k, il = li ? li[k] : k;
   xcf_core<N, NT>(spec_p + ip * L::SPEC, spec_l + il * L::SPEC, lds, tw, tid, epi);
   float m = epi.m;
@@ -1316,8 +1326,11 @@ int band_of(int n) {
 bool size_supported(int n) { return band_of(n) > 0; }
 bool fft_supported(int n) { return n == 64 || n == 96 || n == 128 || n == 160; }
 
+// 128: one pair 12.6 us (256 threads: 15.3).  160, whose 106 KB of LDS leave one block per CU: 8,100 pairs 732 us with
+// 512 threads and a branch per value, 639 with selects, 524 with 1,024 threads; 128 269 -> 231 us with selects
+// (each with the entry point's 80 us)
 template <int N>
-static constexpr int nt_xcf() { return N <= 64 ? 256 : 512; }  // 128: one pair 12.6 us (256 threads: 15.3)
+static constexpr int nt_xcf() { return N <= 64 ? 256 : N == 160 ? 1024 : 512; }
 template <int N>
 static constexpr int nt_spec() { return N <= 96 ? 256 : 512; }
 
@@ -1613,7 +1626,7 @@ hipError_t launch_xcf_peak(int n, const float2* spec_p, const float2* spec_l,
                            const int32_t* pi, const int32_t* li, int64_t k, int max_shift,
                            float* h_int, int32_t* s_int, float* map, hipStream_t stream) {
   if (k <= 0) return hipSuccess;
-  const int64_t kmax = kMaxItems / 512;
+  const int64_t kmax = kMaxItems / 1024;
   if (k > kmax) {
     const int64_t sc = (int64_t)(band_of(n) + 1) * (2 * band_of(n) + 1);
     for (int64_t s = 0; s < k; s += kmax) {
@@ -1628,8 +1641,13 @@ hipError_t launch_xcf_peak(int n, const float2* spec_p, const float2* spec_l,
   }
   EBSD_DISPATCH(n, {
     constexpr int NT = nt_xcf<NN>();
-    hipLaunchKernelGGL((k_xcf_peak<NN, NT>), dim3((unsigned)k), dim3(NT), 0, stream, (const cf*)spec_p,
-                       (const cf*)spec_l, pi, li, max_shift, h_int, s_int, map);
+    const auto run = [&](auto kernel) {
+      hipLaunchKernelGGL(kernel, dim3((unsigned)k), dim3(NT), 0, stream, (const cf*)spec_p, (const cf*)spec_l, pi, li,
+                         max_shift, h_int, s_int, map);
+    };
+    if (map) run(k_xcf_peak<NN, NT, true, true>);
+    else if (max_shift >= 0) run(k_xcf_peak<NN, NT, false, true>);
+    else run(k_xcf_peak<NN, NT, false, false>);
   });
   return hipGetLastError();
 }
