@@ -258,10 +258,10 @@ int ebsd_pc_map(const ebsd_pc_model* model, int64_t P, double* pc_out, void* str
  * cannot allocate (code under HIP graph capture, tight serving loops,
  * harnesses that forbid hipMalloc).  Same arguments, kernels and results as
  * ebsd_refine_orientations (bit for bit); its scratch is one static device
- * array of 256 MiB per GPU, held from the library's first use on that GPU
- * until the process ends.  A batch needs per pattern
+ * array of 256 MiB and 64 KiB per GPU, held from the library's first use on
+ * that GPU until the process ends.  A batch needs per pattern
  * 4 n^2 + 16 (2B+1)(B+1) + 8 n_rho n_eta + 32 bytes (B = 3n/8), at n = 256
- * another 198,768 bytes of transform scratch, plus tables of a few KB and
+ * another 198,664 bytes of transform scratch, plus tables of up to 0.9 MB and
  * 256-byte alignment of each buffer: at the default parameters at most
  * about 980 patterns of 128 x 128, or 200 of 256 x 256, per call.
  * Larger batches return EBSD_E_INVALID (the message states the bytes needed)

@@ -708,7 +708,9 @@ int ebsd_plan_destroy(ebsd_plan plan) {
 // which each GPU the library runs on holds until the process ends.  In host
 // code its name is not a device address; the address of each device's copy
 // comes from hipGetSymbolAddress on the first call on that device.
-constexpr size_t kNoAllocBytes = size_t(256) << 20;
+// 256 MiB for the patterns' buffers, and room for the sub-pixel tables' constants of the coarse grid (16 KB at
+// 128, 30 KB at 256), which without it took one pattern of the largest batch at 96 (1,744 at the defaults).
+constexpr size_t kNoAllocBytes = (size_t(256) << 20) + (size_t(64) << 10);
 static __device__ __align__(256) unsigned char scratch[kNoAllocBytes];
 
 namespace {
