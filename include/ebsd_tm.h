@@ -72,7 +72,8 @@ extern "C" {
  *   FP32    FP32 FFT form (every cyclic shift, or a window), or the exact
  *           FP32 DFT form over a window
  *   FP16X2  DFT-GEMMs on MFMA, operands split into FP16 hi + lo halves,
- *           products hi*hi + hi*lo + lo*hi accumulated in FP32
+ *           products hi*hi + hi*lo + lo*hi accumulated in FP32 (spectra of
+ *           the caller's own: up to a product of 60 of the two norms)
  *   BF16X2  the same with BF16 halves
  *   BF16    BF16 operands, one product (reported, not parity-bound)
  * The winner's integer peak, sub-pixel peak and the refinement always run

@@ -16,9 +16,10 @@
 // Z, A and D are formed in FP32 on the vector ALU.  The products take one of two forms (SPLIT):
 //  - FP32 operands on v_mfma_f32_16x16x4_f32 (exact products, FP32 sums);
 //  - every operand split into two FP16 halves x = hi + lo, both rounded to nearest even, the
-//    product formed as hi*hi + hi*lo + lo*hi with FP32 sums.  E is scaled by 2^12 first (exact),
-//    so that the lo halves of typical band values are normal FP16 numbers; unit-energy spectra
-//    keep |A|, |C|, |S| below 2^13.
+//    product formed as hi*hi + hi*lo + lo*hi with FP32 sums.  E is scaled by 2^10 first (exact),
+//    so that the lo halves of typical band values are normal FP16 numbers; |A|, |C|, |S| are at most
+//    2^10 |E| |T|, below the FP16 maximum up to a product of 63 of the spectra's norms (2^12: 15).
+//    The largest error of unit-energy spectra is the same with either factor.
 //
 // One wave owns one pair at a time.  Stage 1 runs transposed: A operand = the formed values (row
 // v = lane % 16, this lane's eight rows u = 32 kc + 8 (lane / 16) + j), B operand = the phase
@@ -41,8 +42,8 @@ typedef unsigned u4v __attribute__((ext_vector_type(4)));
 typedef unsigned u2v __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
 
-constexpr float kScale = 4096.0f;
-constexpr float kUnscale = 1.0f / 4096.0f;
+constexpr float kScale = 1024.0f;
+constexpr float kUnscale = 1.0f / 1024.0f;
 
 constexpr int kRing = 4 * 8 * 64 * 16;  // bytes of LDS per pattern of a block
 
