@@ -1090,6 +1090,9 @@ __global__ __launch_bounds__(NT) void k_spectra(const T* __restrict__ imgs, int6
   using L = Lay<N>;
   constexpr int R1 = L::R1, R2 = L::R2, B = L::B, NV = L::NV, NK = L::NK;
   constexpr int IS = N + R2;                                   // row stride of the image in LDS
+  // a piece in LDS: odd rows at 160 (170 values apart) start 8 bytes off a multiple of 16
+  typedef float im4 __attribute__((ext_vector_type(4), aligned(8)));
+  static_assert(IS * sizeof(float) % alignof(im4) == 0, "rows of the image keep the pieces aligned");
   constexpr int PX = N * N / 4, PT = (PX + NT - 1) / NT;       // 16-byte pieces, per thread
   __shared__ __align__(16) cf lds[L::cmax(L::LDS, N * IS / 2)];
   __shared__ cf tw[N];
@@ -1115,8 +1118,8 @@ __global__ __launch_bounds__(NT) void k_spectra(const T* __restrict__ imgs, int6
     const int t = tid + NT * j;
     if (PX % NT == 0 || t < PX) {
       const int row = 4 * t / N, col = 4 * t - row * N;
-      *reinterpret_cast<float4*>(im + row * IS + col) =
-          make_float4(ld_px(px[j].v[0]), ld_px(px[j].v[1]), ld_px(px[j].v[2]), ld_px(px[j].v[3]));
+      *reinterpret_cast<im4*>(im + row * IS + col) =
+          im4{ld_px(px[j].v[0]), ld_px(px[j].v[1]), ld_px(px[j].v[2]), ld_px(px[j].v[3])};
     }
   }
   __syncthreads();
