@@ -141,9 +141,14 @@ hipError_t launch_xcf_peak(int n, const float2* spec_p, const float2* spec_l,
                            const int32_t* pi, const int32_t* li, int64_t k, int max_shift,
                            float* h_int, int32_t* s_int, float* map, hipStream_t stream);
 
-// Phase tables of a local grid of shifts (k_grid_peak.hip), in complex elements.
+// Phase tables of a local grid of shifts (k_grid_peak.hip), in complex elements, the
+// LDS of one block, and the peak over every point of the grid (centre null: 0;
+// int_keys: ties by the cyclic shift index; s or si may be null).
 int grid_table_size(int n, int kappa, int m);
 size_t grid_lds_bytes(int n, int m);
+hipError_t launch_grid(int n, const float2* spec_p, const float2* spec_l, const int32_t* pi, const int32_t* li,
+                       int64_t k, const int32_t* centre, int kappa, int m, int int_keys, const float2* tab, float* h,
+                       float* s, int32_t* si, hipStream_t stream);
 
 // Phase tables of the upsampled peak for (n, kappa): size in complex
 // elements, their construction, and the LDS that bounds the accepted kappa.

@@ -236,8 +236,7 @@ static hipError_t grid_vj(int n, int bnd, const float2* spec_p, const float2* sp
                        (const cf*)tab, h, s, si, k0, lib_l);                                                        \
   } while (0)
   // rows per thread rounded up as little as possible: every extra row is a
-  // full set of FMAs on zeros (the sub-pixel grid, 151 rows at kappa = 100,
-  // takes 5 on 32 x 32 threads)
+  // full set of FMAs on zeros
   if (mb <= 1) EBSD_GRID(1);
   else if (mb <= 2) EBSD_GRID(2);
   else if (mb <= 3) EBSD_GRID(3);
@@ -256,9 +255,9 @@ static hipError_t grid_vj(int n, int bnd, const float2* spec_p, const float2* sp
   return hipGetLastError();
 }
 
-static hipError_t launch_grid(int n, const float2* spec_p, const float2* spec_l, const int32_t* pi,
-                              const int32_t* li, int64_t k, const int32_t* centre, int kappa, int m, int int_keys,
-                              const float2* tab, float* h, float* s, int32_t* si, hipStream_t stream) {
+hipError_t launch_grid(int n, const float2* spec_p, const float2* spec_l, const int32_t* pi, const int32_t* li,
+                       int64_t k, const int32_t* centre, int kappa, int m, int int_keys, const float2* tab, float* h,
+                       float* s, int32_t* si, hipStream_t stream) {
   if (k <= 0) return hipSuccess;
   const int bnd = band_of(n);
   if (bnd < 0 || grid_lds_bytes(n, m) > 160 * 1024) return hipErrorInvalidValue;

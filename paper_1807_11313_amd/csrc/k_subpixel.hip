@@ -321,7 +321,20 @@ int subpixel_table_size(int n, int kappa) {
   return sub_offset(n, kappa) + more;
 }
 
-// The full grid's evaluation in LDS, which still bounds the accepted upsampling factors
+// Small grids of many pairs cost less in full (k_grid_peak.hip, the same values and winners), whose small blocks
+// share a CU: 5,000 pairs, full / bounded, at kappa = 4 (7 x 7 points) 65 / 145 us at 64, 92 / 200 at 96, 139 / 266
+// at 128, 175 / 308 at 160, 1,500 at 256 146 / 338; at kappa = 20 (31 x 31) 90 / 147, 130 / 202, 197 / 270, 282 /
+// 314, 261 / 343; at 30 (47 x 47) 118 / 149, 179 / 202, 280 / 270, 389 / 314, 424 / 378.  Few pairs leave the
+// bounded form's blocks (512 at a time, 256 at 256) no second round: 512 pairs at 128 cost it 39 us up to kappa =
+// 40, in full 38 at 4 and 46 at 20; 600 pairs 53, and 39 at 4; 512 pairs at 256 120 us at 20, 164 at 40, in full 112
+// and 153.
+static bool full_grid_pays(int n, int m, int64_t k) {
+  const int rows = 2 * m + 1;
+  if (n == 256) return k > 256 && rows <= (k <= 512 ? 64 : 40);
+  return k > 512 && rows <= (k <= 2048 || n == 160 ? 32 : n == 128 ? 40 : 48);
+}
+
+// The full grid's evaluation in LDS, which bounds the accepted upsampling factors
 size_t subpixel_lds_bytes(int n, int kappa) { return grid_lds_bytes(n, sub_m(kappa)); }
 
 hipError_t launch_subpixel_tables(int n, int kappa, float2* tab, hipStream_t stream) {
@@ -345,6 +358,8 @@ hipError_t launch_subpixel(int n, const float2* spec_p, const float2* spec_l, co
   if (k <= 0) return hipSuccess;
   const int bnd = band_of(n), m = sub_m(kappa);
   if (bnd < 0 || subpixel_lds_bytes(n, kappa) > 160 * 1024) return hipErrorInvalidValue;
+  if (full_grid_pays(n, m, k))
+    return launch_grid(n, spec_p, spec_l, pi, li, k, s_int, kappa, m, 0, tab, h_sub, s_sub, nullptr, stream);
   const int64_t sc = (int64_t)(bnd + 1) * (2 * bnd + 1);
   const int64_t kmax = (int64_t(1) << 31) / 512;  // blocks x threads of one dispatch below 2^31
   const float* coarse = reinterpret_cast<const float*>(tab + sub_offset(n, kappa));
