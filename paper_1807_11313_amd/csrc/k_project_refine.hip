@@ -28,7 +28,9 @@ __device__ __forceinline__ void keys4(float t, float* w) {
   w[3] = -0.5f * (s + __fmaf_rn(-2.0f, s2, s3));
 }
 
-// A block projects a 32 x 32 px tile of one template, four pixels per thread.
+// A block projects a 32 x 32 px tile of one template, four pixels per thread, or, at sizes that are not a
+// multiple of 32 (TILED false), 256 or 1,024 pixels counted along strips of 8 rows, column by column: its waves'
+// pixels are 8 x 8 as well, and none lie outside the image, as 47 of 64 did in the tiles of 33 x 33.
 // Bound by the vector ALU (two arctangents, a square root and the cubic
 // weights per pixel) once the gathers are cheap:
 //  - a wave's 64 pixels are 8 x 8, which is also compact in the master: its
@@ -44,8 +46,8 @@ __device__ __forceinline__ void keys4(float t, float* w) {
 // About 190 VALU instructions per pixel are left, 0.40 ms at full issue.
 // WIDE: the row loads, where a byte offset into the master fits 32 bits; a
 // master of 4 GB or more takes every tap by its own 64-bit address.
-// With gridDim.z = 4 a block takes one of the four pixels only.
-template <bool WIDE>
+// With gridDim.z = 4, or `tiles` 0 where not TILED, a block takes one of the four pixels only.
+template <bool WIDE, bool TILED>
 __global__ __launch_bounds__(256) void k_project(const float* __restrict__ master, int mh, int mw,
                                                  const double* __restrict__ q,
                                                  const double* __restrict__ pc_per, double pcx,
@@ -53,9 +55,13 @@ __global__ __launch_bounds__(256) void k_project(const float* __restrict__ maste
                                                  float* __restrict__ out) {
 #pragma clang fp contract(off)
   const int64_t k = blockIdx.y;
-  const int tile_y = blockIdx.x / tiles, tile_x = blockIdx.x - tile_y * tiles;
-  const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
-  const int i0 = tile_x * 32 + (wave & 1) * 8 + (lane & 7), j0 = tile_y * 32 + (wave >> 1) * 8 + (lane >> 3);
+  int i0 = 0, j0 = 0;
+  if constexpr (TILED) {
+    const int tile_y = blockIdx.x / tiles, tile_x = blockIdx.x - tile_y * tiles;
+    const int lane = threadIdx.x & 63, wave = threadIdx.x >> 6;
+    i0 = tile_x * 32 + (wave & 1) * 8 + (lane & 7);
+    j0 = tile_y * 32 + (wave >> 1) * 8 + (lane >> 3);
+  }
   const double qw = q[4 * k], qx = q[4 * k + 1], qy = q[4 * k + 2], qz = q[4 * k + 3];
   const double yy = qy * qy, zz = qz * qz, wy = qw * qy, wz = qw * qz, yz = qy * qz;
   const float r00 = (float)fma(fma(qy, qy, zz), -2.0, 1.0), r01 = (float)(2 * fma(qx, qy, -wz)),
@@ -77,9 +83,19 @@ __global__ __launch_bounds__(256) void k_project(const float* __restrict__ maste
       const_cast<float*>(master), (short)0, WIDE ? (int)((unsigned)mh * (unsigned)mw * 4u) : 0, 0x00020000);
 #pragma unroll
   for (int sub = 0; sub < 4; ++sub) {
-    if (gridDim.z == 4 && sub != (int)blockIdx.z) continue;
-    const int i = i0 + 16 * (sub & 1), j = j0 + 16 * (sub >> 1);
-    if (i >= n || j >= n) continue;
+    int i, j;
+    if constexpr (TILED) {
+      if (gridDim.z == 4 && sub != (int)blockIdx.z) continue;
+      i = i0 + 16 * (sub & 1);
+      j = j0 + 16 * (sub >> 1);
+    } else {
+      if (!tiles && sub) break;
+      const int t = (int)blockIdx.x * (tiles ? 1024 : 256) + sub * 256 + (int)threadIdx.x;
+      if (t >= n * n) break;
+      const int strip = t / (8 * n), at = t - strip * 8 * n, rows = min(8, n - 8 * strip);
+      i = rows == 8 ? at >> 3 : at / rows;
+      j = 8 * strip + at - i * rows;
+    }
     const float dx = __fmaf_rn(inv_n, (float)i + 0.5f, -(float)pcx);
     const float dy = __fmaf_rn(inv_n, (float)j + 0.5f, -(float)pcy);
     const float rn = rsqrtf(__fmaf_rn(dz, dz, __fmaf_rn(dy, dy, dx * dx)));
@@ -624,14 +640,24 @@ hipError_t launch_project(int n, const float* master, int mh, int mw, const doub
     }
     return hipSuccess;
   }
-  const int tiles = (n + 31) / 32;
+  const bool tiled = n % 32 == 0;
+  int tiles = n / 32;
   // one pixel per thread while four would leave CUs idle: a single template
   // at 128 x 128 takes 4.6 us on 64 blocks, about 7 us on 16; from 1,024 blocks of
-  // four pixels on (16 templates at 256, 64 at 128) the shared set-up wins
-  const bool few = (int64_t)tiles * tiles * k < 1024;
-  const dim3 grid((unsigned)(tiles * tiles), (unsigned)k, few ? 4u : 1u);
+  // four pixels on (16 templates at 256, 64 at 128) the shared set-up wins.  And where much of
+  // the last of those blocks would be empty: 33 x 33 is 1,024 + 65 pixels, 3,000 templates from a master of
+  // 1001 x 2001 in blocks of 1,024 148 us, of 256 95; 40 x 40 (1,024 + 576) 150 and 124
+  const int quads = tiled ? tiles * tiles : (n * n + 1023) / 1024;
+  const bool few = (int64_t)quads * k < 1024 || (int64_t)n * n * 32 <= (int64_t)quads * 1024 * 25;
+  dim3 grid((unsigned)quads, (unsigned)k, few ? 4u : 1u);
+  if (!tiled) {
+    tiles = few ? 0 : 1;
+    grid = dim3((unsigned)(few ? (n * n + 255) / 256 : quads), (unsigned)k);
+  }
   const bool wide = (int64_t)mh * mw < (int64_t(1) << 30);
-  hipLaunchKernelGGL(wide ? k_project<true> : k_project<false>, grid, dim3(256), 0, stream, master, mh, mw, q, pc_per, pcx, pcy, pcz, n, tiles, out);
+  const auto kernel = wide ? (tiled ? k_project<true, true> : k_project<true, false>)
+                           : (tiled ? k_project<false, true> : k_project<false, false>);
+  hipLaunchKernelGGL(kernel, grid, dim3(256), 0, stream, master, mh, mw, q, pc_per, pcx, pcy, pcz, n, tiles, out);
   return hipGetLastError();
 }
 
