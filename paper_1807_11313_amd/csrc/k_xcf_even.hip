@@ -537,6 +537,10 @@ hipError_t run_even(const float2* spec_p, int64_t p, const float2* spec_l, int64
 // Patterns per block: as many as the registers of two waves per SIMD hold.  Split 2 / 3 / 4 patterns: 2.72 /
 // 3.00 / 2.56e8 pairs/s at 128, 0.98 / 1.07 / 0.92e8 at 256 (four spill); FP32 2 / 4 / 5: 1.85 / 1.99 / 1.93e8
 // and 0.66 / 0.72 / 0.68e8.  Two tiles of shifts (16 <= max_shift) take a quarter as many accumulators' patterns: one.
+// One, too, where the blocks of several would leave CUs without one: a block works out all of its patterns' places.
+// FP32, 4 patterns x 200 templates 63 -> 29 us at 128, 63 -> 30 at 160, 176 -> 66 at 256, x 1,000 (125 blocks of
+// four) 64 -> 42, 64 -> 44, 177 -> 113; 16 x 500 (252) 64 -> 68, 64 -> 71, 177 -> 197.  Split, 4 x 200 36 -> 29, 35 ->
+// 30, 61 -> 40, 4 x 1,000 (250 blocks of three) 35 -> 31, 40 -> 41, 71 -> 75.
 template <bool SPLIT, int ST>
 constexpr int even_pb() { return ST == 2 ? 1 : SPLIT ? 3 : 4; }
 template <int N, bool SPLIT, bool DISC>
@@ -544,7 +548,10 @@ hipError_t pick_even(const float2* spec_p, int64_t p, const float2* spec_l, int6
                      unsigned char* frag, float* scores, hipStream_t stream) {
   if (max_shift >= 16)
     return run_even<N, 2, even_pb<SPLIT, 2>(), SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
-  return run_even<N, 1, even_pb<SPLIT, 1>(), SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
+  constexpr int PB = even_pb<SPLIT, 1>();
+  if ((p + PB - 1) / PB * ((l + 7) / 8) <= 192 || p == 1)
+    return run_even<N, 1, 1, SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
+  return run_even<N, 1, PB, SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
 }
 
 template <int N, int ST, bool SPLIT>

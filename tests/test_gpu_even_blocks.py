@@ -1,0 +1,61 @@
+"""Windowed searches (FP16 hi + lo, and FP32 DFT): blocks of several patterns, with remainders, give the bits of blocks
+of one, and a few patterns do not cost what many do."""
+
+import pytest
+
+pytestmark = pytest.mark.gpu
+
+FORMS = {"fp16x2": (2, 1), "fp32": (3, 0)}
+
+
+def _spectra(n, p, l):
+    import torch
+    import paper_1807_11313_amd as tm
+
+    g = torch.Generator(device="cuda:0").manual_seed(n + p)
+    base = torch.randn((64, 1, n // 8, n // 8), generator=g, device="cuda:0")
+    up = torch.nn.functional.interpolate(base, size=(n, n), mode="bicubic")[:, 0].contiguous()
+    sl = tm.pattern_spectra(up + 0.5 * torch.randn(up.shape, generator=g, device="cuda:0"))
+    sp = tm.pattern_spectra(up + 0.5 * torch.randn(up.shape, generator=g, device="cuda:0"))
+    at = torch.arange(max(p, l), device="cuda:0")
+    return tm, sp[at[:p] % 64].contiguous(), sl[at[:l] * 5 % 64].contiguous()
+
+
+@pytest.mark.parametrize("form", sorted(FORMS))
+@pytest.mark.parametrize("n, s", [(64, 0), (64, 15), (96, 7), (128, 15), (160, 3), (256, 15), (64, 16), (96, 31), (128, 16),
+                                  (256, 31)])
+def test_blocks_of_patterns_equal_single_ones(form, n, s):
+    import torch
+
+    f, prec = FORMS[form]
+    for p, l in ((2, 1539), (3, 1545), (5, 1540), (9, 1551)):            # from 193 blocks on, and 8 k, 8 k + 1 ... templates
+        tm, sp, sl = _spectra(n, p, l)
+        prm = tm.params_default(max_shift=s, form=f, precision=prec)
+        out = tm.xcf_scores(sp, sl, n, prm)
+        for i in range(p):
+            assert torch.equal(out[i:i + 1], tm.xcf_scores(sp[i:i + 1].contiguous(), sl, n, prm)), (p, i)
+
+
+@pytest.mark.parametrize("n", [128, 256])
+def test_few_patterns_cost_little(n):
+    import torch
+
+    tm, sp, sl = _spectra(n, 100, 200)
+    prm = tm.params_default(max_shift=7, form=3)
+
+    def cost(p):
+        best = float("inf")
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                tm.xcf_scores(sp[:p], sl, n, prm)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    cost(4)
+    # a block of one pattern against the blocks of four that 100 patterns fill the chip with: measured 29 of 172 us at
+    # 128 and 66 of 511 at 256 (63 and 176 where four patterns take a block of four)
+    assert cost(4) < 0.25 * cost(100)
