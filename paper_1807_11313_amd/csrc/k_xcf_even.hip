@@ -31,13 +31,15 @@
 
 #include <math.h>
 
+#include <type_traits>
+
 namespace ebsd {
 
 namespace {
 
 typedef _Float16 h8 __attribute__((ext_vector_type(8)));
-typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef _Float16 h4 __attribute__((ext_vector_type(4)));
+typedef _Float16 h2 __attribute__((ext_vector_type(2)));
 typedef unsigned u4v __attribute__((ext_vector_type(4)));
 typedef unsigned u2v __attribute__((ext_vector_type(2)));
 typedef float f4 __attribute__((ext_vector_type(4)));
@@ -52,31 +54,32 @@ constexpr int kRing = 4 * 8 * 64 * 16;  // bytes of LDS per pattern of a block
 template <int N, int ST, bool DISC>
 struct EvenLay {
   static constexpr int B = Plan<N>::B, NV = B + 1, NK = 2 * B + 1, SPEC = NV * NK;
-  // rows u in [0, 32 KC) and columns v in [0, 16 VT) run through the products.  Where B is a
-  // multiple of 32 (16) the row u = B (column v = B), which in the disc is non-zero at v = 0 (u = 0)
-  // only, is added to the result in FP32 instead of opening another chunk
-  static constexpr bool UTOP = DISC && B % 32 == 0, VTOP = DISC && B % 16 == 0;
-  static constexpr int KC = UTOP ? B / 32 : B / 32 + 1;
+  // rows u in [0, 32 KC + 16 HALF) and columns v in [0, 16 VT) run through the products.  Where B is a
+  // multiple of 16 the row u = B and the column v = B, which in the disc are non-zero at v = 0 and u = 0
+  // only, are added to the result in FP32 instead of opening another chunk
+  static constexpr bool UTOP = DISC && B % 16 == 0, VTOP = UTOP;
+  static constexpr int ROWS16 = UTOP ? B / 16 : B / 16 + 1;
+  static constexpr int KC = ROWS16 / 2, HALF = ROWS16 % 2, NS = KC + HALF;  // chunks of 32 rows, of 16; both
   static constexpr int VT = VTOP ? B / 16 : B / 16 + 1;
   // constants, the same bytes in both forms: stage 1 [KC][ST][cos, sin] x 2 x 64 lanes x 16 B
-  // (FP16: hi, lo halves of 8 rows; FP32: rows 0-3, 4-7), stage 2 [VT][ST][w cos, w sin] x 1024 B
-  // (FP16: [hi, lo][lane] x 4 halves; FP32: [lane] x 4)
-  static constexpr int W_BYTES = KC * ST * 4096, C_BYTES = VT * ST * 2048;
+  // (FP16: hi, lo halves of 8 rows; FP32: rows 0-3, 4-7), its half chunk [ST][cos, sin] x 1024 B, stage 2
+  // [VT][ST][w cos, w sin] x 1024 B (FP16: [hi, lo][lane] x 4 halves; FP32: [lane] x 4)
+  static constexpr int H_AT = KC * ST * 4096, W_BYTES = H_AT + HALF * ST * 2048, C_BYTES = VT * ST * 2048;
   static constexpr int FRAG_BYTES = W_BYTES + C_BYTES;
 };
 
 template <int N, int ST, bool SPLIT, bool DISC>
 __global__ void k_even_consts(unsigned char* __restrict__ frag) {
   using L = EvenLay<N, ST, DISC>;
-  constexpr int nw = L::W_BYTES / 4;
+  constexpr int nf = L::H_AT / 4, nw = L::W_BYTES / 4;
   const int i = blockIdx.x * 256 + threadIdx.x;  // one constant per thread
   if (i >= nw + L::C_BYTES / 4) return;
-  const bool first = i < nw;
-  const int per = first ? 8 : 4, c = first ? i : i - nw;
+  const bool full = i < nf, first = i < nw;
+  const int per = full ? 8 : 4, at = full ? 0 : (first ? nf : nw), c = i - at;
   const int j = c % per, lane = (c / per) & 63, rest = c / (per * 64);
-  const int part = rest & 1, st = (rest >> 1) % ST, chunk = (rest >> 1) / ST;
+  const int part = rest & 1, st = (rest >> 1) % ST, chunk = full || !first ? (rest >> 1) / ST : L::KC;
   const int s = st * 16 + (lane & 15);
-  const int f = first ? chunk * 32 + 8 * (lane >> 4) + j : chunk * 16 + 4 * (lane >> 4) + j;
+  const int f = chunk * (first ? 32 : 16) + per * (lane >> 4) + j;
   double val = 0.0;
   if (f < (first ? (L::UTOP ? L::B : L::B + 1) : (L::VTOP ? L::B : L::NV))) {
     double sn, cs;
@@ -85,7 +88,7 @@ __global__ void k_even_consts(unsigned char* __restrict__ frag) {
     if (!first && f > 0) val *= 2.0;
   }
   const float x = (float)val;
-  unsigned char* base = frag + (first ? 0 : L::W_BYTES) + rest * per * 256;
+  unsigned char* base = frag + at * 4 + rest * per * 256;
   if constexpr (SPLIT) {
     const _Float16 h = (_Float16)x, l = (_Float16)(x - (float)h);
     _Float16* o = reinterpret_cast<_Float16*>(base) + lane * per + j;
@@ -99,8 +102,10 @@ __global__ void k_even_consts(unsigned char* __restrict__ frag) {
 // Four pairs of floats split into packed FP16 halves: hi[i] = (x[2i], x[2i + 1]) rounded, lo[i] =
 // the exact remainders (one mixed-precision FMA each) rounded: four full-rate instructions a pair.
 // The empty asm keeps the compiler from folding the conversion into the FMA that made x, as a
-// mixed FMA that writes one FP16 half: those run at half rate.  The conversions themselves are left
-// to the compiler, which knows the wait between them and a matrix instruction.
+// mixed FMA that writes one FP16 half: those run at half rate.  The waits between a matrix instruction
+// and others are the compiler's, who does not look into an asm: each FMA works in place, on a register
+// that the conversion before it has read and that no matrix instruction in flight reads or writes, and the
+// conversions are left to the compiler.
 __device__ __forceinline__ unsigned pack_f16(float a, float b) {
   return __builtin_bit_cast(unsigned, h2{(_Float16)a, (_Float16)b});
 }
@@ -109,18 +114,17 @@ __device__ __forceinline__ void split4(const float* x, unsigned* hi, unsigned* l
   for (int i = 0; i < 4; ++i) {
     float a = x[2 * i], b = x[2 * i + 1];
     asm("" : "+v"(a), "+v"(b));
-    const unsigned h = pack_f16(a, b);
-    float ra, rb;
-    asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel_hi:[1,0,0]" : "=v"(ra) : "v"(h), "v"(a));
-    asm("v_fma_mix_f32 %0, -%1, 1.0, %2 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "=v"(rb) : "v"(h), "v"(b));
-    hi[i] = h;
-    lo[i] = pack_f16(ra, rb);
+    hi[i] = pack_f16(a, b);
+    asm("v_fma_mix_f32 %0, -%1, 1.0, %0 op_sel_hi:[1,0,0]" : "+v"(a) : "v"(hi[i]));
+    asm("v_fma_mix_f32 %0, -%1, 1.0, %0 op_sel:[1,0,0] op_sel_hi:[1,0,0]" : "+v"(b) : "v"(hi[i]));
+    lo[i] = pack_f16(a, b);
   }
 }
 
 __device__ __forceinline__ f4 mfma32(const u4v& a, const u4v& b, const f4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x32_f16(__builtin_bit_cast(h8, a), __builtin_bit_cast(h8, b), c, 0, 0, 0);
 }
+
 __device__ __forceinline__ f4 mfma16(const u2v& a, const u2v& b, const f4& c) {
   return __builtin_amdgcn_mfma_f32_16x16x16f16(__builtin_bit_cast(h4, a), __builtin_bit_cast(h4, b), c, 0, 0, 0);
 }
@@ -143,16 +147,19 @@ __device__ __forceinline__ cf load_cf(__amdgpu_buffer_rsrc_t r, int voff, int so
   return __builtin_bit_cast(cf, __builtin_amdgcn_raw_buffer_load_b64(r, voff, soff, 0));
 }
 
-// Byte offsets of a lane's values of chunk (vt, kc): rows u0 + j, u0 = 32 kc + 8 q, at pos + j * row, rows
-// -(u0 + j) at neg + (7 - j) * row.  The row of u = -0 lies past the end of the spectrum (a buffer load
+// Byte offsets of a lane's values of chunk (vt, kc): rows u0 + j, u0 = 32 kc + 8 q (32 KC + 4 q of the half
+// chunk, whose j >= 4 are not used), at pos + j * row, rows -(u0 + j) at neg + (7 - j) * row.  The row of u = -0 lies past the end of the spectrum (a buffer load
 // there returns zero); rows above B hold other values of the spectrum and meet zero constants, as do
 // the columns past the last one, which read the last.
-template <int N>
-__device__ __forceinline__ void chunk_offsets(int vt, int kc, int r16, int q4, int* pos, int* neg) {
-  constexpr int B = Plan<N>::B, NV = B + 1, NK = 2 * B + 1;
-  const int v = min(vt * 16 + r16, NV - 1), u0 = kc * 32 + 8 * q4;
-  *pos = (u0 * NV + v) * (int)sizeof(cf);
-  *neg = ((NK - u0 - 7) * NV + v) * (int)sizeof(cf);
+// rows8: 8 q rows in bytes; everything else of the rows is uniform.
+template <class L>
+__device__ __forceinline__ void chunk_offsets(int step, int r16, int rows8, int* pos, int* neg) {
+  constexpr int ROW = L::NV * (int)sizeof(cf);
+  const int vt = step / L::NS, kc = step - vt * L::NS;
+  const int v = min(vt * 16 + r16, L::NV - 1) * (int)sizeof(cf);
+  const int u0 = kc * 32 * ROW + (L::HALF && kc == L::KC ? rows8 / 2 : rows8);
+  *pos = u0 + v;
+  *neg = (L::NK - 7) * ROW - u0 + v;
 }
 
 // A block of 8 waves correlates PB patterns with 8 templates, one per wave.  The patterns' values of each
@@ -162,9 +169,10 @@ __device__ __forceinline__ void chunk_offsets(int vt, int kc, int r16, int q4, i
 // Bound by issue: vector and matrix instructions of the waves on one SIMD hardly overlap here (128 FMAs
 // and 32 of the 16-cycle products take 1,886 cycles a pair of waves, 2,155 one after the other), so the cost of a
 // step is their sum: 80 VALU instructions to form A and D, 64 to split them, 12 products (split), or 80 and 32
-// products of 32 cycles (FP32), 73 % of the SIMD cycles busy.  Measured, max_shift 15, 2,000 x 2,000 pairs at 128 and
-// 600 x 2,000 at 256: split 3.0e8 / 1.07e8 pairs/s (complex products over every u and s: 2.4e8 / 0.65e8), FP32
-// 1.99e8 / 0.72e8 (one block per pair on the vector ALU: 0.31e8 / 0.09e8).
+// products of 32 cycles (FP32).  The half chunk of 16 rows takes half of the vector instructions: 1,200 x 1,500 split
+// pairs (whole calls) at 96 6.07 -> 5.27 ms, at 128 6.11 -> 5.37, at max_shift 31 12.7 -> 11.0 and 12.9 -> 10.9.
+// Measured, max_shift 15, 1,200 x 1,500 pairs at 128 and 500 x 1,500 at 256: split 3.4e8 / 1.16e8 pairs/s (complex
+// products over every u and s: 2.5e8 / 0.84e8).
 // Super-tiles of TS template blocks: consecutive blocks (running at one time on an XCD) cycle through
 // the TS template blocks of one pattern block, so both stay in that XCD's L2
 template <int N>
@@ -186,10 +194,10 @@ __device__ __forceinline__ void even_tile(unsigned char* smem, const cf* __restr
                                           const cf* __restrict__ T, bool lok, int max_shift, float* __restrict__ out,
                                           int64_t row) {
   using L = EvenLay<N, ST, DISC>;
-  constexpr int VT = L::VT, KC = L::KC, NV = L::NV, NSTEP = VT * KC, ROW = NV * (int)sizeof(cf);
+  constexpr int VT = L::VT, KC = L::KC, NV = L::NV, NSTEP = VT * L::NS, ROW = NV * (int)sizeof(cf);
   constexpr int NSLOT = 4, AHEAD = 2;
   constexpr float SCALE = SPLIT ? kScale : 1.0f, UNSCALE = SPLIT ? kUnscale : 1.0f;
-  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, q4 = lane >> 4;
+  const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, q4 = lane >> 4, rows8 = 8 * ROW * q4;
   const int wave = __builtin_amdgcn_readfirstlane(tid >> 6);
   const u4v* wf = reinterpret_cast<const u4v*>(smem);
   const unsigned char* cfr = smem + L::W_BYTES;
@@ -218,7 +226,7 @@ __device__ __forceinline__ void even_tile(unsigned char* smem, const cf* __restr
 #pragma unroll
   for (int step = 0; step < AHEAD; ++step) {
     int pos, neg;
-    chunk_offsets<N>(step / KC, step % KC, r16, q4, &pos, &neg);
+    chunk_offsets<L>(step, r16, rows8, &pos, &neg);
     stage_load(pos, neg);
     if (step == 0) {
 #pragma unroll
@@ -250,30 +258,41 @@ __device__ __forceinline__ void even_tile(unsigned char* smem, const cf* __restr
       for (int s = 0; s < ST; ++s)
 #pragma unroll
         for (int c = 0; c < 4; ++c) acc[pb][s][c] = f4{0.f, 0.f, 0.f, 0.f};
-#pragma unroll 1
-    for (int kc = 0; kc < KC; ++kc) {
-      const int step = vt * KC + kc, slot = step & (NSLOT - 1);
+    const auto chunk = [&](auto half, int kc) {
+      constexpr bool HF = decltype(half)::value;
+      constexpr int J = HF ? 4 : 8;
+      const int step = vt * L::NS + kc, slot = step & (NSLOT - 1);
       int pos, neg;
       {
-        const int s2 = min(step + AHEAD, NSTEP - 1);
-        chunk_offsets<N>(s2 / KC, s2 % KC, r16, q4, &pos, &neg);
+        chunk_offsets<L>(min(step + AHEAD, NSTEP - 1), r16, rows8, &pos, &neg);
         stage_load(pos, neg);
-        const int s1 = min(step + 1, NSTEP - 1);
-        chunk_offsets<N>(s1 / KC, s1 % KC, r16, q4, &pos, &neg);
+        chunk_offsets<L>(min(step + 1, NSTEP - 1), r16, rows8, &pos, &neg);
       }
-      f4 e[8];
+      if constexpr (HF) {  // the full chunk that follows
 #pragma unroll
-      for (int j = 0; j < 8; ++j) e[j] = ring[((slot * PB) * 8 + j) * 64 + lane];
+        for (int j = J; j < 8; ++j) {
+          tp[j] = load_cf(tr, pos, j * ROW);
+          tn[j] = load_cf(tr, neg, (7 - j) * ROW);
+        }
+      }
+      f4 e[J];
+#pragma unroll
+      for (int j = 0; j < J; ++j) e[j] = ring[((slot * PB) * 8 + j) * 64 + lane];
       u4v w[ST][4];  // [cos, cos, sin, sin]: hi, lo halves or rows 0-3, 4-7
+      u2v w2[ST][4];  // the half chunk's halves
 #pragma unroll
       for (int s = 0; s < ST; ++s)
 #pragma unroll
-        for (int c = 0; c < 4; ++c) w[s][c] = wf[((kc * ST + s) * 4 + c) * 64 + lane];
+        for (int c = 0; c < 4; ++c) {
+          if constexpr (!HF) w[s][c] = wf[((kc * ST + s) * 4 + c) * 64 + lane];
+          else if constexpr (SPLIT) w2[s][c] = reinterpret_cast<const u2v*>(smem + L::H_AT)[(s * 4 + c) * 64 + lane];
+          else if (!(c & 1)) w[s][c] = reinterpret_cast<const u4v*>(smem + L::H_AT)[(s * 2 + c / 2) * 64 + lane];
+        }
 #pragma unroll
       for (int pb = 0; pb < PB; ++pb) {
         u4v zh[4], zl[4];  // A re, A im, D re, D im
 #pragma unroll
-        for (int j = 0; j < 8; j += 2) {
+        for (int j = 0; j < J; j += 2) {
           float x[8];
 #pragma unroll
           for (int h = 0; h < 2; ++h) {
@@ -288,7 +307,7 @@ __device__ __forceinline__ void even_tile(unsigned char* smem, const cf* __restr
             x[6 + h] = __fmaf_rn(-2.0f, mi, ai);
             if (pb + 1 < PB) {
               e[j + h] = ring[((slot * PB + pb + 1) * 8 + j + h) * 64 + lane];
-            } else {
+            } else if (HF || KC > 1 || !L::HALF || j < 4) {  // a half chunk follows the only full one
               tp[j + h] = load_cf(tr, pos, (j + h) * ROW);
               tn[j + h] = load_cf(tr, neg, (7 - j - h) * ROW);
             }
@@ -314,20 +333,29 @@ __device__ __forceinline__ void even_tile(unsigned char* smem, const cf* __restr
           }
         }
         if constexpr (SPLIT) {
+          // (16-deep products one or two instructions after 32-deep ones into the same accumulators gave wrong
+          // sums in a trial; between those of two chunks lie the vector instructions of a chunk)
+          const auto product = [&](const u4v& z, int s, int k, const f4& a) {
+            if constexpr (HF) return mfma16(u2v{z[0], z[1]}, w2[s][k], a);
+            else return mfma32(z, w[s][k], a);
+          };
 #pragma unroll
           for (int s = 0; s < ST; ++s) {
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[pb][s][c] = mfma32(zh[c], w[s][c & 2], acc[pb][s][c]);
+            for (int c = 0; c < 4; ++c) acc[pb][s][c] = product(zh[c], s, c & 2, acc[pb][s][c]);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[pb][s][c] = mfma32(zh[c], w[s][(c & 2) + 1], acc[pb][s][c]);
+            for (int c = 0; c < 4; ++c) acc[pb][s][c] = product(zh[c], s, (c & 2) + 1, acc[pb][s][c]);
 #pragma unroll
-            for (int c = 0; c < 4; ++c) acc[pb][s][c] = mfma32(zl[c], w[s][c & 2], acc[pb][s][c]);
+            for (int c = 0; c < 4; ++c) acc[pb][s][c] = product(zl[c], s, c & 2, acc[pb][s][c]);
           }
         }
       }
       stage_store((step + AHEAD) & (NSLOT - 1));
       if (step & 1) __syncthreads();
-    }
+    };
+#pragma unroll 1
+    for (int kc = 0; kc < KC; ++kc) chunk(std::false_type{}, kc);
+    if constexpr (L::HALF) chunk(std::true_type{}, KC);
     // stage 2: P1 += cos C re, P2 += cos S im, Q1 += sin C im, Q2 += sin S re
     constexpr int src[4] = {0, 3, 1, 2};  // C re, S im, C im, S re
     if constexpr (SPLIT) {
@@ -540,7 +568,8 @@ hipError_t run_even(const float2* spec_p, int64_t p, const float2* spec_l, int64
 // One, too, where the blocks of several would leave CUs without one: a block works out all of its patterns' places.
 // FP32, 4 patterns x 200 templates 63 -> 29 us at 128, 63 -> 30 at 160, 176 -> 66 at 256, x 1,000 (125 blocks of
 // four) 64 -> 42, 64 -> 44, 177 -> 113; 16 x 500 (252) 64 -> 68, 64 -> 71, 177 -> 197.  Split, 4 x 200 36 -> 29, 35 ->
-// 30, 61 -> 40, 4 x 1,000 (250 blocks of three) 35 -> 31, 40 -> 41, 71 -> 75.
+// 30, 61 -> 40, 4 x 1,000 (250 blocks of three) 35 -> 31, 40 -> 41, 71 -> 75, 16 x 500 (378) 52 -> 46, 65 -> 60, 114
+// -> 129, 40 x 500 (882) 94 -> 96, 120 -> 126, 225 -> 305.
 template <bool SPLIT, int ST>
 constexpr int even_pb() { return ST == 2 ? 1 : SPLIT ? 3 : 4; }
 template <int N, bool SPLIT, bool DISC>
@@ -549,7 +578,7 @@ hipError_t pick_even(const float2* spec_p, int64_t p, const float2* spec_l, int6
   if (max_shift >= 16)
     return run_even<N, 2, even_pb<SPLIT, 2>(), SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
   constexpr int PB = even_pb<SPLIT, 1>();
-  if ((p + PB - 1) / PB * ((l + 7) / 8) <= 192 || p == 1)
+  if ((p + PB - 1) / PB * ((l + 7) / 8) <= (SPLIT && N < 256 ? 512 : 192) || p == 1)
     return run_even<N, 1, 1, SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
   return run_even<N, 1, PB, SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
 }

@@ -28,7 +28,8 @@ def test_blocks_of_patterns_equal_single_ones(form, n, s):
     import torch
 
     f, prec = FORMS[form]
-    for p, l in ((2, 1539), (3, 1545), (5, 1540), (9, 1551)):            # from 193 blocks on, and 8 k, 8 k + 1 ... templates
+    # blocks of four from 193 on, of three from 513 on (193 at 256), with remainders on both sides
+    for p, l in ((2, 1539), (3, 1545), (5, 1540), (2, 4101), (5, 2060), (9, 1551)):
         tm, sp, sl = _spectra(n, p, l)
         prm = tm.params_default(max_shift=s, form=f, precision=prec)
         out = tm.xcf_scores(sp, sl, n, prm)
@@ -59,3 +60,29 @@ def test_few_patterns_cost_little(n):
     # a block of one pattern against the blocks of four that 100 patterns fill the chip with: measured 29 of 172 us at
     # 128 and 66 of 511 at 256 (63 and 176 where four patterns take a block of four)
     assert cost(4) < 0.25 * cost(100)
+
+
+@pytest.mark.parametrize("n", [96, 128])
+def test_small_windows_cost_what_the_bf16_halves_do(n):
+    import torch
+
+    tm, sp, sl = _spectra(n, 600, 1500)
+
+    def cost(precision):
+        best = float("inf")
+        prm = tm.params_default(max_shift=7, form=2, precision=precision)
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(3):
+                tm.xcf_scores(sp, sl, n, prm)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    cost(2)
+    fp16, bf16 = cost(1), cost(2)
+    print("[gpu]   n=%d: fp16x2 %.3f ms, bf16x2 %.3f ms" % (n, fp16 / 3, bf16 / 3), flush=True)
+    # the same products on whole operands: measured 0.94 and 0.96 (1.08 and 1.10 with chunks of 32 rows only)
+    assert fp16 < 1.03 * bf16
