@@ -308,7 +308,8 @@ int pruned_best(int n, const ebsd_params& p, const float2* spec_p, int64_t P, co
   EBSD_ALLOC(items, int2, slab * list_chunks(L), ws);
   EBSD_ALLOC(queue, int, 8, ws);
   EBSD_ALLOC(rows, int32_t, slab, ws);
-  PruneScratch t{scores, cand, count, h0, items, queue, rows, nullptr};
+  EBSD_ALLOC(filled, unsigned long long, slab, ws);
+  PruneScratch t{scores, cand, count, h0, items, queue, rows, filled, nullptr};
   if (p.form != EBSD_FORM_FFT) {
     EBSD_ALLOC(frag, unsigned char, even_frag_bytes(n, p.max_shift), ws);
     t.frag = frag;

@@ -530,7 +530,7 @@ int ebsd_index_proposed(const ebsd_batch* pats, const ebsd_master* mp, const ebs
         const PruneScratch pr{sc_f, (int32_t*)get(sizeof(int32_t) * (size_t)slab * L),
                               (int32_t*)get(sizeof(int32_t) * slab), h_f,
                               (int2*)get(sizeof(int2) * (size_t)slab * list_chunks(L)), (int*)get(sizeof(int) * 8),
-                              (int32_t*)get(sizeof(int32_t) * slab), nullptr};
+                              (int32_t*)get(sizeof(int32_t) * slab), (unsigned long long*)get(sizeof(int64_t) * slab), nullptr};
         if (short_of) return fail(EBSD_E_NOMEM, "fallback scratch allocation failed");
         for (int64_t s = 0; s < nf; s += slab) {
           const int64_t b = std::min<int64_t>(slab, nf - s);

@@ -90,8 +90,8 @@ hipError_t launch_xcf_scores_rows64(const float2* spec_p, int64_t most, const in
 // Best template of every pattern without the score matrix (k_prune.hip), by one
 // of the searches below: the scores that decide are that search's own.  low and
 // stat of both sides come from launch_low_spectra (low_spec_complex() values and
-// one float2 per spectrum).  PruneScratch: scores and cand [p][l], count and h0
-// [p], items [p][list_chunks(l)], queue [8], rows [p], frag for the even forms.
+// one float2 per spectrum).  PruneScratch: scores and cand [p][l], count, h0, rows
+// and fill [p], items [p][list_chunks(l)], queue [8], frag for the even forms.
 enum class PruneBy { None, Fft, EvenFp32, EvenSplit };
 struct PruneScratch {
   float* scores;
@@ -101,6 +101,7 @@ struct PruneScratch {
   int2* items;
   int* queue;
   int32_t* rows;
+  unsigned long long* fill;
   void* frag;
 };
 // Whether lists of that search exist at size n

@@ -291,6 +291,7 @@ int plan_layout(ebsd_ragged_plan_s* pl, Arena& a) {
       c.pr.items = a.take<int2>((size_t)(c.slab * list_chunks(L)));
       c.pr.queue = a.take<int>(8);
       c.pr.rows = a.take<int32_t>((size_t)c.slab);
+      c.pr.fill = a.take<unsigned long long>((size_t)c.slab);
     }
     img_floats = std::max(img_floats, (size_t)(L * c.n * c.n));
     if (pl->flags & EBSD_RAGGED_STENCIL) {

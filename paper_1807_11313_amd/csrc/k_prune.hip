@@ -14,10 +14,11 @@
 // template whose bound lies below h0 is out (99 % of a 4,000-template library for patterns that match it,
 // SNR 5), and of the rest those whose bound from a grid of half the step does.  What remains gets its
 // full score from the search kernel itself, so the pick is that of the whole score matrix, bit for bit,
-// ties included.  Patterns that match nothing keep most of their templates; then the coarse values and the
-// lists come on top of the full search: 200 patterns of noise against 3,000 templates 4.25 -> 4.76 ms at 96,
-// 6.62 -> 6.84 at 128, 14.4 -> 14.8 at 160, where 200 patterns of the library's material take 4.25 -> 0.26,
-// 6.63 -> 0.30 and 14.4 -> 0.36 ms (whole calls).
+// ties included.  What patterns that match less well keep depends on their size.  Whole calls of 200 patterns
+// against 4,000 templates of 15 bands, every pair / matching / another crystal's / noise, in ms: 64 2.06 / 0.26 /
+// 0.29 / 0.62, 96 5.48 / 0.25 / 0.32 / 2.38, 128 8.81 / 0.28 / 0.38 / 8.91, 160 18.9 / 0.30 / 0.54 / 19.8; windows
+// of +-15 px, split: 128 2.50 / 0.29 / 0.56 / 2.66, 256 7.78 / 0.59 / 2.97 / 8.22.  Against fewer templates or
+// patterns noise costs up to a quarter more than every pair (11 x 6,000 at 160, split, 465 -> 589 us; prune_pays).
 #include "ebsd_common.hpp"
 #include "ebsd_internal.hpp"
 
@@ -126,7 +127,7 @@ template <bool ALL>
 __global__ __launch_bounds__(512, 4) void k_coarse(const h8* __restrict__ low_p, int64_t np,
                                                    const h8* __restrict__ low_l, int64_t nl, int64_t npt,
                                                    int64_t nblk, int tc, int last, float* __restrict__ coarse,
-                                                   int* __restrict__ queue) {
+                                                   int* __restrict__ queue, unsigned long long* __restrict__ fill) {
   __shared__ h8 ep[PT * FRAG];
   __shared__ float out[8 * TC * PT];
   const int tid = threadIdx.x, lane = tid & 63, r16 = lane & 15, q4 = lane >> 4;
@@ -137,6 +138,7 @@ __global__ __launch_bounds__(512, 4) void k_coarse(const h8* __restrict__ low_p,
   if (g >= nblk) return;
   const int64_t chunk = g / npt, p0 = (g - chunk * npt) * PT, l0 = chunk * (8 * tc);
   const int pc = (int)(np - p0 < PT ? np - p0 : PT);
+  if (chunk == 0 && tid < pc) fill[p0 + tid] = 0;
   for (int i = tid; i < pc * FRAG; i += 512) ep[i] = low_p[p0 * FRAG + i];
   // stage 1: cos, +-sin of 2 pi u (j + 1/2) / G for this lane's column j = r16 and rows u = 4 q4 + i; stage 2: the
   // same with v in the place of u and the Hermitian weight
@@ -214,6 +216,19 @@ __global__ __launch_bounds__(256) void k_one_each(int64_t p, int32_t* __restrict
   items[i] = make_int2((int)i, 0);
 }
 
+// cos, sin of pi k / (2 G) in FP16, k in [0, 4 G): the half-step grid's phases from a table, worked out per block
+// (eight sincospif a lane) they took longer than the few templates that a block bounds
+struct Phases {
+  _Float16 cs[4 * G][2];
+  constexpr Phases() : cs() {
+    for (int k = 0; k < 4 * G; ++k) {
+      cs[k][0] = (_Float16)(float)cx::cos2pi(k, 4 * G);
+      cs[k][1] = (_Float16)(float)cx::sin2pi(k, 4 * G);
+    }
+  }
+};
+__constant__ Phases c_phases = Phases();
+
 // The largest low value over the 64 x 64 grid of half the step (products as in k_coarse, two tiles per axis), in
 // the wave's last lane; e, x: the low parts of pattern and template
 struct FineConsts {
@@ -224,14 +239,13 @@ struct FineConsts {
     for (int a = 0; a < 2; ++a)
 #pragma unroll
       for (int i = 0; i < 4; ++i) {
-        const int f = 4 * q4 + i;
-        float s, c;
-        sincospif((float)(f * (2 * (16 * a + r16) + 1)) / (float)(2 * G), &s, &c);
-        cp[a][i] = cm[a][i] = (_Float16)c;
-        cp[a][4 + i] = (_Float16)s;
-        cm[a][4 + i] = (_Float16)(-s);
-        c2[a][i] = (_Float16)(f ? 2.0f * c : c);
-        s2[a][i] = (_Float16)(f ? 2.0f * s : s);
+        const int f = 4 * q4 + i, k = (f * (2 * (16 * a + r16) + 1)) & (4 * G - 1);
+        const _Float16 c = c_phases.cs[k][0], s = c_phases.cs[k][1], w = f ? (_Float16)2.0f : (_Float16)1.0f;
+        cp[a][i] = cm[a][i] = c;
+        cp[a][4 + i] = s;
+        cm[a][4 + i] = -s;
+        c2[a][i] = w * c;
+        s2[a][i] = w * s;
       }
   }
 };
@@ -269,71 +283,98 @@ __device__ __forceinline__ float fine_max(const FineConsts& k, h8 ea, h8 eb, h8 
 }
 
 // The templates of each pattern that its bound keeps: cand[p l ..] (any order) and count[p], and their chunks
-// in the queue, of list_chunk(count) entries or, with rows, of kListChunk.  Up to FINE of them are bounded
+// in the queue, of list_chunk(count) entries or, with rows, of kListChunk.  What the first bound keeps is bounded
 // once more from the grid of half the step, with a quarter of the curvature term (0.11 to 0.14 -> 0.03), one
 // wave a template: 5,000 x 4,000 pairs at 128 keep so few that their full scores take 0.76 ms instead of 2.53,
-// 1,500 x 1,859 at 160 0.30 instead of 0.91.  More than FINE are patterns that match nothing.
-// With rows, a pattern that keeps more than a third of the library goes there instead (queue[5] counts them)
-// and its count is -1: a pair of a list costs up to 3 times one of a row in the even forms, whose rows share
-// patterns, and 1.4 times at 64, whose rows share a template load; at 96 to 160 it is 1.05 and a row launch
-// would not pay.
-constexpr int FINE = 1024;
-__global__ __launch_bounds__(512, 4) void k_prune_select(const float* __restrict__ coarse, int64_t l, float h28,
-                                                         const h8* __restrict__ low_p, const h8* __restrict__ low_l,
+// 1,500 x 1,859 at 160 0.30 instead of 0.91.  Of 4,000 templates patterns of another crystal (15 bands, SNR 5)
+// keep 2.8 / 7.7 / 12 / 17 % after the first bound and 0.2 / 0.3 / 0.4 / 0.5 % after the second at 64 / 96 / 128 /
+// 160, and patterns of noise 88 / 100 / 100 / 100 % and 2.7 / 27 / 92 / 100 %, so a block that finds most of its
+// first SAMPLE templates still kept (with rows: too many for a list) leaves the others with the first bound.
+// A block takes `slice` templates of a pattern, so that few patterns fill the chip as well; the last block of a
+// pattern (fill[p]: entries so far, and blocks in the upper half) puts its list in the queue.
+// With rows, a pattern that keeps more than 1 / part of the library goes there instead (queue[5] counts them)
+// and its count is -1: a pair of a list costs 2 to 4 times one of a row in the even forms, whose rows share
+// patterns (200 patterns of noise against 4,000 templates at 96, split, part 4 and 8: 0.89 and 1.40 ms; at 256,
+// part 3, 4, 8: 8.80, 8.56, 8.49, where the second bound gains noise nothing and is left out: 8.05), and 1.4 times
+// at 64, whose rows share a template load; at 96 to 160 it is 1.05 and a row launch would not pay.
+constexpr int SLICE = 4096, SAMPLE = 32;
+__global__ __launch_bounds__(512, 4) void k_prune_select(const float* __restrict__ coarse, int64_t l, int slice, int ns,
+                                                         float h28, const h8* __restrict__ low_p,
+                                                         const h8* __restrict__ low_l,
                                                          const float2* __restrict__ stat_p,
                                                          const float2* __restrict__ stat_l,
                                                          const float* __restrict__ h0, int last,
                                                          int32_t* __restrict__ cand, int32_t* __restrict__ count,
-                                                         int2* __restrict__ items, int* __restrict__ queue,
-                                                         int32_t* __restrict__ rows) {
-  const int64_t p = blockIdx.x;
+                                                         unsigned long long* __restrict__ fill, int2* __restrict__ items,
+                                                         int* __restrict__ queue, int32_t* __restrict__ rows,
+                                                         int part) {
+  const int64_t p = blockIdx.x / ns, i0 = (int64_t)(blockIdx.x - p * ns) * slice;
+  const int len = (int)(l - i0 < slice ? l - i0 : slice);
   const int tid = threadIdx.x, lane = tid & 63;
-  __shared__ int kept, fine;
-  __shared__ int list[FINE];
+  __shared__ int kept, fine, at0, total;
+  __shared__ unsigned short list[SLICE], best[SLICE];
   if (tid == 0) kept = fine = 0;
   __syncthreads();
   const float2 sp = stat_p[p];
   const float eh = 1.0002f * sp.x, kl = 1.0002f * h28 * sp.y, least = h0[p] - kRound;
-  for (int64_t i0 = 0; i0 < l; i0 += 512) {
-    const int64_t i = i0 + tid;
+  for (int j0 = 0; j0 < len; j0 += 512) {
+    const int j = j0 + tid;
     bool keep = false;
-    if (i < l) {
-      const float2 sl = stat_l[i];
-      keep = coarse[p * l + i] + __fmaf_rn(kl, sl.y, eh * sl.x) >= least;
+    if (j < len) {
+      const float2 sl = stat_l[i0 + j];
+      keep = coarse[p * l + i0 + j] + __fmaf_rn(kl, sl.y, eh * sl.x) >= least;
     }
     const unsigned long long mask = __ballot(keep);
     if (mask == 0) continue;
     int at = 0;
     if (lane == 0) at = atomicAdd(&kept, __popcll(mask));
     at = __shfl(at, 0, 64) + __popcll(mask & ((1ull << lane) - 1));
-    if (keep) {
-      cand[p * l + at] = (int32_t)i;
-      if (at < FINE) list[at] = (int)i;
-    }
+    if (keep) list[at] = (unsigned short)j;
   }
   __syncthreads();
   int n = kept;
-  if (rows && n > l / 3) {
+  const unsigned short* out = list;
+  if ((n > 1 || (n == 1 && ns > 1)) && !(rows && part > 4 && 3 * n > len)) {
+    const int r16 = lane & 15, q4 = lane >> 4;
+    FineConsts k;
+    k.init(r16, q4);
+    const h8 ea = low_p[p * FRAG + lane], eb = low_p[p * FRAG + 64 + lane];
+    const auto bound = [&](int from, int to) {
+      for (int j = from + __builtin_amdgcn_readfirstlane(tid >> 6); j < to; j += 8) {
+        const int64_t i = i0 + list[j];
+        const h8 xp = low_l[i * FRAG + lane], xm = low_l[i * FRAG + 64 + lane];
+        const float2 sl = stat_l[i];
+        const float m = fine_max(k, ea, eb, xp, xm, r16, q4, last) * (1.0f / (kScale * kScale));
+        if (lane == 63 && m + __fmaf_rn(0.25f * kl, sl.y, eh * sl.x) >= least) best[atomicAdd(&fine, 1)] = list[j];
+      }
+      __syncthreads();
+    };
+    bound(0, min(n, SAMPLE));
+    if (n <= SAMPLE) {
+      n = fine;
+      out = best;
+    } else if (rows ? part * fine * n <= SAMPLE * len : 4 * fine <= 3 * SAMPLE) {
+      __syncthreads();
+      bound(SAMPLE, n);
+      n = fine;
+      out = best;
+    }
+  }
+  if (tid == 0) {
+    const unsigned long long old = ns > 1 ? atomicAdd(fill + p, (1ull << 32) | (unsigned)n) : 0;
+    at0 = (int)(unsigned)old;
+    total = (int)(old >> 32) == ns - 1 ? at0 + n : -1;
+  }
+  __syncthreads();
+  for (int t = tid; t < n; t += 512) cand[p * l + at0 + t] = (int32_t)(i0 + out[t]);
+  n = total;
+  if (n < 0) return;
+  if (rows && part * n > l) {
     if (tid == 0) {
       count[p] = -1;
       rows[atomicAdd(queue + 5, 1)] = (int)p;
     }
     return;
-  }
-  if (n > 1 && n <= FINE) {
-    const int r16 = lane & 15, q4 = lane >> 4;
-    FineConsts k;
-    k.init(r16, q4);
-    const h8 ea = low_p[p * FRAG + lane], eb = low_p[p * FRAG + 64 + lane];
-    for (int j = __builtin_amdgcn_readfirstlane(tid >> 6); j < n; j += 8) {
-      const int64_t i = list[j];
-      const h8 xp = low_l[i * FRAG + lane], xm = low_l[i * FRAG + 64 + lane];
-      const float2 sl = stat_l[i];
-      const float m = fine_max(k, ea, eb, xp, xm, r16, q4, last) * (1.0f / (kScale * kScale));
-      if (lane == 63 && m + __fmaf_rn(0.25f * kl, sl.y, eh * sl.x) >= least) cand[p * l + atomicAdd(&fine, 1)] = (int)i;
-    }
-    __syncthreads();
-    n = fine;
   }
   const int ch = rows ? kListChunk : list_chunk(n), nc = (n + ch - 1) / ch;
   __shared__ int first;
@@ -484,7 +525,7 @@ bool prune_pays(int n, PruneBy by, int max_shift, int64_t pairs) {
 }
 
 int64_t prune_slab(int64_t p, int64_t l) {
-  return std::max<int64_t>(1, std::min({p, (int64_t(1) << 26) / l, int64_t(1) << 22}));
+  return std::max<int64_t>(1, std::min({p, (int64_t(1) << 26) / l, int64_t(1) << 21}));
 }
 
 int64_t low_spec_complex() { return FRAG * (int)sizeof(h8) / (int)sizeof(float2); }
@@ -523,7 +564,7 @@ hipError_t launch_pruned_best(int n, PruneBy by, const float2* spec_p, const flo
     const int64_t pc = p - s < pmax ? p - s : pmax, npt = (pc + PT - 1) / PT, nblk = npt * nch;
     hipLaunchKernelGGL(last == 15 ? k_coarse<true> : k_coarse<false>, dim3((unsigned)((nblk + 7) / 8 * 8)), dim3(512), 0,
                        stream, (const h8*)low_p + s * FRAG, pc, (const h8*)low_l, l, npt, nblk, tc, last,
-                       ws.scores + s * l, ws.queue);
+                       ws.scores + s * l, ws.queue, ws.fill + s);
     if ((e = hipGetLastError()) != hipSuccess) return e;
   }
   if ((e = launch_library_argmax(ws.scores, p, l, best, ws.h0, stream)) != hipSuccess) return e;
@@ -538,9 +579,15 @@ hipError_t launch_pruned_best(int n, PruneBy by, const float2* spec_p, const flo
                               ws.frag, true, ws.h0, stream);
   }
   if (e != hipSuccess) return e;
-  hipLaunchKernelGGL(k_prune_select, dim3((unsigned)p), dim3(512), 0, stream, ws.scores, l, 0.125f * h * h,
-                     (const h8*)low_p, (const h8*)low_l, stat_p, stat_l, ws.h0, last_of(0.5f * h, 31), ws.cand,
-                     ws.count, ws.items, ws.queue, by == PruneBy::Fft && n != 64 ? nullptr : ws.rows);
+  // slices down to 256 templates while they leave CUs without two blocks: 11 patterns of noise against 3,000
+  // templates at 64 in whole rows 0.31 ms, in slices 0.14; 500 against 1,000 in four slices each lose 2 %
+  int slice = SLICE;
+  while (slice > 256 && p * ((l + slice - 1) / slice) < 512) slice >>= 1;
+  const int64_t ns = (l + slice - 1) / slice;
+  hipLaunchKernelGGL(k_prune_select, dim3((unsigned)(p * ns)), dim3(512), 0, stream, ws.scores, l, slice, (int)ns,
+                     0.125f * h * h, (const h8*)low_p, (const h8*)low_l, stat_p, stat_l, ws.h0, last_of(0.5f * h, 31),
+                     ws.cand, ws.count, ws.fill, ws.items, ws.queue,
+                     by == PruneBy::Fft && n != 64 ? nullptr : ws.rows, n < 160 ? 4 : 8);
   if ((e = hipGetLastError()) != hipSuccess) return e;
   const int64_t most = p * list_chunks(l);
   e = by == PruneBy::Fft
