@@ -508,20 +508,24 @@ bool prune_supported(int n, PruneBy by, int max_shift) {
   return by != PruneBy::None && even_supported(n, max_shift);
 }
 
-// From 2^13 pairs on, 2^14 at 96 and 2^15 at 64, whose full searches are cheaper.  Below that the pruned search's six
-// launches and its lists cost more than they save: a plan's call with 4,000
-// pairs 122 -> 140 us at 128, 197 -> 184 at 160 (noise 247); 8,000 pairs 174 ->
-// 157 and 298 -> 195, 116 -> 122 at 96; 16,000 pairs 174 -> 118 at 96, 262 ->
-// 147 at 128, 491 -> 191 at 160; at 64 16,000 90 -> 107, 33,000 141 -> 122 (noise
-// 241), 6,000,000 15.0 -> 1.4 ms (noise 16.8).
-// The windowed forms' own products (k_xcf_even.hip) are cheaper and their lists dearer: from 2^14 pairs on,
-// 2^15 at 64 and 2^13 at 256.  Whole calls, +-15 px, split / FP32: 17,000 pairs at 128 140 -> 129 / 198 ->
-// 135 us, 33,000 205 -> 142 / 289 -> 148; 33,000 at 64 103 -> 96 / 133 -> 99; at 256 9,000 439 -> 423 / 562
-// -> 447, 60,000 891 -> 467 / 1,301 -> 487.  Noise: 33,000 pairs at 128 205 -> 290 / 289 -> 368.
+// Below some number of pairs the pruned search's launches and its lists cost more than they save, and patterns that
+// match nothing pay for them on top of what they keep.  The lines lie where matching patterns gain what patterns of
+// noise lose or more.  Whole calls of a plan, every pair / matching / noise, in us:
+//   FFT    64: 33,000 pairs 144 / 111 / 154, 66,000 240 / 126 / 171
+//          96: 17,000 210 / 102 / 162;  128: 8,400 180 / 118 / 193, 17,000 280 / 121 / 198
+//          160: 8,400 383 / 137 / 269
+//   split  64: 33,000 104 / 98 / 126, 66,000 152 / 113 / 144;  96: 17,000 133 / 115 / 180, 33,000 170 / 129 / 200
+//          128: 33,000 189 / 142 / 260, 66,000 283 / 153 / 353;  160: 33,000 267 / 176 / 361, 66,000 399 / 189 / 524
+//          256: 8,400 491 / 364 / 617, 17,000 530 / 413 / 625
+//   FP32   64: 33,000 137 / 101 / 127;  128: 17,000 181 / 132 / 243, 33,000 256 / 146 / 305
+//          160: 17,000 262 / 162 / 349, 33,000 384 / 183 / 472;  256: 8,400 548 / 390 / 670
+// (windows of +-15 px; the split form's own products are the cheapest, its lists the dearest).
 bool prune_pays(int n, PruneBy by, int max_shift, int64_t pairs) {
   if (!prune_supported(n, by, max_shift)) return false;
-  if (by == PruneBy::Fft) return pairs >= (int64_t(1) << (n == 64 ? 15 : n == 96 ? 14 : 13));
-  return pairs >= (int64_t(1) << (n == 256 ? 13 : n == 64 ? 15 : 14));
+  int at;
+  if (by == PruneBy::Fft) at = n == 64 ? 15 : n == 96 ? 14 : 13;
+  else at = (n == 256 ? 13 : n == 96 ? 14 : 15) + (by == PruneBy::EvenSplit);
+  return pairs >= int64_t(1) << at;
 }
 
 int64_t prune_slab(int64_t p, int64_t l) {

@@ -55,7 +55,7 @@ def test_long_windowed_lists(n, p, l, form, precision, window):
 
 
 @pytest.mark.parametrize("n, p, l, form, precision", [(64, 33, 1000, 1, 0), (64, 11, 3000, 1, 0), (96, 200, 4000, 1, 0),
-                                                      (160, 8, 1100, 1, 0)])
+                                                      (160, 8, 1100, 1, 0), (128, 33, 1000, 2, 1), (160, 17, 1000, 3, 0)])
 def test_noise_costs_what_the_full_search_does(n, p, l, form, precision):
     import torch
 
