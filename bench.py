@@ -48,14 +48,15 @@ def gemm_pair_flops(n, s, precision):
     return one * (1 if precision == 3 else 3)
 
 
-# Matrix flops per pair that k_xcf_even issues: 16 x 16 tiles over the band rows in chunks of 32 and columns in
-# chunks of 16 (the last row and column of a band that fills them are added apart), with the +-u and +-s symmetries.
+# Matrix flops per pair that k_xcf_even issues: 16 x 16 tiles over the band rows in chunks of 32 and one of 16, and
+# columns in chunks of 16 (the last row and column of a band that fills them are added apart), with the +-u and +-s
+# symmetries.
 def even_pair_flops(n, s, split):
     b, st = 3 * n // 8, 1 if s < 16 else 2
-    kc, vt = b // 32 + (b % 32 != 0), b // 16 + (b % 16 != 0)
+    vt = rows16 = b // 16 + (b % 16 != 0)
     if split:
-        return vt * (kc * 12 * 16384 * st + 12 * 8192 * st * st)
-    return vt * (kc * 32 * st + 16 * st * st) * 2048
+        return vt * (rows16 * 12 * 8192 * st + 12 * 8192 * st * st)
+    return vt * (rows16 * 16 * st + 16 * st * st) * 2048
 
 
 def kernel_source_hash(prof):
@@ -647,9 +648,9 @@ def capture_sweep(tm, n_ref=8, span=30.0, step=0.5):
 
 def precision_256(tm, patterns, library, steps, window=15, sample=3, n_sub=96, fp32_steps=1):
     """The map at 256 x 256 with the search over a +-15 px window, followed by
-    the same refinement: first in FP32 (the exact windowed DFT on the vector
-    ALUs; the FFT form is not built at this size), then as split-precision
-    DFT-GEMMs on MFMA.  Per precision: patterns/s, pairs/s and the roofline of
+    the same refinement: first in FP32 (the exact windowed DFT on the FP32
+    matrix cores; the FFT form is not built at this size), then as
+    split-precision DFT-GEMMs on MFMA.  Per precision: patterns/s, pairs/s and the roofline of
     the search kernel, agreement of the best template with the FP32 search,
     accuracy against the simulated truth, and the error against the FP64
     oracle on a sample of patterns: scores over a random subset of the
@@ -845,8 +846,8 @@ def ragged_batch(tm, patterns, library, steps, sample_per_size=1):
             if found >= sample_per_size:
                 break
     res = {"workload": "ragged: %d patterns, binnings 64/96/128/160 (25%% each, shuffled), %d-orientation cubic "
-                       "library, exhaustive FFT XCF + 27-point +-0.5 deg stencil + 2-iteration refinement, one "
-                       "graph launch per step" % (P, L),
+                       "library, the pick of the exhaustive FFT XCF (templates dropped by an upper bound only) "
+                       "+ 27-point +-0.5 deg stencil + 2-iteration refinement, one graph launch per step" % (P, L),
            "patterns_per_s": P / dt, "ms_per_step": dt * 1e3, "library_pairs_per_s_whole_step": P * L / dt,
            "stencil_candidates_per_step": 27 * P, "plan_create_s_incl_autotune": t_plan,
            "tiles": plan.tiles(), "steps": steps,
@@ -994,6 +995,8 @@ def learned_proposal(tm, library, n_train, epochs, n_test, k=32, bsz=256, n=128)
                                    "indexed of 10,000 validation patterns (refined within 1 deg of the truth)",
            "validation_correctly_indexed": float(ok_val.mean()), "tau_over_all_validation": tau_all,
            "refine_s": t_rf,
+           "exhaustive_note": "the whole library, templates dropped by an upper bound of their peak only; picks as "
+                              "from every pair",
            "exhaustive": {"search_patterns_per_s": n_test / t_ex, "patterns_per_s_with_refinement":
                           n_test / (t_ex + t_rf), "pairs": n_test * library,
                           "pick_vs_truth_deg_median": float(np.median(mis_ex)),

@@ -88,10 +88,11 @@ extern "C" {
  * DFTGEMM evaluates only the shift window |s_x|, |s_y| <= max_shift
  * (max_shift >= 0 required; the window's 2 max_shift + 1 shifts are padded
  * to a multiple of 16 and must fit the on-chip constant operands).
- * DFT is the same windowed evaluation in FP32 on the vector ALUs, exactly
- * the two products of the band-limited correlation (Equations 3 and 6a at
- * the window's shifts, no split): the FP32 reference of the split forms,
- * at every supported size (max_shift >= 0, 2 max_shift + 1 <= 208). */
+ * DFT is the same windowed evaluation in FP32, exactly the two products of
+ * the band-limited correlation (Equations 3 and 6a at the window's shifts,
+ * no split): the FP32 reference of the split forms, at every supported size
+ * (max_shift >= 0, 2 max_shift + 1 <= 208; on the matrix cores up to 31, on
+ * the vector ALUs beyond). */
 #define EBSD_FORM_AUTO 0
 #define EBSD_FORM_FFT 1
 #define EBSD_FORM_DFTGEMM 2
@@ -177,9 +178,12 @@ const char* ebsd_last_error(void);
  *   best_q    float64 [P][4]  lib_q[best_idx]        (may be NULL)
  *   peak_h    float32 [P] upsampled peak height of the winner
  *   shift     float32 [P][2] upsampled (s_x, s_y) px of the winner
- *   scores    float32 [P][L] integer peak of every pair (may be NULL: large FP32
- *             searches then drop templates by an upper bound of their peak;
- *             the picks are the same)
+ *   scores    float32 [P][L] integer peak of every pair (may be NULL: large
+ *             searches in the FP32 forms and FP16X2 then drop templates by an
+ *             upper bound of their peak; the picks are the same)
+ * Scratch without `scores`: 4 bytes a pair, or where templates are dropped 9
+ * bytes a pair and 2 KB a template and pattern, at most 2^26 pairs (0.6 GB) at
+ * a time.
  */
 int ebsd_index_patterns(const ebsd_batch* pats, const ebsd_master* mp, const ebsd_geometry* geo,
                         const double* lib_q, int64_t L, const ebsd_params* prm, int32_t* best_idx,
@@ -191,7 +195,7 @@ int ebsd_index_patterns(const ebsd_batch* pats, const ebsd_master* mp, const ebs
  * and Pattern Centre Refinement", one library at the nominal pattern
  * centre).  ebsd_plan_create projects the L templates at geo's nominal
  * pattern centre and keeps their filtered band spectra, with a copy of
- * lib_q, in device memory the plan owns (L x 38 KB at n = 128, and 4 KB for
+ * lib_q, in device memory the plan owns (L x 38 KB at n = 128, and 2 KB for
  * the search's bounds); the parameters are fixed with it.  It first checks on
  * the device that every lib_q row is a unit quaternion (| |q| - 1 | <= 1e-6;
  * EBSD_E_INVALID otherwise, nothing kept) and therefore waits for `stream`
@@ -451,7 +455,9 @@ int ebsd_timing_read(double* total_ms, int64_t* launches);
  * capacity).  The chosen tiles are kept for the life of the process, keyed by
  * the device architecture, compute-unit count, size and shift window, and
  * reused by later plans.  Sizes with enough pairs for the search that drops
- * templates by a bound (see ebsd_index_patterns) run it with its fixed tile.
+ * templates by a bound (see ebsd_index_patterns) run it with its fixed tile;
+ * a plan holds that search's scratch for each such size (up to 0.6 GB), and
+ * 4 bytes a pair for the others.
  *
  * ebsd_ragged_run indexes the batch against the library (method of
  * ebsd_index_patterns, each pattern against templates projected at its own

@@ -1,4 +1,4 @@
-// Template projection, sub-pixel peak, library argmax and refinement kernels (gfx950).
+// Template projection, log-polar rotation, library argmax and refinement kernels (gfx950).
 #include "ebsd_common.hpp"
 #include "ebsd_internal.hpp"
 

@@ -117,11 +117,11 @@ __device__ __forceinline__ void form_sums(h8 ea, h8 eb, h8 xp, h8 xm, h8* ad, h8
 //   max(cos F1 + |sin F3|, cos F2 + |sin F4|)
 // over the four sign pairs.  A block holds PT patterns in LDS; each of its 8 waves takes tc templates in turn,
 // a template's 16 values per lane serving all the patterns; every phase constant stays in registers.
-// Bound by issue: 8 matrix products (about 130 cycles) and 50 vector instructions a pair.  200 x 3,000 pairs
+// Bound by issue: 8 matrix products and 60 vector instructions a pair, 43 and 83 % of the SIMD cycles.  200 x 3,000 pairs
 // take 119 us, 5,000 x 4,000 2.84 ms (7.0e9 pairs/s); with FP32 products (32 of 16x16x4) 424 us and 12.0 ms; a
 // 64 x 64 FFT search of wider low parts (|u|, |v| <= 24) ran at 4.2e8 pairs/s.  2 KB a spectrum are read once
-// per block of 32 patterns and 128 templates.  Fewer templates per wave (tc) fill the chip for few pairs: 11 x
-// 3,000 pairs 230 -> 34 us (measured on the FP32 form).
+// per block of 32 patterns and 128 templates.  Fewer templates per wave (tc) fill the chip for few pairs:
+// whole calls at 128 of 11 x 3,000 pairs 176 -> 124 us, 33 x 1,000 276 -> 134, 500 x 1,000 355 -> 268.
 // ALL: every grid point counts (last = 15), no masks between the two patterns of a step.
 template <bool ALL>
 __global__ __launch_bounds__(512, 4) void k_coarse(const h8* __restrict__ low_p, int64_t np,

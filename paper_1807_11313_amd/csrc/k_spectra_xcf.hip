@@ -1074,8 +1074,8 @@ __global__ __launch_bounds__(FLay<N>::NT, WLay<N>::MINW) void k_xcf_scoresf(cons
 // LDS (rows R2 values longer, so that a wave's 64 / R2 rows by R2 columns meet
 // distinct banks), where the statistics and the first pass read it; all of a
 // thread's loads are in flight together with the twiddles' and the window's.
-// One block's latency is what bounds it (two blocks per CU by LDS, ten
-// barriers).  4,900 images: 42 / 106 / 175 / 415 us at 64 / 96 / 128 / 160 (47 /
+// One block's latency is what bounds it (ten barriers; by LDS one block per CU
+// at 160, two at 128 and three at 96, eight at 64).  4,900 images: 42 / 106 / 175 / 415 us at 64 / 96 / 128 / 160 (47 /
 // 153 / 298 / 790 with 4-byte loads of global memory for both and the roots of
 // unity worked out per block); one image at 128 13 us with its launch (15-20).
 template <class T>

@@ -1,5 +1,5 @@
-// Correlation search as split FP16 DFT products on the matrix cores (gfx950),
-// with the +-u and +-s symmetries of the phase factors used in both stages.
+// Correlation search over a shift window as DFT products on the matrix cores (gfx950), in FP32 or in
+// split FP16, with the +-u and +-s symmetries of the phase factors used in both stages.
 //
 // For one pattern-template pair with Z = E conj(T) over the stored band
 // (u in [-B, B], v in [0, B]; w_0 = 1, w_v = 2 for the Hermitian half)
@@ -169,7 +169,8 @@ __device__ __forceinline__ void chunk_offsets(int step, int r16, int rows8, int*
 // Bound by issue: vector and matrix instructions of the waves on one SIMD hardly overlap here (128 FMAs
 // and 32 of the 16-cycle products take 1,886 cycles a pair of waves, 2,155 one after the other), so the cost of a
 // step is their sum: 80 VALU instructions to form A and D, 64 to split them, 12 products (split), or 80 and 32
-// products of 32 cycles (FP32).  The half chunk of 16 rows takes half of the vector instructions: 1,200 x 1,500 split
+// products of 32 cycles (FP32); 61 and 24 % of the cycles issue vector and matrix work at 128 split, 70 and 22 at 256,
+// 30 and 63 in FP32.  The half chunk of 16 rows takes half of the vector instructions: 1,200 x 1,500 split
 // pairs (whole calls) at 96 6.07 -> 5.27 ms, at 128 6.11 -> 5.37, at max_shift 31 12.7 -> 11.0 and 12.9 -> 10.9.
 // Measured, max_shift 15, 1,200 x 1,500 pairs at 128 and 500 x 1,500 at 256: split 3.4e8 / 1.16e8 pairs/s (complex
 // products over every u and s: 2.5e8 / 0.84e8).
@@ -563,8 +564,8 @@ hipError_t run_even(const float2* spec_p, int64_t p, const float2* spec_l, int64
 }
 
 // Patterns per block: as many as the registers of two waves per SIMD hold.  Split 2 / 3 / 4 patterns: 2.72 /
-// 3.00 / 2.56e8 pairs/s at 128, 0.98 / 1.07 / 0.92e8 at 256 (four spill); FP32 2 / 4 / 5: 1.85 / 1.99 / 1.93e8
-// and 0.66 / 0.72 / 0.68e8.  Two tiles of shifts (16 <= max_shift) take a quarter as many accumulators' patterns: one.
+// 3.00 / 2.56e8 pairs/s at 128 (before its half chunk; with it 3 take 3.35), 0.98 / 1.07 / 0.92e8 at 256 (four
+// spill); FP32 2 / 4 / 5: 1.85 / 1.99 / 1.93e8 and 0.66 / 0.72 / 0.68e8.  Two tiles of shifts (16 <= max_shift) take a quarter as many accumulators' patterns: one.
 // One, too, where the blocks of several would leave CUs without one: a block works out all of its patterns' places.
 // FP32, 4 patterns x 200 templates 63 -> 29 us at 128, 63 -> 30 at 160, 176 -> 66 at 256, x 1,000 (125 blocks of
 // four) 64 -> 42, 64 -> 44, 177 -> 113; 16 x 500 (252) 64 -> 68, 64 -> 71, 177 -> 197.  Split, 4 x 200 36 -> 29, 35 ->
