@@ -566,11 +566,14 @@ hipError_t run_even(const float2* spec_p, int64_t p, const float2* spec_l, int64
 // Patterns per block: as many as the registers of two waves per SIMD hold.  Split 2 / 3 / 4 patterns: 2.72 /
 // 3.00 / 2.56e8 pairs/s at 128 (before its half chunk; with it 3 take 3.35), 0.98 / 1.07 / 0.92e8 at 256 (four
 // spill); FP32 2 / 4 / 5: 1.85 / 1.99 / 1.93e8 and 0.66 / 0.72 / 0.68e8.  Two tiles of shifts (16 <= max_shift) take a quarter as many accumulators' patterns: one.
-// One, too, where the blocks of several would leave CUs without one: a block works out all of its patterns' places.
-// FP32, 4 patterns x 200 templates 63 -> 29 us at 128, 63 -> 30 at 160, 176 -> 66 at 256, x 1,000 (125 blocks of
-// four) 64 -> 42, 64 -> 44, 177 -> 113; 16 x 500 (252) 64 -> 68, 64 -> 71, 177 -> 197.  Split, 4 x 200 36 -> 29, 35 ->
-// 30, 61 -> 40, 4 x 1,000 (250 blocks of three) 35 -> 31, 40 -> 41, 71 -> 75, 16 x 500 (378) 52 -> 46, 65 -> 60, 114
-// -> 129, 40 x 500 (882) 94 -> 96, 120 -> 126, 225 -> 305.
+// Few blocks: a CU runs one at a time, so a search takes ceil(blocks / CUs) rounds, and what counts is rounds times
+// the time of a block.  Split blocks of 1 / 2 / 3 patterns take about 1 / 1.75 / 2.5 (64 to 160) or 1 / 1.35 / 1.75
+// (256): 16 patterns x 500 templates (1,008 / 504 / 378 blocks) 40 / 36 / 45 us at 128, 59 / 49 / 61 at 160, 128 / 91 /
+// 113 at 256; 4 x 1,000 (500 / 250 / 250) 40 / 31 / 38 at 160, 75 / 58 / 69 at 256; 40 x 500 (2,520 / 1,260 / 882) 82 /
+// 76 / 82, 125 / 106 / 117, 302 / 210 / 219; 100 x 1,000 354 / 341 / 320, 555 / 485 / 466, 1,438 / 1,010 / 900.
+// FP32 in blocks of four: one where these would leave CUs without one, as a block works out all of its patterns'
+// places: 4 patterns x 200 templates 63 -> 29 us at 128, 63 -> 30 at 160, 176 -> 66 at 256, x 1,000 (125 blocks of
+// four) 64 -> 42, 64 -> 44, 177 -> 113; 16 x 500 (252) 64 -> 68, 64 -> 71, 177 -> 197.
 template <bool SPLIT, int ST>
 constexpr int even_pb() { return ST == 2 ? 1 : SPLIT ? 3 : 4; }
 template <int N, bool SPLIT, bool DISC>
@@ -579,9 +582,20 @@ hipError_t pick_even(const float2* spec_p, int64_t p, const float2* spec_l, int6
   if (max_shift >= 16)
     return run_even<N, 2, even_pb<SPLIT, 2>(), SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
   constexpr int PB = even_pb<SPLIT, 1>();
-  if ((p + PB - 1) / PB * ((l + 7) / 8) <= (SPLIT && N < 256 ? 512 : 192) || p == 1)
+  const int64_t ntb = (l + 7) / 8;
+  if constexpr (SPLIT) {
+    const auto rounds = [p, ntb](int pb) { return ((p + pb - 1) / pb * ntb + 255) / 256; };
+    const int64_t one = 20 * rounds(1), two = (N == 256 ? 27 : 35) * rounds(2), three = (N == 256 ? 35 : 50) * rounds(3);
+    if (p > 1 && two < three && two < one)
+      return run_even<N, 1, 2, SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
+    if (p > 1 && three <= one)
+      return run_even<N, 1, PB, SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
     return run_even<N, 1, 1, SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
-  return run_even<N, 1, PB, SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
+  } else {
+    if ((p + PB - 1) / PB * ntb <= 192 || p == 1)
+      return run_even<N, 1, 1, SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
+    return run_even<N, 1, PB, SPLIT, DISC>(spec_p, p, spec_l, l, max_shift, frag, scores, stream);
+  }
 }
 
 template <int N, int ST, bool SPLIT>

@@ -86,3 +86,42 @@ def test_small_windows_cost_what_the_bf16_halves_do(n):
     print("[gpu]   n=%d: fp16x2 %.3f ms, bf16x2 %.3f ms" % (n, fp16 / 3, bf16 / 3), flush=True)
     # the same products on whole operands: measured 0.94 and 0.96 (1.08 and 1.10 with chunks of 32 rows only)
     assert fp16 < 1.03 * bf16
+
+
+@pytest.mark.parametrize("n, s", [(64, 15), (96, 15), (128, 7), (160, 15), (256, 15)])
+def test_split_blocks_of_two_and_three_equal_single_ones(n, s):
+    import torch
+
+    # the blocks that take the fewest rounds of the chip: of two (15 x 500 and 31 x 1,000, 2 x 1,539), of three (the
+    # others), with remainders of one and of two patterns
+    for p, l in ((2, 1539), (15, 500), (31, 1000), (61, 1000), (62, 1003)):
+        tm, sp, sl = _spectra(n, p, l)
+        prm = tm.params_default(max_shift=s, form=2, precision=1)
+        out = tm.xcf_scores(sp, sl, n, prm)
+        for i in {0, 1, p // 2, p - 2, p - 1}:
+            assert torch.equal(out[i:i + 1], tm.xcf_scores(sp[i:i + 1].contiguous(), sl, n, prm)), (p, i)
+
+
+def test_sixteen_patterns_fill_the_chip():
+    import torch
+
+    tm, sp, sl = _spectra(256, 48, 500)
+    prm = tm.params_default(max_shift=15, form=2, precision=1)
+
+    def cost(p):
+        best = float("inf")
+        for _ in range(7):
+            a, b = torch.cuda.Event(enable_timing=True), torch.cuda.Event(enable_timing=True)
+            a.record()
+            for _ in range(5):
+                tm.xcf_scores(sp[:p], sl, 256, prm)
+            b.record()
+            torch.cuda.synchronize()
+            best = min(best, a.elapsed_time(b))
+        return best
+
+    cost(48)
+    # 48 x 500: four full rounds of blocks of three, 222 us; 16 x 500 two of blocks of two, 91 us, but 113 of three
+    few, many = cost(16), cost(48)
+    print("[gpu]   16 x 500 %.0f us, 48 x 500 %.0f us" % (200 * few, 200 * many), flush=True)
+    assert few < 0.46 * many
